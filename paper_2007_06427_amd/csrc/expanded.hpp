@@ -27,7 +27,7 @@ namespace lo {
 
 // A and Cb from band column values v (zero outside the band): IFFT of v and of (i omega) v.
 template <int N>
-__device__ __forceinline__ void x_inverse_pair(const Shape& sh, const ColPos& p, const cd* v, const Work& w, cd* ex,
+__device__ __forceinline__ void x_inverse_pair(const Shape& sh, const ColPos<N>& p, const cd* v, const Work& w, cd* ex,
                                                const TwCache<N, ColG<N>::PT>& twc) {
     using G = ColG<N>;
     cd a[G::PT], b[G::PT];
@@ -46,9 +46,9 @@ template <int N>
 __device__ __forceinline__ void col_pass_XA(const Shape& sh, int block, const Work& w, cd* ex,
                                             const cd* __restrict__ tw) {
     using G = ColG<N>;
-    const ColPos p = col_pos<N>(sh, block);
+    const ColPos<N> p(sh, block);
     TwCache<N, G::PT> twc;
-    tw_cache_load<N, G::PT>(twc, p.t, tw);
+    tw_cache_load<N, G::PT>(twc, p.p, tw);
     const cd* u = w.U + ((size_t)p.l * sh.C + p.j) * sh.NB;
     cd v[G::PT];
 #pragma unroll
@@ -65,15 +65,13 @@ __device__ __forceinline__ void col_pass_XC(const Shape& sh, int block, const Wo
                                             int mode, double dtau, int scheme, bool fuse, cd* ex,
                                             const cd* __restrict__ tw) {
     using G = ColG<N>;
-    const ColPos p = col_pos<N>(sh, block);
+    const ColPos<N> p(sh, block);
     const size_t col = (size_t)p.l * sh.C + p.j;
-    const cd* Xc = w.BD + col * N;
     cd v[G::PT];
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) v[m] = p.active ? Xc[p.t + m * G::TPF] : cd{0.0, 0.0};
+    col_load<N>(sh, p, w.BD, v);
     TwCache<N, G::PT> twc;
-    tw_cache_load<N, G::PT>(twc, p.t, tw);
-    fft<N, G::PT, false>(v, p.t, ex + p.f * xlen<N>(), twc);
+    tw_cache_load<N, G::PT>(twc, p.p, tw);
+    fft_fwd<N, G::PT>(v, ex, twc, p.p);
     const double Tl = p.active ? Tl_[p.l] : 1.0;
     const double q = kTwoPi * p.j / sh.L;
     const double q2 = q * q, q4 = q2 * q2;
@@ -108,14 +106,27 @@ __device__ __forceinline__ void col_pass_XC(const Shape& sh, int block, const Wo
     if (fuse) x_inverse_pair<N>(sh, p, v, w, ex, twc);
 }
 
-// LDS of the row pass: the A and Cb tiles stay readable while the exchange regions (after
-// them) carry the transforms.
+// LDS of the row pass: the staged spectra of A and Cb stay readable while the exchange regions
+// (after them) carry the transforms.
 template <int M>
 struct XRowG {
     using G = RowG<M>;
-    static constexpr int EX = 2 * G::TILE;
-    static constexpr int LDS = 2 * G::TILE + G::XL;  // complex values
+    static constexpr int SR = G::up_to(2 * G::PW * G::ST, 16, G::WMOD);  // staging region per wavefront
+    static constexpr int EX = kBlock / 64 * SR;
+    static constexpr int LDS = EX + G::P * G::E::XS;  // complex values
 };
+
+// Sum over the threads of a points-side transform, in a fixed order (xor tree over its lanes).
+template <int M, int PT>
+__device__ __forceinline__ double points_sum(double x) {
+    using E = Fft<M, PT>;
+    if constexpr (E::L <= 2) {  // the lanes of k0 (L = 2) and of the radix-F digit
+        for (int o = 32; o >= 64 / E::F; o >>= 1) x += __shfl_xor(x, o, 64);
+        return E::L == 2 ? wsum_lanes(x, PT) : x;
+    } else {
+        return wsum_lanes(x, E::TPF);
+    }
+}
 
 // (i q)^n z for n = 0 .. 4
 __device__ __forceinline__ cd ipow_q(cd z, double q, int n) {
@@ -136,31 +147,35 @@ __device__ __forceinline__ void row_pass_X(const Shape& sh, int block, const Wor
     constexpr int PT = G::PT;
     const size_t nrows = (size_t)sh.nloops * sh.N;
     const size_t g0 = (size_t)block * G::ROWS;
-    const int t = threadIdx.x % G::TPF, p = threadIdx.x / G::TPF;
+    constexpr int SR = XRowG<M>::SR;
+    const FftPos<M, PT> pos(threadIdx.x);
+    const int t = pos.t;
     TwCache<M, PT> twc;
-    tw_cache_load<M, PT>(twc, t, tw);
-    cd* tA = lds;
-    cd* tS = lds + G::TILE;
-    cd* ex = lds + XRowG<M>::EX + p * xlen<M>();
+    tw_cache_load<M, PT>(twc, pos, tw);
+    cd* ex = lds + XRowG<M>::EX;
     {
         const cd* const src[2] = {w.A, w.Cb};
-        load_rows<G::ROWS, G::CMAX, G::TS, G::TILE, 2>(tA, src, g0, sh, nrows);
+        RowLoad<G, 2> ld;
+        ld.issue(src, g0, sh, nrows);
+        ld.template commit<SR>(lds);
     }
     __syncthreads();
-    const size_t ga = g0 + p, gb = g0 + G::P + p;
+    const cd* tA = lds + stage_base<G, SR>(pos.xs, 0);
+    const cd* tS = lds + stage_base<G, SR>(pos.xs, 1);
+    // the rows on this thread's points side
+    const size_t ga = g0 + pos.xt, gb = ga + G::P;
     const double ia = ga < nrows ? 1.0 / T[ga >> sh.logN] : 1.0;
     const double ib = gb < nrows ? 1.0 / T[gb >> sh.logN] : 1.0;
     const double dq = kTwoPi / sh.L;
     // values of the field (i q)^n X on rows a (real parts) and b (imaginary parts)
-    auto field = [&](const cd* tile, int n, cd* v) {
+    auto field = [&](const cd* z, int n, cd* v) {
+        row_gather<G>(z, t, v);
 #pragma unroll
         for (int m = 0; m < PT; ++m) {
             const int e = t + m * G::TPF;
-            const double q = dq * (double)((e <= M / 2) ? e : e - M);
-            const cd a = herm_ext(tile, G::TS, p, e, M, sh.Kx), b = herm_ext(tile, G::TS, G::P + p, e, M, sh.Kx);
-            v[m] = pack2(ipow_q(a, q, n), ipow_q(b, q, n));
+            v[m] = ipow_q(v[m], dq * (double)((e <= M / 2) ? e : e - M), n);
         }
-        fft<M, PT, true>(v, t, ex, twc);
+        fft_inv<M, PT>(v, ex, twc, pos);
     };
     cd u[PT], u1[PT], u2[PT], f[PT], acc[PT], r[PT];
     field(tA, 0, u);
@@ -198,11 +213,11 @@ __device__ __forceinline__ void row_pass_X(const Shape& sh, int block, const Wor
                     u[m].y * u1[m].y * u1[m].y;
     }
     // per-row sums over x, scaled by 1/(M N): finalize_loop then forms J and dJ/dT
-    ja = wsum_lanes(ja, G::TPF);
-    jb = wsum_lanes(jb, G::TPF);
-    da = wsum_lanes(da, G::TPF);
-    db = wsum_lanes(db, G::TPF);
-    if (t == 0) {
+    ja = points_sum<M, PT>(ja);
+    jb = points_sum<M, PT>(jb);
+    da = points_sum<M, PT>(da);
+    db = points_sum<M, PT>(db);
+    if (pos.n0 == 0) {
         const double s = 1.0 / ((double)M * sh.N);
         double* part = reinterpret_cast<double*>(w.G);
         if (ga < nrows) {
@@ -215,41 +230,10 @@ __device__ __forceinline__ void row_pass_X(const Shape& sh, int block, const Wor
         }
     }
     // forward transform of G_1NL (rows a + i b), split into the two rows' half spectra
-    fft<M, PT, false>(acc, t, ex, twc);
-#pragma unroll
-    for (int m = 0; m < PT; ++m) ex[xpos(t + m * G::TPF)] = acc[m];
-    wave_lds_order();
-    const int lane = threadIdx.x % 64;
-    const int pw0 = (threadIdx.x / 64) * G::PW;
-    const int nout = 2 * G::PW * sh.C;
-    const double s = 0.5 / M;
-    cd outv[G::NOUT];
-#pragma unroll
-    for (int i = 0; i < G::NOUT; ++i) {
-        const int idx = lane + 64 * i;
-        if (idx < nout) {
-            const int pp = pw0 + idx / (2 * sh.C);
-            const int rem = idx % (2 * sh.C);
-            const int j = rem % sh.C;
-            const cd* e2 = lds + XRowG<M>::EX + pp * xlen<M>();
-            const cd a = e2[xpos(j)];
-            const cd b = e2[xpos((M - j) & (M - 1))];
-            outv[i] = rem >= sh.C ? cd{(a.y + b.y) * s, (b.x - a.x) * s} : cd{(a.x + b.x) * s, (a.y - b.y) * s};
-        }
-    }
-    __syncthreads();  // every wave is done with the input tiles: the output tile overwrites tA
-#pragma unroll
-    for (int i = 0; i < G::NOUT; ++i) {
-        const int idx = lane + 64 * i;
-        if (idx < nout) {
-            const int pp = pw0 + idx / (2 * sh.C);
-            const int rem = idx % (2 * sh.C);
-            // consecutive lanes write consecutive j of one row (row b after row a)
-            lds[(rem % sh.C) * G::TS + (rem >= sh.C ? G::P + pp : pp)] = outv[i];
-        }
-    }
+    fft_fwd<M, PT>(acc, ex, twc, pos);
+    row_put<G>(lds + stage_base<G, SR>(pos.xs, 0), t, acc);  // over this wavefront's own inputs
     __syncthreads();
-    store_rows<G::ROWS, G::CMAX>(lds, G::TS, w.BD, g0, sh, nrows);
+    row_store<G, SR, false>(lds, w.BD, g0, sh, nrows);
 }
 
 }  // namespace lo

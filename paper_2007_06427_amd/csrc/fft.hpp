@@ -1,22 +1,32 @@
 // Double-precision complex FFT building blocks for gfx950 (CDNA4).
 //
-// A transform of length n = 2^p (8 <= n <= 1024) runs as a Stockham autosort sequence of
-// radix-2/4/8/16 stages on PT points per thread (PT = 8 or 16), n/PT threads per transform.
-// When n/PT <= 64 the transform lives inside one wavefront: stages exchange data through
-// that wavefront's own LDS region and need no block barrier. Longer transforms span several
-// wavefronts and synchronise with block barriers.
+// A transform of length N = F PT^L (8 <= N <= 1024, F < PT) runs on PT points per thread,
+// N/PT threads per transform: one radix-F stage and L radix-PT stages, with a re-distribution
+// between stages. Every butterfly's inputs sit in one thread's registers.
 //
-// Register convention: on entry to and exit from a transform, thread t of the transform
-// holds element t + m * (n/PT) in register slot m, for m = 0 .. PT-1. Entry and exit
-// positions are the same, so an inverse transform can hand its output to a forward
-// transform in registers. Pointwise work between the two (products, spectral assembly)
-// touches no memory.
+// A transform pair is (inverse: spectrum -> points) and (forward: points -> spectrum), each
+// the mirror of the other, so the points between them can stay in whatever order the
+// last inverse stage leaves them in:
+//   spectrum layout: thread t holds e = t + m TPF in slot m (TPF = N/PT), natural order;
+//   points layout:   slot m = k + F b of a thread holds n = n0 + TPF b + (N/F) k.
+// FftPos gives both for a thread, and which of the block's transforms it works on in each.
 //
-// Sign convention: FWD uses exp(-2 pi i), INV uses exp(+2 pi i). Neither scales.
+// Re-distribution between stages. What bounds it is the LDS write port: on MI355X a wavefront's
+// ds_write_b128 takes 14 cycles of its CU's LDS and its ds_read_b128 4.4 (a 1024-byte access at
+// about 64 and 256 bytes per cycle), so a full exchange of 8 values per lane costs about 147
+// CU cycles per wavefront, three quarters of them the writes. The radix-F stage therefore
+// re-distributes in registers: v_permlane32_swap and v_permlane16_swap exchange a register bit
+// with lane bit 5 or 4 (one instruction per pair of dwords), on the vector units of one SIMD
+// instead of the LDS that the CU's four SIMDs share. The radix-PT stages exchange
+// through LDS: a 256-point transform has one such exchange (4 x 8 x 8), a 32-point one none.
+// Against radix 8, 8, 4 with two LDS exchanges (three at 1024 points), on 64 loops of 256 x 1024:
+// pass A 29.3 -> 25.9 us, the forward pass C 46.7 -> 41.8, the reverse pass E 45.0 -> 41.0.
 //
-// LDS exchange: a transform's region holds n + n/8 complex values. Element `pos` sits at
-// pos + pos/8: one 16-byte pad every 8 elements, which makes the stride-8 and stride-16
-// scatters of the early stages free of bank conflicts on 64 banks of 4 bytes.
+// The stages between which transforms stay inside one wavefront need no block barrier
+// (the LDS performs a wavefront's operations in issue order). A 1024-point transform of 8 points
+// per thread spans two wavefronts; its first exchange crosses them, the second does not.
+//
+// Sign convention: forward uses exp(-2 pi i), inverse exp(+2 pi i). Neither scales.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -154,66 +164,119 @@ __device__ __forceinline__ void dft16(cd* v, int s0) {
     }
 }
 
-// Radix plan per length and points per thread (product = N, every radix divides PT).
-template <int N, int PT>
-struct Plan;
-template <> struct Plan<8, 8>     { static constexpr int S = 1; static constexpr int R[4] = {8, 0, 0, 0}; };
-template <> struct Plan<16, 8>    { static constexpr int S = 2; static constexpr int R[4] = {8, 2, 0, 0}; };
-template <> struct Plan<32, 8>    { static constexpr int S = 2; static constexpr int R[4] = {8, 4, 0, 0}; };
-template <> struct Plan<64, 8>    { static constexpr int S = 2; static constexpr int R[4] = {8, 8, 0, 0}; };
-template <> struct Plan<128, 8>   { static constexpr int S = 3; static constexpr int R[4] = {8, 8, 2, 0}; };
-template <> struct Plan<256, 8>   { static constexpr int S = 3; static constexpr int R[4] = {8, 8, 4, 0}; };
-template <> struct Plan<512, 8>   { static constexpr int S = 3; static constexpr int R[4] = {8, 8, 8, 0}; };
-template <> struct Plan<1024, 8>  { static constexpr int S = 4; static constexpr int R[4] = {8, 8, 8, 2}; };
-template <> struct Plan<1024, 16> { static constexpr int S = 3; static constexpr int R[4] = {16, 8, 8, 0}; };
-// Four points per thread (short row transforms spread over more threads).
-template <> struct Plan<8, 4>     { static constexpr int S = 2; static constexpr int R[4] = {4, 2, 0, 0}; };
-template <> struct Plan<16, 4>    { static constexpr int S = 2; static constexpr int R[4] = {4, 4, 0, 0}; };
-template <> struct Plan<32, 4>    { static constexpr int S = 3; static constexpr int R[4] = {4, 4, 2, 0}; };
-template <> struct Plan<64, 4>    { static constexpr int S = 3; static constexpr int R[4] = {4, 4, 4, 0}; };
+// Exact base-2 logarithm of a power of two.
+constexpr int ilog2(int n) { return n <= 1 ? 0 : 1 + ilog2(n / 2); }
 
-template <int N>
-constexpr int xlen() {  // padded exchange length
-    return N + N / 8;
-}
-__device__ __forceinline__ int xpos(int pos) { return pos + (pos >> 3); }
-
-// Per-thread twiddle cache. In stage s (radix R, span NS) butterfly i of thread t needs
-// w^(k r), r = 1 .. R-1, with w = exp(-2 pi i / (NS R)) and k = (t + i N/PT) mod NS. These
-// depend only on t, so a thread loads them once and reuses them for every transform it runs.
-// Per butterfly the cache holds w^k, w^2k, w^4k (and w^8k for radix 16) as read from the
-// table, and the other powers are formed by one or two complex products: w^3k =
-// w^k w^2k, w^5k = w^k w^4k, w^6k = w^2k w^4k, w^7k = w^3k w^4k, and for radix 16
-// w^(8k + m) = w^8k w^(mk). Each twiddle is within a few units in the last place. The
-// inverse transform uses the conjugates.
-template <int N, int PT>
-struct TwCache {
-    static constexpr int NBASE = 4;                  // base powers kept per butterfly
-    static constexpr int MAXNB = PT / 2;             // butterflies per thread in a radix-2 stage
-    cd w[4][MAXNB][NBASE];                           // [stage][butterfly][1, 2, 4, 8]
+// XLOW: neighbouring lanes of a wavefront work on different transforms (lane = x + XPW t)
+// instead of on neighbouring values of one. For transforms that read and write arrays whose
+// fastest index is the transform (rows of an array held column by column in LDS).
+template <int N, int PT, bool XLOW = false>
+struct Fft {
+    static constexpr int LP = ilog2(PT), LN = ilog2(N);
+    static constexpr int L = LN / LP;         // radix-PT stages
+    static constexpr int LF = LN % LP;        // log2 of the radix of the remaining stage
+    static constexpr int F = 1 << LF;
+    static constexpr int TPF = N / PT;        // threads per transform
+    static constexpr int XPW = TPF >= 64 ? 1 : 64 / TPF;  // transforms per wavefront
+    static constexpr bool TWO_WAVES = TPF == 128;
+    static_assert(F <= 4 && L >= 1 && L <= 3 && TPF <= 128, "no plan for this length");
+    static_assert(L < 3 || F == 1 || TWO_WAVES, "three exchanged stages: one wavefront or two");
+    // Strides of the exchange layouts. A b128 access is served 16 lanes at a time on 64 banks
+    // of 4 bytes, so 16 consecutive lanes should fall on 16 different 16-byte slots modulo 16:
+    // the strides are chosen for that in both directions of each exchange.
+    static constexpr int KS = L == 2 ? TPF + 1 : (TWO_WAVES ? 64 : TPF) + 16 / PT;
+    static constexpr int K1 = TWO_WAVES ? 2 * PT + 1 : PT + 1;  // first exchange of three stages
+    static constexpr int X1 = PT * PT * K1, X2 = (TWO_WAVES ? 2 : 1) * PT * KS;
+    // complex values of exchange space per transform (at least N, for other uses of the region)
+    static constexpr int XS = L == 1 ? N + 1 : L == 2 ? PT * KS + (XLOW ? 16 / XPW : 0) : (X1 > X2 ? X1 : X2);
 };
 
-template <int N, int PT, int S, int NS>
-__device__ __forceinline__ void tw_cache_fill(TwCache<N, PT>& c, int t, const cd* __restrict__ tw) {
-    constexpr int R = Plan<N, PT>::R[S];
-    if constexpr (NS > 1) {
-        constexpr int NB = PT / R;
-        constexpr int step = TW_N / (NS * R);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const int k = (t + i * (N / PT)) % NS;
-            c.w[S][i][0] = tw[(k * step) & (TW_N - 1)];
-            if constexpr (R >= 4) c.w[S][i][1] = tw[(2 * k * step) & (TW_N - 1)];
-            if constexpr (R >= 8) c.w[S][i][2] = tw[(4 * k * step) & (TW_N - 1)];
-            if constexpr (R >= 16) c.w[S][i][3] = tw[(8 * k * step) & (TW_N - 1)];
+// Where a thread of a block stands. xs, t: transform and position in the spectrum layout;
+// xt, n0: transform and first point in the points layout.
+template <int N, int PT, bool XLOW = false>
+struct FftPos {
+    using E = Fft<N, PT, XLOW>;
+    int xs, t, xt, n0;
+    int k0, k1, f0, f1;  // digits of the exchanges (f1: with f0, for two wavefronts)
+    __device__ __forceinline__ explicit FftPos(int tid) {
+        const int lane = tid % 64, wave = tid / 64;
+        k0 = k1 = f0 = f1 = 0;
+        if constexpr (E::L == 1) {
+            f0 = lane / (64 / E::F);
+            xs = xt = wave * (64 / E::F) + lane % (64 / E::F);
+            t = n0 = f0;
+        } else if constexpr (E::TWO_WAVES) {
+            // points: lane bits k0 (3), low bits of k1 (2), f0; wavefront: top bit of k1.
+            // spectrum: lane bits f0, low bits of f1 (2), f2 (3); wavefront: top bit of f1.
+            const int w = wave & 1;
+            xs = xt = wave >> 1;
+            k0 = lane & 7;
+            k1 = ((lane >> 3) & 3) + 4 * w;
+            f0 = lane >> 5;
+            n0 = k0 + 8 * k1 + 64 * f0;
+            f1 = (lane >> 3) + 8 * w;  // between the exchanges: lane bits k0 (3), f0, f1 (2)
+            t = (lane & 7) + 8 * w + 16 * (lane >> 3);
+        } else if constexpr (E::L == 2) {
+            constexpr int X = E::XPW;
+            const int in = XLOW ? lane / X : lane;  // lane without the low transform bits
+            k0 = in % PT;
+            const int rest = in / PT;
+            f0 = XLOW ? rest : rest / X;
+            xt = wave * X + (XLOW ? lane % X : rest % X);
+            n0 = k0 + PT * f0;
+            xs = wave * X + (XLOW ? lane % X : lane / E::TPF);
+            t = XLOW ? in : lane % E::TPF;
+        } else {
+            static_assert(E::F == 1 && !XLOW, "");
+            xs = xt = tid / E::TPF;
+            t = n0 = tid % E::TPF;
+            k0 = t % PT;
+            k1 = f1 = t / PT;
         }
     }
-    if constexpr (S + 1 < Plan<N, PT>::S) tw_cache_fill<N, PT, S + 1, NS * R>(c, t, tw);
+    // point held in slot m
+    __device__ __forceinline__ int point(int m) const {
+        return n0 + E::TPF * (m / E::F) + (N / E::F) * (m % E::F);
+    }
+};
+
+// Per-thread twiddle cache. Stage i (1 .. L, after the radix-F stage) multiplies its input m by
+// w^m with w = exp(-2 pi i t_i / (F PT^i)), t_i the position in the spectrum of the stages
+// before it. These depend only on the thread, so it loads them once and reuses them for
+// every transform it runs. The cache holds w, w^2, w^4 (and w^8) as read from the table, and
+// the other powers are formed by one or two complex products, each within a few units in the
+// last place. The inverse transform uses the conjugates, after its butterflies.
+template <int N, int PT>
+struct TwCache {
+    static constexpr int NB = ilog2(PT);
+    static constexpr int L = Fft<N, PT>::L;
+    cd w[L][NB];
+};
+
+// Table entries of stage i, whose input spectrum positions run over [0, F PT^(i-1)).
+template <int N, int PT, int I, class Pos>
+__device__ __forceinline__ void tw_cache_fill(TwCache<N, PT>& c, const Pos& p, const cd* __restrict__ tw) {
+    using E = Fft<N, PT>;
+    constexpr int span = I == 1 ? E::F : I == 2 ? E::F * PT : E::F * PT * PT;
+    if constexpr (span > 1) {
+        constexpr int step = TW_N / (span * PT);
+        int ti;
+        if constexpr (I == E::L) {
+            ti = p.t;
+        } else if constexpr (I == 1) {
+            ti = p.f0;
+        } else {
+            ti = p.f1;  // the middle stage of three
+        }
+#pragma unroll
+        for (int b = 0; b < TwCache<N, PT>::NB; ++b) c.w[I - 1][b] = tw[((ti << b) * step) & (TW_N - 1)];
+    }
+    if constexpr (I < E::L) tw_cache_fill<N, PT, I + 1>(c, p, tw);
 }
 
-template <int N, int PT>
-__device__ __forceinline__ void tw_cache_load(TwCache<N, PT>& c, int t, const cd* __restrict__ tw) {
-    tw_cache_fill<N, PT, 0, 1>(c, t, tw);
+template <int N, int PT, class Pos>
+__device__ __forceinline__ void tw_cache_load(TwCache<N, PT>& c, const Pos& p, const cd* __restrict__ tw) {
+    tw_cache_fill<N, PT, 1>(c, p, tw);
 }
 
 // An opaque copy of a cached twiddle: products formed from it are not merged with products
@@ -265,8 +328,8 @@ __device__ __forceinline__ void apply_twiddles(cd* v, int i, const cd* base) {
 // moves across this point. Read results are waited for where they are used.
 __device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
 
-// Ordering between stages: wavefront order when the transform fits in one wavefront,
-// otherwise a block barrier (every thread of the block then runs the same transform code).
+// Ordering between the threads of one transform: wavefront order when it fits in one
+// wavefront, otherwise a block barrier (every thread of the block then runs the same code).
 template <int TPF>
 __device__ __forceinline__ void xsync() {
     if constexpr (TPF <= 64) {
@@ -276,70 +339,145 @@ __device__ __forceinline__ void xsync() {
     }
 }
 
-// One Stockham stage: radix R, span NS (product of earlier radices), for thread t.
-// Butterfly i of the thread is b = t + i * (N/PT); its element r lives in slot i + r * (PT/R).
-template <int N, int PT, int S, int R, int NS, bool INV>
-__device__ __forceinline__ void compute_stage(cd* v, const TwCache<N, PT>& c) {
-    constexpr int NB = PT / R;
+template <int PT, bool INV>
+__device__ __forceinline__ void dft_pt(cd* v) {
+    if constexpr (PT == 16) {
+        dft16<INV, 1>(v, 0);
+    } else if constexpr (PT == 8) {
+        dft8<INV>(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]);
+    } else {
+        dft4<INV>(v[0], v[1], v[2], v[3]);
+    }
+}
+
+// Radix-F butterflies over the low bits of the slot index.
+template <int PT, int F, bool INV>
+__device__ __forceinline__ void dft_f(cd* v) {
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        if constexpr (NS > 1) apply_twiddles<R, NB, INV>(v, i, c.w[S][i]);
-        if constexpr (R == 16) {
-            dft16<INV, NB>(v, i);
-        } else if constexpr (R == 8) {
-            dft8<INV>(v[i], v[i + NB], v[i + 2 * NB], v[i + 3 * NB], v[i + 4 * NB], v[i + 5 * NB], v[i + 6 * NB],
-                      v[i + 7 * NB]);
-        } else if constexpr (R == 4) {
-            dft4<INV>(v[i], v[i + NB], v[i + 2 * NB], v[i + 3 * NB]);
-        } else {
-            dft2<INV>(v[i], v[i + NB]);
+    for (int b = 0; b < PT; b += F) {
+        if constexpr (F == 4) dft4<INV>(v[b], v[b + 1], v[b + 2], v[b + 3]);
+        if constexpr (F == 2) dft2<INV>(v[b], v[b + 1]);
+    }
+}
+
+// Exchange of a register bit with lane bit 5 (W = 32) or 4 (W = 16): lanes whose bit is clear
+// keep a and receive their partner's a in b; the others keep b and receive their partner's b
+// in a.
+template <int W>
+__device__ __forceinline__ void swap_dword(unsigned& a, unsigned& b) {
+    auto r = W == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false)
+                     : __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+template <int W>
+__device__ __forceinline__ void swap_lane_bit(cd& a, cd& b) {
+    unsigned u[4], v[4];
+    __builtin_memcpy(u, &a, sizeof(cd));
+    __builtin_memcpy(v, &b, sizeof(cd));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) swap_dword<W>(u[i], v[i]);
+    __builtin_memcpy(&a, u, sizeof(cd));
+    __builtin_memcpy(&b, v, sizeof(cd));
+}
+// The low bits of the slot index (F values) against the top lane bits; its own inverse.
+template <int PT, int F>
+__device__ __forceinline__ void swap_f(cd* v) {
+#pragma unroll
+    for (int b = 0; b < PT; b += F) {
+        if constexpr (F == 4) {
+            swap_lane_bit<16>(v[b], v[b + 1]);
+            swap_lane_bit<16>(v[b + 2], v[b + 3]);
+            swap_lane_bit<32>(v[b], v[b + 2]);
+            swap_lane_bit<32>(v[b + 1], v[b + 3]);
         }
+        if constexpr (F == 2) swap_lane_bit<32>(v[b], v[b + 1]);
     }
 }
 
-template <int N, int PT, int R, int NS>
-__device__ __forceinline__ void write_stage_outputs(const cd* v, int t, cd* ex) {
-    constexpr int NB = PT / R;
+// Exchange S (1 .. L-1) between radix-PT stages S and S + 1 through ex, the exchange space of
+// the block's transforms (XS values each). Forward: slot = digit f_S in, digit k_(L-1-S) out.
+template <int N, int PT, bool XLOW, int S, bool FWD, class Pos>
+__device__ __forceinline__ void exchange(cd* v, cd* ex, const Pos& p) {
+    using E = Fft<N, PT, XLOW>;
+    // slot of (points-side thread, its register m) and of (spectrum-side thread, its register m)
+    auto near_pts = [&](int m) {
+        if constexpr (E::L == 2) return p.xt * E::XS + p.k0 * E::KS + p.f0 + E::F * m;
+        if constexpr (E::TWO_WAVES && S == 1) return p.xt * E::XS + p.k0 + 8 * (p.k1 * E::K1 + p.f0 + 2 * m);
+        if constexpr (E::TWO_WAVES && S == 2) {
+            const int w = p.f1 >> 3;
+            return p.xt * E::XS + (w * PT + p.k0) * E::KS + (p.f1 & 7) + 8 * m;
+        }
+        if constexpr (S == 1) return p.xt * E::XS + p.k0 + PT * (p.k1 * E::K1 + m);
+        return p.xt * E::XS + p.k0 * E::KS + p.f1 + PT * m;
+    };
+    auto near_spec = [&](int m) {
+        if constexpr (E::L == 2) return p.xs * E::XS + m * E::KS + p.t;
+        if constexpr (E::TWO_WAVES && S == 1) {
+            return p.xt * E::XS + p.k0 + 8 * (m * E::K1 + p.f1);
+        }
+        if constexpr (E::TWO_WAVES && S == 2) {
+            const int w = p.f1 >> 3;
+            return p.xt * E::XS + (w * PT + m) * E::KS + p.k0 + 8 * (p.f1 & 7);
+        }
+        if constexpr (S == 1) return p.xt * E::XS + p.k0 + PT * (m * E::K1 + p.f1);
+        return p.xs * E::XS + m * E::KS + p.t;
+    };
+    constexpr bool CROSS = E::TWO_WAVES && S == 1;  // the two wavefronts of a transform exchange
+    if constexpr (CROSS) __syncthreads();           // the other wavefront may still read its part
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        const int b = t + i * (N / PT);
-        const int base = (b / NS) * NS * R + (b % NS);
+    for (int m = 0; m < PT; ++m) ex[FWD ? near_pts(m) : near_spec(m)] = v[m];
+    if constexpr (CROSS) __syncthreads();
+    else wave_lds_order();
 #pragma unroll
-        for (int r = 0; r < R; ++r) ex[xpos(base + r * NS)] = v[i + r * NB];
+    for (int m = 0; m < PT; ++m) v[m] = ex[FWD ? near_spec(m) : near_pts(m)];
+    if constexpr (CROSS) __syncthreads();
+    else wave_lds_order();
+}
+
+// Forward transform, points layout in, spectrum layout out. All threads of a wavefront (of
+// the block, for transforms of two wavefronts) must call; ex: the block's exchange space.
+template <int N, int PT, bool XLOW = false>
+__device__ __forceinline__ void fft_fwd(cd* v, cd* ex, const TwCache<N, PT>& c, const FftPos<N, PT, XLOW>& p) {
+    using E = Fft<N, PT, XLOW>;
+    if constexpr (E::F > 1) {
+        dft_f<PT, E::F, false>(v);
+        swap_f<PT, E::F>(v);
+        apply_twiddles<PT, 1, false>(v, 0, c.w[0]);
+    }
+    dft_pt<PT, false>(v);
+    if constexpr (E::L >= 2) {
+        exchange<N, PT, XLOW, 1, true>(v, ex, p);
+        apply_twiddles<PT, 1, false>(v, 0, c.w[1]);
+        dft_pt<PT, false>(v);
+    }
+    if constexpr (E::L >= 3) {
+        exchange<N, PT, XLOW, 2, true>(v, ex, p);
+        apply_twiddles<PT, 1, false>(v, 0, c.w[2]);
+        dft_pt<PT, false>(v);
     }
 }
 
-template <int N, int PT, int R>
-__device__ __forceinline__ void read_stage_inputs(cd* v, int t, const cd* ex) {
-    constexpr int NB = PT / R;
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        const int b = t + i * (N / PT);
-#pragma unroll
-        for (int r = 0; r < R; ++r) v[i + r * NB] = ex[xpos(b + r * (N / R))];
+// Inverse transform, spectrum layout in, points layout out.
+template <int N, int PT, bool XLOW = false>
+__device__ __forceinline__ void fft_inv(cd* v, cd* ex, const TwCache<N, PT>& c, const FftPos<N, PT, XLOW>& p) {
+    using E = Fft<N, PT, XLOW>;
+    dft_pt<PT, true>(v);
+    if constexpr (E::L >= 3) {
+        apply_twiddles<PT, 1, true>(v, 0, c.w[2]);
+        exchange<N, PT, XLOW, 2, false>(v, ex, p);
+        dft_pt<PT, true>(v);
     }
-}
-
-template <int N, int PT, bool INV, int S, int NS>
-__device__ __forceinline__ void run_stages(cd* v, int t, cd* ex, const TwCache<N, PT>& c) {
-    constexpr int R = Plan<N, PT>::R[S];
-    if constexpr (S > 0) {
-        constexpr int Rp = Plan<N, PT>::R[S - 1];
-        write_stage_outputs<N, PT, Rp, NS / Rp>(v, t, ex);
-        xsync<N / PT>();
-        read_stage_inputs<N, PT, R>(v, t, ex);
-        xsync<N / PT>();
+    if constexpr (E::L >= 2) {
+        apply_twiddles<PT, 1, true>(v, 0, c.w[1]);
+        exchange<N, PT, XLOW, 1, false>(v, ex, p);
+        dft_pt<PT, true>(v);
     }
-    compute_stage<N, PT, S, R, NS, INV>(v, c);
-    if constexpr (S + 1 < Plan<N, PT>::S) run_stages<N, PT, INV, S + 1, NS * R>(v, t, ex, c);
-}
-
-// Full length-N transform of the values in v (see the register convention above). All
-// threads of the transform must be in the calling wavefront; ex is the transform's own
-// exchange region of xlen<N>() values.
-template <int N, int PT, bool INV>
-__device__ __forceinline__ void fft(cd* v, int t, cd* ex, const TwCache<N, PT>& c) {
-    run_stages<N, PT, INV, 0, 1>(v, t, ex, c);
+    if constexpr (E::F > 1) {
+        apply_twiddles<PT, 1, true>(v, 0, c.w[0]);
+        swap_f<PT, E::F>(v);
+        dft_f<PT, E::F, true>(v);
+    }
 }
 
 }  // namespace lo

@@ -778,6 +778,7 @@ __global__ __launch_bounds__(kBlock, (ResG<M, N>::BLOCKS_PER_CU)) void k_residen
     const int l = blockIdx.x;
     Shape s1 = sh;
     s1.nloops = 1;
+    s1.ld = R::LD;
     Work w{};
     w.A = A;
     w.BD = X;
@@ -1013,6 +1014,7 @@ Shape make_shape(double L, int Nx, int Ns, int nloops) {
     s.NB = 2 * s.Ks + 1;
     s.logN = 0;
     while ((1 << s.logN) < Ns) ++s.logN;
+    s.ld = Ns;
     s.nloops = nloops;
     s.L = L;
     return s;
@@ -1452,21 +1454,14 @@ int row_tiles(const Shape& s) {
     const int rows = 4096 / s.M;
     return (s.N + rows - 1) / rows;
 }
-size_t pass_lds_bytes(const Shape& s) {
-    const size_t col = (size_t)col_per_block(s.N) * (s.N + s.N / 8);  // F columns of N + N/8 values
-    const int rows = 4096 / s.M, cmax = (s.M - 1) / 3 + 1;
-    // two input tiles, or the exchange regions: kBlock / (M/8) pairs of 9M/8 values (rows <= 512)
-    const size_t row = std::max<size_t>(2 * (size_t)cmax * (rows + 1), (size_t)kBlock * 9);
-    return std::max(col, row) * sizeof(cd);
-}
 // Dynamic LDS of one pass of the launch-per-pass form for a loop of this shape (row passes:
-// with 8 or 4 points per thread).
-size_t rag_lds_bytes(const Shape& s, int pass, int pt) {
+// with 8 or 4 points per thread, or with raw tiles copied by the load unit).
+size_t rag_lds_bytes(const Shape& s, int pass, const RagVariant& v) {
     size_t n = 0;
     auto row = [&](auto c) {
         constexpr int M_ = decltype(c)::value;
         if constexpr (M_ <= 64) {
-            if (pt == 4) {
+            if (v.pt == 4) {
                 using G = RowG<M_, 4>;
                 n = pass == PASS_B ? G::LDS_B : G::LDS;
                 return;
@@ -1474,6 +1469,7 @@ size_t rag_lds_bytes(const Shape& s, int pass, int pt) {
         }
         using G = RowG<M_>;
         n = pass == PASS_B ? G::LDS_B : G::LDS;
+        if (v.dma) n = std::max<size_t>(n, (pass == PASS_B ? 1 : 2) * (size_t)G::TILE);
     };
     auto col = [&](auto c) { n = ColG<decltype(c)::value>::LDS; };
     if (is_row_pass(pass))
@@ -1481,6 +1477,10 @@ size_t rag_lds_bytes(const Shape& s, int pass, int pt) {
     else
         host_size_switch<8, 1024>(s.N, col);
     return n * sizeof(cd);
+}
+// Dynamic LDS of the persistent kernel, which runs every pass.
+size_t pass_lds_bytes(const Shape& s) {
+    return std::max(rag_lds_bytes(s, PASS_D, rag_variant(PASS_D, 0)), rag_lds_bytes(s, PASS_C, rag_variant(PASS_C, 0)));
 }
 bool rag_covers(const BatchPlan* p, int pass, int v) {
     if (v < 0 || v >= rag_count(pass)) return false;
@@ -2129,7 +2129,7 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
         for (int pass = PASS_A; pass <= PASS_E; ++pass)
             for (int v = 0; v < rag_count(pass); ++v)
                 p->pass_lds[pass][v] =
-                    std::max(p->pass_lds[pass][v], rag_lds_bytes(b.sh, pass, rag_variant(pass, v).pt));
+                    std::max(p->pass_lds[pass][v], rag_lds_bytes(b.sh, pass, rag_variant(pass, v)));
         p->min_m = std::min(p->min_m, b.sh.M);
         p->max_m = std::max(p->max_m, b.sh.M);
         p->min_n = std::min(p->min_n, b.sh.N);

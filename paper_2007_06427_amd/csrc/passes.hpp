@@ -63,6 +63,7 @@ struct Shape {
     int C;       // Kx + 1 retained columns
     int NB;      // 2 Ks + 1 retained temporal modes
     int logN;    // log2(N)
+    int ld;      // elements from one column of an intermediate to the next (N; N + 1 in LDS)
     int nloops;
     double L;
 };
@@ -115,11 +116,11 @@ __device__ __forceinline__ double wsum_lanes(double x, int width) {
 }
 
 // ---------------------------------------------------------------------------- column passes
-// TPF = N/PT threads per column transform, F = kBlock / TPF columns per block, thread
-// tid -> t = tid % TPF (position within the transform), f = tid / TPF (column in block).
-// Column c = block * F + f runs over nloops * C columns, loop-major. Every column length takes
-// 8 points per thread: a 1024-point column spans two wavefronts (radix 8, 8, 8, 2, block
-// barriers between stages). 16 points per thread, one wavefront per column and two exchanges,
+// TPF = N/PT threads per column transform, F = kBlock / TPF columns per block, each thread's
+// columns and positions from FftPos (its spectrum side: column js, band values at t + m TPF; its
+// points side: column jt, s-grid points point(m)). Column c = block * F + f runs over
+// nloops * C columns, loop-major. Every column length takes 8 points per thread: a
+// 1024-point column spans two wavefronts. 16 points per thread, one wavefront per column,
 // measured slower on 64 loops of 256 x 1024 (pass C 57.8 against 52.8 us, the reverse pass's
 // column pass 79.9 against 73.9 us): the LDS of a column is the same, so a CU holds the same
 // columns, on half the wavefronts.
@@ -131,18 +132,26 @@ struct ColG {
     static constexpr int PT = col_pt(N);
     static constexpr int TPF = N / PT;
     static constexpr int F = kBlock / TPF;
-    static constexpr int LDS = F * xlen<N>();  // complex values of exchange space per block
+    static constexpr int LDS = F * Fft<N, PT>::XS;  // complex values of exchange space per block
 };
 
-// Per-column sum over the TPF threads of each transform, in a fixed order. Within a
-// wavefront this is an xor tree. A transform that spans two wavefronts adds the two
+// Per-column sum over the TPF threads of each transform (spectrum side), in a fixed order.
+// Within a wavefront this is an xor tree. A transform that spans two wavefronts adds the two
 // wavefront sums through `red` (2 kBlock/64 doubles of LDS), lower wavefront first.
-template <int TPF>
+template <int N>
 __device__ __forceinline__ void col_sum2(double& a, double& b, double* red) {
-    a = wsum_lanes(a, TPF < 64 ? TPF : 64);
-    b = wsum_lanes(b, TPF < 64 ? TPF : 64);
-    if constexpr (TPF > 64) {
-        static_assert(TPF == 128, "transforms span at most two wavefronts");
+    using G = ColG<N>;
+    if constexpr (Fft<N, G::PT>::L == 1) {  // a transform's threads are the lanes equal modulo 64 / TPF
+        for (int o = 32; o >= 64 / G::TPF; o >>= 1) {
+            a += __shfl_xor(a, o, 64);
+            b += __shfl_xor(b, o, 64);
+        }
+    } else {
+        a = wsum_lanes(a, G::TPF < 64 ? G::TPF : 64);
+        b = wsum_lanes(b, G::TPF < 64 ? G::TPF : 64);
+    }
+    if constexpr (G::TPF > 64) {
+        static_assert(G::TPF == 128, "transforms span at most two wavefronts");
         const int wave = threadIdx.x / 64;
         if (threadIdx.x % 64 == 0) {
             red[2 * wave] = a;
@@ -156,29 +165,32 @@ __device__ __forceinline__ void col_sum2(double& a, double& b, double* red) {
     }
 }
 
-struct ColPos {
-    bool active;
-    int l, j, t, f;
-};
-
+// The columns of a thread. Spectrum side: active, loop l, column j, position t. Points side:
+// whether its column exists, and the column's first point within the thread's slots.
 template <int N>
-__device__ __forceinline__ ColPos col_pos(const Shape& sh, int block) {
+struct ColPos {
     using G = ColG<N>;
-    ColPos p;
-    p.t = threadIdx.x % G::TPF;
-    p.f = threadIdx.x / G::TPF;
-    const int c = block * G::F + p.f;
-    p.active = c < sh.nloops * sh.C;
-    p.l = p.active ? c / sh.C : 0;
-    p.j = p.active ? c % sh.C : 0;
-    return p;
-}
+    FftPos<N, G::PT> p;
+    bool active, active_t;
+    int l, j, t;
+    size_t col_t;  // column index of the points side
+    __device__ __forceinline__ ColPos(const Shape& sh, int block) : p(threadIdx.x) {
+        const int c = block * G::F + p.xs, n = sh.nloops * sh.C;
+        t = p.t;
+        active = c < n;
+        l = active ? c / sh.C : 0;
+        j = active ? c % sh.C : 0;
+        const int ct = block * G::F + p.xt;
+        active_t = ct < n;
+        col_t = active_t ? ct : 0;
+    }
+};
 
 // The band values of this thread's slots of column (l, j) (zero outside the band or for an
 // inactive column), read through band_get. Column passes issue these loads before their
 // transforms, so that their latency overlaps the transform instead of following it.
 template <int N>
-__device__ __forceinline__ void band_prefetch(const Shape& sh, const ColPos& p, const cd* u, int herm0,
+__device__ __forceinline__ void band_prefetch(const Shape& sh, const ColPos<N>& p, const cd* u, int herm0,
                                               cd* out) {
     using G = ColG<N>;
 #pragma unroll
@@ -188,16 +200,25 @@ __device__ __forceinline__ void band_prefetch(const Shape& sh, const ColPos& p, 
     }
 }
 
+// The s-grid values of this thread's slots of its points-side column of X.
+template <int N>
+__device__ __forceinline__ void col_load(const Shape& sh, const ColPos<N>& p, const cd* X, cd* v) {
+    using G = ColG<N>;
+    const cd* x = X + p.col_t * sh.ld;
+#pragma unroll
+    for (int m = 0; m < G::PT; ++m) v[m] = p.active_t ? x[p.p.point(m)] : cd{0.0, 0.0};
+}
+
 // Inverse s-transform of band column values v (already zero outside the band) into X.
 template <int N>
-__device__ __forceinline__ void col_inverse_store(const Shape& sh, const ColPos& p, cd* v, cd* X, cd* ex,
+__device__ __forceinline__ void col_inverse_store(const Shape& sh, const ColPos<N>& p, cd* v, cd* X, cd* ex,
                                                   const TwCache<N, ColG<N>::PT>& twc) {
     using G = ColG<N>;
-    fft<N, G::PT, true>(v, p.t, ex + p.f * xlen<N>(), twc);
-    if (p.active) {
-        cd* x = X + ((size_t)p.l * sh.C + p.j) * N;
+    fft_inv<N, G::PT>(v, ex, twc, p.p);
+    if (p.active_t) {
+        cd* x = X + p.col_t * sh.ld;
 #pragma unroll
-        for (int m = 0; m < G::PT; ++m) x[p.t + m * G::TPF] = v[m];
+        for (int m = 0; m < G::PT; ++m) x[p.p.point(m)] = v[m];
     }
 }
 
@@ -205,16 +226,12 @@ template <int N>
 __device__ __forceinline__ void col_pass_A(const Shape& sh, int block, const Work& w, cd* ex,
                                            const cd* __restrict__ tw) {
     using G = ColG<N>;
-    const ColPos p = col_pos<N>(sh, block);
+    const ColPos<N> p(sh, block);
     TwCache<N, G::PT> twc;
-    tw_cache_load<N, G::PT>(twc, p.t, tw);
+    tw_cache_load<N, G::PT>(twc, p.p, tw);
     const cd* u = w.U + ((size_t)p.l * sh.C + p.j) * sh.NB;
     cd v[G::PT];
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) {
-        const int kk = band_row(p.t + m * G::TPF, N, sh.Ks);
-        v[m] = (p.active && kk >= 0) ? band_get(u, p.j, kk, sh.NB, w.herm0) : cd{0.0, 0.0};
-    }
+    band_prefetch<N>(sh, p, u, w.herm0, v);
     col_inverse_store<N>(sh, p, v, w.A, ex, twc);
 }
 
@@ -226,9 +243,9 @@ template <int N, bool WITH_U = true>
 __device__ __forceinline__ void col_pass_AC(const Shape& sh, int block, const Work& w, cd* ex,
                                             const cd* __restrict__ tw) {
     using G = ColG<N>;
-    const ColPos p = col_pos<N>(sh, block);
+    const ColPos<N> p(sh, block);
     TwCache<N, G::PT> twc;
-    tw_cache_load<N, G::PT>(twc, p.t, tw);
+    tw_cache_load<N, G::PT>(twc, p.p, tw);
     const size_t col = (size_t)p.l * sh.C + p.j;
     const cd* r = w.R + col * sh.NB;
     const double q = kTwoPi * p.j / sh.L;
@@ -248,16 +265,14 @@ __device__ __forceinline__ void col_pass_C(const Shape& sh, int block, const dou
                                            int mode, double dtau, int scheme, cd* ex, double* red,
                                            const cd* __restrict__ tw) {
     using G = ColG<N>;
-    const ColPos p = col_pos<N>(sh, block);
+    const ColPos<N> p(sh, block);
     const size_t col = (size_t)p.l * sh.C + p.j;
-    const cd* Bc = w.BD + col * N;
     cd v[G::PT], ub[G::PT];
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) v[m] = p.active ? Bc[p.t + m * G::TPF] : cd{0.0, 0.0};
+    col_load<N>(sh, p, w.BD, v);
     band_prefetch<N>(sh, p, w.U + col * sh.NB, w.herm0, ub);  // in flight during the transform
     TwCache<N, G::PT> twc;
-    tw_cache_load<N, G::PT>(twc, p.t, tw);
-    fft<N, G::PT, false>(v, p.t, ex + p.f * xlen<N>(), twc);
+    tw_cache_load<N, G::PT>(twc, p.p, tw);
+    fft_fwd<N, G::PT>(v, ex, twc, p.p);
 
     const double Tl = p.active ? T[p.l] : 1.0;
     const double invT = 1.0 / Tl;
@@ -303,7 +318,7 @@ __device__ __forceinline__ void col_pass_C(const Shape& sh, int block, const dou
         }
         v[m] = x;
     }
-    col_sum2<G::TPF>(Jp, dTp, red);
+    col_sum2<N>(Jp, dTp, red);
     if (p.active && p.t == 0) {
         w.partial[2 * col] = Jp;
         w.partial[2 * col + 1] = dTp;
@@ -316,19 +331,17 @@ __device__ __forceinline__ void col_pass_E(const Shape& sh, int block, const Wor
                                            int scheme, bool fuseA, cd* ex, const cd* __restrict__ tw,
                                            const double* __restrict__ T = nullptr) {
     using G = ColG<N>;
-    const ColPos p = col_pos<N>(sh, block);
+    const ColPos<N> p(sh, block);
     const size_t col = (size_t)p.l * sh.C + p.j;
-    const cd* Dc = w.BD + col * N;
     cd v[G::PT], gb[G::PT];
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) v[m] = p.active ? Dc[p.t + m * G::TPF] : cd{0.0, 0.0};
+    col_load<N>(sh, p, w.BD, v);
     // G_lin or (reverse mode) the saved residual, in flight during the transform. In the step
     // (U1, then the next step's pass A on the new column) the loads issued after the transform
     // measured faster: pass E at 256 x 1024 took 70.4 us against 75.8 with them in flight.
     if (mode != MODE_STEP) band_prefetch<N>(sh, p, (mode == MODE_ADJOINT ? w.R : w.G) + col * sh.NB, 0, gb);
     TwCache<N, G::PT> twc;
-    tw_cache_load<N, G::PT>(twc, p.t, tw);
-    fft<N, G::PT, false>(v, p.t, ex + p.f * xlen<N>(), twc);
+    tw_cache_load<N, G::PT>(twc, p.p, tw);
+    fft_fwd<N, G::PT>(v, ex, twc, p.p);
     if (mode == MODE_STEP) band_prefetch<N>(sh, p, w.G + col * sh.NB, 0, gb);
 
     const double invN = 1.0 / N;
@@ -385,81 +398,190 @@ __device__ __forceinline__ void col_pass_E(const Shape& sh, int block, const Wor
 }
 
 // ---------------------------------------------------------------------------- row passes
-// TPF = M/PT threads per row transform, P = kBlock / TPF pairs of rows per block, thread
-// tid -> t = tid % TPF, p = tid / TPF. A block covers ROWS = 2P consecutive global rows
+// TPF = M/PT threads per row transform, P = kBlock / TPF pairs of rows per block, each
+// thread's pairs and positions from FftPos. A block covers ROWS = 2P consecutive global rows
 // g0 .. g0 + 2P - 1 (g = l * N + n, loop-major), paired as (g0 + p, g0 + P + p).
+//
+// Every transform carries the two rows of a pair, f + i g, so its spectrum Z = F + i G over the
+// signed frequencies |e| <= Kx is all that passes between memory and the transform. On the
+// way in, the thread that loads F_j and G_j forms Z_j and Z_{-j} = conj F_j + i conj G_j and
+// stages them in LDS in the order the transform reads them; on the way out, the transforms
+// leave Z in LDS and the thread that stores row values reads Z_j and Z_{-j} and splits them. The
+// LDS write port is what the row passes run out of first (fft.hpp), and this takes 6 + 6 b128
+// writes per thread and field besides the exchange, against 6 (raw tile) + 8 (Z) + 6 (output
+// tile) when the rows were staged as separate half spectra: on 64 loops of 256 x 1024 pass B went
+// from 64.4 to 54.0 us and pass D from 72.7 to 62.0 (with the exchanges of fft.hpp).
 template <int M, int PT_ = (M >= 1024 ? 16 : 8)>
 struct RowG {
-    static constexpr int PT = PT_;
+    static constexpr int PT = PT_, ROW_M = M;
+    using E = Fft<M, PT>;
     static constexpr int TPF = M / PT;  // <= 64: one transform per wavefront at most
     static constexpr int P = kBlock / TPF;
     static constexpr int ROWS = 2 * P;
-    static constexpr int CMAX = (M - 1) / 3 + 1;
-    static constexpr int TS = ROWS + 1;  // padded row stride of a tile [j][r]
+    static constexpr int Kx = (M - 1) / 3;
+    static constexpr int CMAX = Kx + 1;
+    static constexpr int PW = E::XPW;  // pairs per wavefront
+    // Staged spectrum of a pair: frequency e at e (e <= Kx) or e - SH (e >= M - Kx). Strides of a
+    // pair (ST) and of a wavefront's region (a multiple of 16 plus WMOD) put 16 consecutive
+    // lanes of a staging write (consecutive pairs, then j) on 16 different slots modulo 16.
+    static constexpr int SH = M - 2 * Kx - 1;
+    static constexpr int up_to(int n, int mod, int r) { return n + ((r - n) % mod + mod) % mod; }
+    static constexpr int ST = P >= 16 ? 2 * Kx + 1 : P == 8 ? up_to(2 * Kx + 1, 16, 2) : up_to(2 * Kx + 1, 16, 4);
+    static constexpr int WMOD = M == 64 ? 8 : 4;
+    static constexpr int wave_region(int fields) {
+        const int st = fields * PW * ST, xs = E::L == 1 ? 0 : PW * E::XS;
+        return up_to(st > xs ? st : xs, 16, WMOD);
+    }
+    static constexpr int LDS = kBlock / 64 * wave_region(2);    // two fields (pass D)
+    static constexpr int LDS_B = kBlock / 64 * wave_region(1);  // one field (pass B)
+    static constexpr int NL = (P * CMAX + kBlock - 1) / kBlock;  // (pair, j) items per thread
+    // raw tiles [j][r] of the load unit's copies (load_rows_lds)
+    static constexpr int TS = ROWS + 1;
     static constexpr int TILE = CMAX * TS;
-    static constexpr int XL = P * xlen<M>();
-    // LDS: two input tiles, aliased afterwards by the exchange regions and the output tile
-    static constexpr int LDS = (2 * TILE > XL ? 2 * TILE : XL);
-    static constexpr int LDS_B = (TILE > XL ? TILE : XL);  // pass B holds one input tile
-    static constexpr int PW = 64 / TPF;                   // pairs per wavefront
-    static constexpr int NOUT = (2 * PW * CMAX + 63) / 64;  // split outputs per thread
 };
 
-// Load rows [g0, g0 + ROWS) of NT intermediates X[0..NT) into tiles tile + i * TILE, laid
-// out [j][r] with stride TS, coalesced along n. Rows past nrows read as zero. issue() puts
-// every global load of the tile in flight (into registers); commit() stores them to LDS, so
-// a caller can do other work while the loads travel. ROWS and N are powers of two, and the
-// row passes' column count C = (M-1)/3 + 1 is CMAX. Tiles start at multiples of ROWS, so when
-// N >= ROWS a tile lies inside one loop and its elements sit at j N + r from the tile's first
-// row (32-bit offsets); shorter loops take the general row-by-row address.
-template <int ROWS, int CMAX, int TS, int TILE, int NT>
-struct RowTiles {
-    static constexpr int NL = (ROWS * CMAX + kBlock - 1) / kBlock;
-    static constexpr int n = ROWS * CMAX;
-    cd buf[NT][NL];
+// Item k of a thread: pair p and column j, consecutive lanes on consecutive pairs.
+template <class G>
+__device__ __forceinline__ bool row_item(int k, int& p, int& j) {
+    const int i = threadIdx.x + k * kBlock;
+    p = i % G::P;
+    j = i / G::P;
+    return G::P * G::CMAX % kBlock == 0 || j < G::CMAX;
+}
+
+// Staging slot of (pair p, field q) in regions of WR values per wavefront.
+template <class G, int WR>
+__device__ __forceinline__ int stage_base(int p, int q) {
+    return p / G::PW * WR + (q * G::PW + p % G::PW) * G::ST;
+}
+
+// Address of column 0 of global row g; element j follows at j * sh.N (intermediates in HBM).
+__device__ __forceinline__ size_t row_offset(size_t g, const Shape& sh) {
+    return ((g >> sh.logN) * sh.C) * sh.N + (g & (size_t)(sh.N - 1));
+}
+
+// The rows of NT intermediates X[0..NT) for this thread's items: issue() puts every global load
+// in flight (into registers), commit() stages them as packed spectra. Rows past nrows read as
+// zero. ROWS and N are powers of two and tiles start at multiples of ROWS, so when N >= ROWS a
+// tile lies inside one loop and its elements sit at j N + r from the tile's first row (32-bit
+// offsets); shorter loops take the general row-by-row address.
+template <class G, int NT>
+struct RowLoad {
+    cd fa[NT][G::NL], fb[NT][G::NL];
     __device__ __forceinline__ void issue(const cd* const (&X)[NT], size_t g0, const Shape& sh, size_t nrows) {
-        if (sh.N >= ROWS) {
-            const size_t base = ((g0 >> sh.logN) * CMAX) * sh.N + (g0 & (size_t)(sh.N - 1));
+        const bool in_loop = sh.N >= G::ROWS;
+        const size_t base = row_offset(g0, sh);
 #pragma unroll
-            for (int k = 0; k < NL; ++k) {
-                const int i = threadIdx.x + k * kBlock;
-                const int j = i / ROWS, r = i % ROWS;
-                const bool ok = (n % kBlock == 0 || i < n) && g0 < nrows;
+        for (int k = 0; k < G::NL; ++k) {
+            int p, j;
+            const bool item = row_item<G>(k, p, j);
+            const size_t ga = g0 + p, gb = ga + G::P;
+            const bool oka = item && ga < nrows, okb = item && gb < nrows;
+            const size_t a = in_loop ? base + (j * sh.N + p) : oka ? row_offset(ga, sh) + (size_t)j * sh.N : 0;
+            const size_t b = in_loop ? base + (j * sh.N + G::P + p) : okb ? row_offset(gb, sh) + (size_t)j * sh.N : 0;
 #pragma unroll
-                for (int q = 0; q < NT; ++q) buf[q][k] = ok ? X[q][base + (j * sh.N + r)] : cd{0.0, 0.0};
+            for (int q = 0; q < NT; ++q) {
+                fa[q][k] = oka ? X[q][a] : cd{0.0, 0.0};
+                fb[q][k] = okb ? X[q][b] : cd{0.0, 0.0};
             }
-            return;
-        }
-#pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            const int i = threadIdx.x + k * kBlock;
-            const int j = i / ROWS, r = i % ROWS;
-            const size_t g = g0 + r;
-            const bool ok = i < n && g < nrows;
-            const size_t off = ok ? ((g >> sh.logN) * CMAX + j) * sh.N + (g & (size_t)(sh.N - 1)) : 0;
-#pragma unroll
-            for (int q = 0; q < NT; ++q) buf[q][k] = ok ? X[q][off] : cd{0.0, 0.0};
         }
     }
-    __device__ __forceinline__ void commit(cd* tile, const Shape&) const {
+    template <int WR>
+    __device__ __forceinline__ void commit(cd* lds) const {
 #pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            const int i = threadIdx.x + k * kBlock;
-            if (n % kBlock == 0 || i < n) {
-                const int j = i / ROWS, r = i % ROWS;
+        for (int k = 0; k < G::NL; ++k) {
+            int p, j;
+            if (!row_item<G>(k, p, j)) continue;
 #pragma unroll
-                for (int q = 0; q < NT; ++q) tile[q * TILE + j * TS + r] = buf[q][k];
+            for (int q = 0; q < NT; ++q) {
+                cd* z = lds + stage_base<G, WR>(p, q);
+                const cd f = fa[q][k], g = fb[q][k];
+                if (j == 0) {
+                    z[0] = cd{f.x, g.x};  // X_0 is read as real
+                } else {
+                    z[j] = cd{f.x - g.y, f.y + g.x};
+                    z[G::ROW_M - G::SH - j] = cd{f.x + g.y, g.x - f.y};
+                }
             }
         }
     }
 };
 
-template <int ROWS, int CMAX, int TS, int TILE, int NT>
-__device__ __forceinline__ void load_rows(cd* tile, const cd* const (&X)[NT], size_t g0, const Shape& sh,
-                                          size_t nrows) {
-    RowTiles<ROWS, CMAX, TS, TILE, NT> ld;
-    ld.issue(X, g0, sh, nrows);
-    ld.commit(tile, sh);
+// The staged spectrum of a pair (field base z) in the slots of thread t; slots outside the
+// band are zero. A slot wholly inside or outside the band is resolved at compile time.
+template <class G, int m = 0>
+__device__ __forceinline__ void row_gather(const cd* z, int t, cd* v) {
+    if constexpr (m < G::PT) {
+        constexpr int lo = m * G::TPF, hi = lo + G::TPF - 1;
+        constexpr int Kx = G::Kx, M = G::ROW_M;
+        if constexpr (hi <= Kx) {
+            v[m] = z[lo + t];
+        } else if constexpr (lo >= M - Kx) {
+            v[m] = z[lo + t - G::SH];
+        } else if constexpr (lo > Kx && hi < M - Kx) {
+            v[m] = cd{0.0, 0.0};
+        } else {
+            const int e = lo + t;
+            const bool pos = e <= Kx, in = pos || e >= M - Kx;
+            const cd x = z[in ? (pos ? e : e - G::SH) : 0];
+            v[m] = in ? x : cd{0.0, 0.0};
+        }
+        row_gather<G, m + 1>(z, t, v);
+    }
+}
+
+// The reverse: the in-band slots of a transform's output into the staged layout.
+template <class G, int m = 0>
+__device__ __forceinline__ void row_put(cd* z, int t, const cd* v) {
+    if constexpr (m < G::PT) {
+        constexpr int lo = m * G::TPF, hi = lo + G::TPF - 1;
+        constexpr int Kx = G::Kx, M = G::ROW_M;
+        if constexpr (hi <= Kx) {
+            z[lo + t] = v[m];
+        } else if constexpr (lo >= M - Kx) {
+            z[lo + t - G::SH] = v[m];
+        } else if constexpr (!(lo > Kx && hi < M - Kx)) {
+            const int e = lo + t;
+            if (e <= Kx) z[e] = v[m];
+            if (e >= M - Kx) z[e - G::SH] = v[m];
+        }
+        row_put<G, m + 1>(z, t, v);
+    }
+}
+
+// Split of Z = W_a + i W_b at +-j into the half spectra of rows a and b: W_a(j) = (Z_j + conj
+// Z_{-j}) / 2, W_b(j) = (Z_j - conj Z_{-j}) / (2i), scaled by 1/M. With DX they are
+// differentiated on the way, i q_j / 2 W (the half derivative of a square).
+template <int M, bool DX>
+__device__ __forceinline__ void row_split(double L, int j, cd a, cd b, cd& wa, cd& wb) {
+    if constexpr (DX) {
+        const double c = (kTwoPi / L) * (0.25 / M) * j;  // q_j / 2 and the 1/(2M) of the split
+        wa = cd{c * (b.y - a.y), c * (a.x + b.x)};
+        wb = cd{c * (a.x - b.x), c * (a.y + b.y)};
+    } else {
+        constexpr double s = 0.5 / M;
+        wa = cd{(a.x + b.x) * s, (a.y - b.y) * s};
+        wb = cd{(a.y + b.y) * s, (b.x - a.x) * s};
+    }
+}
+
+// Rows of the products from the staged spectra (regions of WR values per wavefront) to X.
+template <class G, int WR, bool DX>
+__device__ __forceinline__ void row_store(const cd* lds, cd* X, size_t g0, const Shape& sh, size_t nrows) {
+    const bool in_loop = sh.N >= G::ROWS;
+    const size_t base = row_offset(g0, sh);
+#pragma unroll
+    for (int k = 0; k < G::NL; ++k) {
+        int p, j;
+        if (!row_item<G>(k, p, j)) continue;
+        const cd* z = lds + stage_base<G, WR>(p, 0);
+        const cd a = z[j], b = z[j == 0 ? 0 : G::ROW_M - G::SH - j];
+        cd wa, wb;
+        row_split<G::ROW_M, DX>(sh.L, j, a, b, wa, wb);
+        const size_t ga = g0 + p, gb = ga + G::P;
+        if (ga < nrows) X[in_loop ? base + (j * sh.N + p) : row_offset(ga, sh) + (size_t)j * sh.N] = wa;
+        if (gb < nrows) X[in_loop ? base + (j * sh.N + G::P + p) : row_offset(gb, sh) + (size_t)j * sh.N] = wb;
+    }
 }
 
 // The same tiles as load_rows, copied by the load unit straight into LDS
@@ -494,33 +616,6 @@ __device__ __forceinline__ void load_rows_lds(cd* tile, const cd* const (&X)[NT]
     if constexpr (WAIT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// Store tile[j][r] (stride TS) to rows [g0, g0 + ROWS) of X, addressed as RowTiles loads them.
-template <int ROWS, int CMAX>
-__device__ __forceinline__ void store_rows(const cd* tile, int TS, cd* X, size_t g0, const Shape& sh,
-                                           size_t nrows) {
-    constexpr int NL = (ROWS * CMAX + kBlock - 1) / kBlock;
-    constexpr int n = ROWS * CMAX;
-    if (sh.N >= ROWS) {
-        if (g0 >= nrows) return;
-        cd* base = X + ((g0 >> sh.logN) * CMAX) * sh.N + (g0 & (size_t)(sh.N - 1));
-#pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            const int i = threadIdx.x + k * kBlock;
-            const int j = i / ROWS, r = i % ROWS;
-            if (n % kBlock == 0 || i < n) base[j * sh.N + r] = tile[j * TS + r];
-        }
-        return;
-    }
-#pragma unroll
-    for (int k = 0; k < NL; ++k) {
-        const int i = threadIdx.x + k * kBlock;
-        const int j = i / ROWS, r = i % ROWS;
-        const size_t g = g0 + r;
-        if (i < n && g < nrows)
-            X[((g >> sh.logN) * CMAX + j) * sh.N + (g & (size_t)(sh.N - 1))] = tile[j * TS + r];
-    }
-}
-
 // Element e of the Hermitian extension of half spectrum tile[j][r] (j < C; X_0 read as real):
 // tile[e] for e <= Kx, conj(tile[M - e]) for e >= M - Kx, zero between. Written without
 // branches (one read of a valid element, then selects), since e differs across the lanes of
@@ -536,52 +631,13 @@ __device__ __forceinline__ cd herm_ext(const cd* tile, int TS, int r, int e, int
 // Spectrum of f + i g for two real rows f, g given by their half spectra (packed complex).
 __device__ __forceinline__ cd pack2(cd f, cd g) { return cd{f.x - g.y, f.y + g.x}; }
 
-// herm_ext for the elements e = t + m TPF (m = 0 .. PT-1) that thread t of a row transform
-// holds, with the band limit Kx = (M-1)/3 of an M-point row known at compile time. A slot
-// whose elements all lie in the band reads them directly (e <= Kx) or as conjugates of their
-// partners (e >= M - Kx); a slot wholly outside the band is zero; only a slot that straddles
-// a band edge selects per lane. The values are herm_ext's, bit for bit.
-template <int M, int PT, int m>
-__device__ __forceinline__ cd herm_slot(const cd* tile, int TS, int r, int t) {
-    constexpr int TPF = M / PT, Kx = (M - 1) / 3;
-    constexpr int lo = m * TPF, hi = lo + TPF - 1;
-    if constexpr (hi <= Kx) {
-        const cd v = tile[(lo + t) * TS + r];
-        if constexpr (lo == 0) return cd{v.x, t == 0 ? 0.0 : v.y};  // X_0 is read as real
-        return v;
-    } else if constexpr (lo >= M - Kx) {
-        const cd v = tile[(M - lo - t) * TS + r];
-        return cd{v.x, -v.y};
-    } else if constexpr (lo > Kx && hi < M - Kx) {
-        return cd{0.0, 0.0};
-    } else {
-        return herm_ext(tile, TS, r, lo + t, M, Kx);
-    }
-}
-
-// va[m] = pack2 of rows ra and rb of a tile, slot by slot (see herm_slot).
-template <int M, int PT, int m = 0>
+// herm_pack for raw tiles: va[m] = pack2 of rows ra and rb of a tile at e = t + m TPF.
+template <int M, int PT>
 __device__ __forceinline__ void herm_pack(const cd* tile, int TS, int ra, int rb, int t, cd* va) {
-    if constexpr (m < PT) {
-        va[m] = pack2(herm_slot<M, PT, m>(tile, TS, ra, t), herm_slot<M, PT, m>(tile, TS, rb, t));
-        herm_pack<M, PT, m + 1>(tile, TS, ra, rb, t, va);
-    }
-}
-
-// herm_pack, and in vb the x-derivatives of the same rows (i q times each element, q of the
-// signed frequency of slot m).
-template <int M, int PT, int m = 0>
-__device__ __forceinline__ void herm_pack_dx(const cd* tile, int TS, int ra, int rb, int t, double dq, cd* va,
-                                             cd* vb) {
-    if constexpr (m < PT) {
-        constexpr int TPF = M / PT;
-        const int e = t + m * TPF;
-        const double q = dq * (double)((e <= M / 2) ? e : e - M);
-        const cd a = herm_slot<M, PT, m>(tile, TS, ra, t), b = herm_slot<M, PT, m>(tile, TS, rb, t);
-        va[m] = pack2(a, b);
-        vb[m] = pack2(cd{-q * a.y, q * a.x}, cd{-q * b.y, q * b.x});
-        herm_pack_dx<M, PT, m + 1>(tile, TS, ra, rb, t, dq, va, vb);
-    }
+    constexpr int TPF = M / PT, Kx = (M - 1) / 3;
+#pragma unroll
+    for (int m = 0; m < PT; ++m)
+        va[m] = pack2(herm_ext(tile, TS, ra, t + m * TPF, M, Kx), herm_ext(tile, TS, rb, t + m * TPF, M, Kx));
 }
 
 // Pass B forms u u_x as (1/2) (u^2)_x (two transforms per pair of rows) for rows of up to
@@ -594,124 +650,101 @@ __device__ __forceinline__ void herm_pack_dx(const cd* tile, int TS, int ra, int
 // stays inside the 1e-12 bound even for a loop made of its lowest mode.
 constexpr int kSquareMaxM = 128;
 
-// Forward transform of the pair's product values va, then the split of the result
-// Z = W_a + i W_b into the two rows' half spectra, W_a(j) = (Z_j + conj Z_{M-j}) / 2 and
-// W_b(j) = (Z_j - conj Z_{M-j}) / (2i), scaled by 1/M, written to tile[j][r] over the
-// inputs' LDS. With DX the rows' spectra are differentiated on the way, i q_j / 2 W (the half
-// derivative of a square).
-template <int M, int PT, bool DX>
-__device__ __forceinline__ void row_forward_split(const Shape& sh, cd* va, cd* lds, cd* ex, int t,
-                                                  const TwCache<M, PT>& twc) {
+// u u_x = (1/2) (u^2)_x on the rows of a pair: one inverse transform of u_a + i u_b, the squares
+// (u_a^2) + i (u_b^2) in physical space and one forward transform (the factor i q_j / 2 is
+// row_split's). Both fields are band-limited, so (u^2)_x of the band equals the band of 2 u u_x
+// exactly; one transform of three is saved.
+template <int M, int PT, bool XLOW>
+__device__ __forceinline__ void row_square(cd* va, cd* ex, const TwCache<M, PT>& twc, const FftPos<M, PT, XLOW>& pos) {
+    fft_inv<M, PT, XLOW>(va, ex, twc, pos);
+#pragma unroll
+    for (int m = 0; m < PT; ++m) va[m] = cd{va[m].x * va[m].x, va[m].y * va[m].y};
+    fft_fwd<M, PT, XLOW>(va, ex, twc, pos);
+}
+
+// Products of two real fields f, g on the rows of a pair. The two inverse x-transforms take the
+// rows of one field at a time (va = f_a + i f_b, vb = g_a + i g_b), so each transform carries
+// values of one scale; packing f and g of one row together would let the round-off of the
+// larger (r_x can exceed u by q_max^5) swamp the smaller. Then one forward transform of
+// (f_a g_a) + i (f_b g_b).
+template <int M, int PT, bool XLOW>
+__device__ __forceinline__ void row_product(cd* va, cd* vb, cd* ex, const TwCache<M, PT>& twc,
+                                            const FftPos<M, PT, XLOW>& pos) {
+    fft_inv<M, PT, XLOW>(va, ex, twc, pos);
+    fft_inv<M, PT, XLOW>(vb, ex, twc, pos);
+#pragma unroll
+    for (int m = 0; m < PT; ++m) va[m] = cd{va[m].x * vb[m].x, va[m].y * vb[m].y};
+    fft_fwd<M, PT, XLOW>(va, ex, twc, pos);
+}
+
+// vb = i q va, the x-derivative of a pair's spectrum, q of the signed frequency e = t + m TPF
+template <int M, int PT>
+__device__ __forceinline__ void row_dx(const cd* va, int t, double dq, cd* vb) {
+    constexpr int TPF = M / PT;
+#pragma unroll
+    for (int m = 0; m < PT; ++m) {
+        const int e = t + m * TPF;
+        const double q = dq * (double)((e <= M / 2) ? e : e - M);
+        vb[m] = cd{-q * va[m].y, q * va[m].x};
+    }
+}
+
+// The transforms of a block's pairs, between the staging barriers: the spectra of `fields`
+// fields are staged in lds; on return the products' spectra are, and every thread may read
+// them. Each wavefront's regions are its own until the barrier, so its exchanges reuse them.
+// DX: the square form of u u_x (one field); otherwise the product of two fields, or of one field
+// and its x-derivative.
+template <int M, int PT, int FIELDS, int WR, bool DX>
+__device__ __forceinline__ void row_transforms(const Shape& sh, cd* lds, const FftPos<M, PT>& pos,
+                                               const TwCache<M, PT>& twc, cd* va, cd* vb) {
     using G = RowG<M, PT>;
-    fft<M, G::PT, false>(va, t, ex, twc);
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) ex[xpos(t + m * G::TPF)] = va[m];
+    // the exchange addresses a wavefront's transforms as x * XS from the block's start: shift
+    // the base so that they fall into the wavefront's own region
+    const int wave = threadIdx.x / 64;
+    cd* ex = lds + wave * (WR - G::PW * G::E::XS);
+    if constexpr (DX)
+        row_square<M, PT, false>(va, ex, twc, pos);
+    else
+        row_product<M, PT, false>(va, vb, ex, twc, pos);
     wave_lds_order();
-    const int lane = threadIdx.x % 64;
-    const int pw0 = (threadIdx.x / 64) * G::PW;
-    constexpr int nout = 2 * G::PW * G::CMAX;
-    const double s = 0.5 / M;
-    const double hq = (kTwoPi / sh.L) * (0.25 / M);  // q_j / 2 per unit j, with the 1/(2M) of the split
-    cd outv[G::NOUT];
-#pragma unroll
-    for (int i = 0; i < G::NOUT; ++i) {
-        const int idx = lane + 64 * i;
-        if (idx < nout) {
-            const int pp = pw0 + idx / (2 * G::CMAX);
-            const int rem = idx % (2 * G::CMAX);
-            const int j = rem % G::CMAX;
-            const bool rb = rem >= G::CMAX;  // row b (else row a) of the pair
-            const cd* e2 = lds + pp * xlen<M>();
-            const cd a = e2[xpos(j)];
-            const cd b = e2[xpos((M - j) & (M - 1))];
-            if constexpr (DX) {
-                const double c = hq * j;
-                outv[i] = rb ? cd{c * (a.x - b.x), c * (a.y + b.y)} : cd{c * (b.y - a.y), c * (a.x + b.x)};
-            } else {
-                outv[i] = rb ? cd{(a.y + b.y) * s, (b.x - a.x) * s} : cd{(a.x + b.x) * s, (a.y - b.y) * s};
-            }
-        }
-    }
-    __syncthreads();  // every wave is done with its exchange region: reuse as the output tile
-#pragma unroll
-    for (int i = 0; i < G::NOUT; ++i) {
-        const int idx = lane + 64 * i;
-        if (idx < nout) {
-            const int pp = pw0 + idx / (2 * G::CMAX);
-            const int rem = idx % (2 * G::CMAX);
-            // consecutive lanes write consecutive j of one row: stride TS, no bank conflicts
-            lds[(rem % G::CMAX) * G::TS + (rem >= G::CMAX ? G::P + pp : pp)] = outv[i];
-        }
-    }
+    row_put<G>(lds + stage_base<G, WR>(pos.xs, 0), pos.t, va);
     __syncthreads();
 }
 
-// u u_x = (1/2) (u^2)_x on rows a and b of a pair: one inverse transform of u_a + i u_b, the
-// squares (u_a^2) + i (u_b^2) in physical space, one forward transform, and the split with the
-// factor i q_j / 2. Both fields are band-limited, so (u^2)_x of the band equals the band of
-// 2 u u_x exactly; one transform of three is saved.
-template <int M, int PT = RowG<M>::PT>
-__device__ __forceinline__ void row_square_dx(const Shape& sh, cd* va, cd* lds, int t, int p,
-                                              const TwCache<M, PT>& twc) {
-    cd* ex = lds + p * xlen<M>();
-    __syncthreads();  // every wave has read its inputs from the tile: the tile is free
-    fft<M, PT, true>(va, t, ex, twc);
-#pragma unroll
-    for (int m = 0; m < PT; ++m) va[m] = cd{va[m].x * va[m].x, va[m].y * va[m].y};
-    row_forward_split<M, PT, true>(sh, va, lds, ex, t, twc);
-}
-
-// Products of two real fields f, g on rows a and b of a pair. The two inverse x-transforms
-// take the rows of one field at a time (va = f_a + i f_b, vb = g_a + i g_b), so each transform
-// carries values of one scale; packing f and g of one row together would let the round-off
-// of the larger (r_x can exceed u by q_max^5) swamp the smaller. Then one forward transform
-// of (f_a g_a) + i (f_b g_b) and the split into the two rows' half spectra (scaled by 1/M),
-// written to tile[j][r] over the inputs' LDS.
-template <int M, int PT = RowG<M>::PT>
-__device__ __forceinline__ void row_products(const Shape& sh, cd* va, cd* vb, cd* lds, int t, int p,
-                                             const TwCache<M, PT>& twc) {
-    using G = RowG<M, PT>;
-    cd* ex = lds + p * xlen<M>();
-    __syncthreads();  // every wave has read its inputs from the tiles: the tiles are free
-    fft<M, G::PT, true>(va, t, ex, twc);
-    fft<M, G::PT, true>(vb, t, ex, twc);
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) va[m] = cd{va[m].x * vb[m].x, va[m].y * vb[m].y};
-    row_forward_split<M, PT, false>(sh, va, lds, ex, t, twc);
-}
-
-// DMA selects load_rows_lds over load_rows (tiles of 64 rows or more). PT below the default
-// spreads each row transform over more threads: tiles are then shorter, and a block covers
-// the rows of one default-size tile (so that tile indices keep their meaning) in SUB
-// consecutive sub-tiles.
+// DMA copies raw tiles by the load unit (load_rows_lds, tiles of 64 rows or more) instead of
+// staging packed spectra through registers. PT below the default spreads each row transform
+// over more threads: tiles are then shorter, and a block covers the rows of one default-size
+// tile (so that tile indices keep their meaning) in SUB consecutive sub-tiles.
 template <int M, bool DMA = false, int PT = RowG<M>::PT>
 __device__ __forceinline__ void row_pass_B(const Shape& sh, int block, const Work& w, cd* lds,
                                            const cd* __restrict__ tw) {
     using G = RowG<M, PT>;
     constexpr int SUB = RowG<M>::ROWS / G::ROWS;
+    constexpr int WR = G::wave_region(1);
+    constexpr bool DX = M <= kSquareMaxM;
     const size_t nrows = (size_t)sh.nloops * sh.N;
-    const int t = threadIdx.x % G::TPF, p = threadIdx.x / G::TPF;
+    const FftPos<M, PT> pos(threadIdx.x);
     TwCache<M, PT> twc;
-    tw_cache_load<M, PT>(twc, t, tw);
+    tw_cache_load<M, PT>(twc, pos, tw);
     auto sub = [&](size_t g0) {
-        {
-            const cd* const src[1] = {w.A};
-            if constexpr (DMA)
-                load_rows_lds<G::ROWS, G::CMAX, G::TS, G::TILE, 1>(lds, src, g0, sh, nrows);
-            else
-                load_rows<G::ROWS, G::CMAX, G::TS, G::TILE, 1>(lds, src, g0, sh, nrows);
-        }
-        __syncthreads();
-        if constexpr (M <= kSquareMaxM) {
-            cd va[PT];
-            herm_pack<M, PT>(lds, G::TS, p, G::P + p, t, va);  // u, rows a and b
-            row_square_dx<M, PT>(sh, va, lds, t, p, twc);
+        const cd* const src[1] = {w.A};
+        cd va[PT], vb[PT];
+        if constexpr (DMA) {
+            load_rows_lds<G::ROWS, G::CMAX, G::TS, G::TILE, 1>(lds, src, g0, sh, nrows);
+            __syncthreads();
+            herm_pack<M, PT>(lds, G::TS, pos.xs, G::P + pos.xs, pos.t, va);
+            __syncthreads();  // every wavefront has read the tile: its regions are free
         } else {
-            cd va[PT], vb[PT];
-            herm_pack_dx<M, PT>(lds, G::TS, p, G::P + p, t, kTwoPi / sh.L, va, vb);  // u and u_x, rows a and b
-            row_products<M, PT>(sh, va, vb, lds, t, p, twc);
+            RowLoad<G, 1> ld;
+            ld.issue(src, g0, sh, nrows);
+            ld.template commit<WR>(lds);
+            __syncthreads();
+            row_gather<G>(lds + stage_base<G, WR>(pos.xs, 0), pos.t, va);
+            wave_lds_order();
         }
-        store_rows<G::ROWS, G::CMAX>(lds, G::TS, w.BD, g0, sh, nrows);
+        if constexpr (!DX) row_dx<M, PT>(va, pos.t, kTwoPi / sh.L, vb);
+        row_transforms<M, PT, 1, WR, DX>(sh, lds, pos, twc, va, vb);
+        row_store<G, WR, DX>(lds, w.BD, g0, sh, nrows);
     };
     const size_t gb = (size_t)block * RowG<M>::ROWS;
     if constexpr (SUB == 1) {
@@ -719,7 +752,7 @@ __device__ __forceinline__ void row_pass_B(const Shape& sh, int block, const Wor
     } else {
 #pragma unroll 1
         for (int h = 0; h < SUB; ++h) {
-            if (h > 0) __syncthreads();  // the previous sub-tile's output tile has been stored
+            if (h > 0) __syncthreads();  // the previous sub-tile's rows have been read
             sub(gb + (size_t)h * G::ROWS);
         }
     }
@@ -775,38 +808,40 @@ __device__ __forceinline__ void row_pass_D(const Shape& sh, int block, const Wor
                 finalize_loop(sh, (int)l, w, T, mode, dtau, J_hist, Jout, dJdTout);
         }
     };
-    cd* tA = lds;
-    cd* tC = lds + G::TILE;
-    const int t = threadIdx.x % G::TPF, p = threadIdx.x / G::TPF;
+    constexpr int WR = G::wave_region(2);
+    const FftPos<M, PT> pos(threadIdx.x);
     TwCache<M, PT> twc;
-    tw_cache_load<M, PT>(twc, t, tw);
+    tw_cache_load<M, PT>(twc, pos, tw);
     auto sub = [&](size_t g0, bool first) {
-        {
-            const cd* const src[2] = {w.A, w.Cb};
-            if constexpr (DMA) {
-                load_rows_lds<G::ROWS, G::CMAX, G::TS, G::TILE, 2, false>(tA, src, g0, sh, nrows);
-                if (first) finalize();
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            } else {
-                RowTiles<G::ROWS, G::CMAX, G::TS, G::TILE, 2> ld;
-                ld.issue(src, g0, sh, nrows);
-                if (first) finalize();
-                ld.commit(tA, sh);
-            }
+        const cd* const src[2] = {w.A, w.Cb};
+        cd va[PT], vb[PT];  // u and r_x
+        if constexpr (DMA) {
+            load_rows_lds<G::ROWS, G::CMAX, G::TS, G::TILE, 2, false>(lds, src, g0, sh, nrows);
+            if (first) finalize();
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            herm_pack<M, PT>(lds, G::TS, pos.xs, G::P + pos.xs, pos.t, va);
+            herm_pack<M, PT>(lds + G::TILE, G::TS, pos.xs, G::P + pos.xs, pos.t, vb);
+            __syncthreads();  // every wavefront has read the tiles: its regions are free
+        } else {
+            RowLoad<G, 2> ld;
+            ld.issue(src, g0, sh, nrows);
+            if (first) finalize();
+            ld.template commit<WR>(lds);
+            __syncthreads();
+            row_gather<G>(lds + stage_base<G, WR>(pos.xs, 0), pos.t, va);
+            row_gather<G>(lds + stage_base<G, WR>(pos.xs, 1), pos.t, vb);
+            wave_lds_order();
         }
-        __syncthreads();
-        cd va[PT], vb[PT];
-        herm_pack<M, PT>(tA, G::TS, p, G::P + p, t, va);  // u
-        herm_pack<M, PT>(tC, G::TS, p, G::P + p, t, vb);  // r_x
-        row_products<M, PT>(sh, va, vb, lds, t, p, twc);
-        store_rows<G::ROWS, G::CMAX>(lds, G::TS, w.BD, g0, sh, nrows);
+        row_transforms<M, PT, 2, WR, false>(sh, lds, pos, twc, va, vb);
+        row_store<G, WR, false>(lds, w.BD, g0, sh, nrows);
     };
     if constexpr (SUB == 1) {
         sub(gb, true);
     } else {
 #pragma unroll 1
         for (int h = 0; h < SUB; ++h) {
-            if (h > 0) __syncthreads();  // the previous sub-tile's output tile has been stored
+            if (h > 0) __syncthreads();  // the previous sub-tile's rows have been read
             sub(gb + (size_t)h * G::ROWS, h == 0);
         }
     }

@@ -37,25 +37,29 @@ struct XiWork {
 };
 
 // ----------------------------------------------------------------------------- columns
-struct XiColPos {
-    bool active, two;  // two: the pair's second column exists (Kx may be odd)
-    int l, j1, t, f;   // j1: 0-based index (j - 1) of the pair's first column
-};
-
+// The column pairs of a thread: spectrum side (l, j1, t, two), points side (active_t, two_t, col_t).
 template <int N>
-__device__ __forceinline__ XiColPos xi_col_pos(const Shape& sh, int block) {
+struct XiColPos {
     using G = ColG<N>;
-    XiColPos p;
-    p.t = threadIdx.x % G::TPF;
-    p.f = threadIdx.x / G::TPF;
-    const int NP = (sh.Kx + 1) / 2;
-    const int gc = block * G::F + p.f;
-    p.active = gc < sh.nloops * NP;
-    p.l = p.active ? gc / NP : 0;
-    p.j1 = p.active ? 2 * (gc % NP) : 0;
-    p.two = p.active && p.j1 + 1 < sh.Kx;
-    return p;
-}
+    FftPos<N, G::PT> p;
+    bool active, two;  // two: the pair's second column exists (Kx may be odd)
+    int l, j1, t;      // j1: 0-based index (j - 1) of the pair's first column
+    bool active_t, two_t;
+    size_t col_t;      // index l Kx + j1 of the points side's pair
+    __device__ __forceinline__ XiColPos(const Shape& sh, int block) : p(threadIdx.x) {
+        const int NP = (sh.Kx + 1) / 2, n = sh.nloops * NP;
+        const int gc = block * G::F + p.xs, gt = block * G::F + p.xt;
+        t = p.t;
+        active = gc < n;
+        l = active ? gc / NP : 0;
+        j1 = active ? 2 * (gc % NP) : 0;
+        two = active && j1 + 1 < sh.Kx;
+        active_t = gt < n;
+        const int jt = active_t ? 2 * (gt % NP) : 0;
+        two_t = active_t && jt + 1 < sh.Kx;
+        col_t = active_t ? (size_t)(gt / NP) * sh.Kx + jt : 0;
+    }
+};
 
 // Spectrum element e (FFT order) of z = b1 + i b2 from the half spectra c1 = b1_hat, c2 =
 // b2_hat (k = 0..Ks) through Hermitian symmetry.
@@ -77,13 +81,14 @@ __device__ __forceinline__ cd xi_pack(const cd* c1, const cd* c2, int e, int N, 
 template <int N>
 __device__ __forceinline__ void xi_split(const cd* v, int t, cd* ex, double s, cd* p1, cd* p2) {
     using G = ColG<N>;
+    xsync<G::TPF>();  // the transform's other wavefront may still read its part of the region
 #pragma unroll
-    for (int m = 0; m < G::PT; ++m) ex[xpos(t + m * G::TPF)] = v[m];
+    for (int m = 0; m < G::PT; ++m) ex[t + m * G::TPF] = v[m];
     xsync<G::TPF>();
 #pragma unroll
     for (int m = 0; m < G::PT; ++m) {
         const int e = t + m * G::TPF;
-        const cd w = ex[xpos((N - e) & (N - 1))];
+        const cd w = ex[(N - e) & (N - 1)];
         const cd z = v[m];
         p1[m] = cd{0.5 * s * (z.x + w.x), 0.5 * s * (z.y - w.y)};
         p2[m] = cd{0.5 * s * (z.y + w.y), 0.5 * s * (w.x - z.x)};
@@ -100,8 +105,8 @@ __device__ __forceinline__ void xi_extend(cd* v, const cd* g1, const cd* g2, int
     for (int m = 0; m < G::PT; ++m) {
         const int e = t + m * G::TPF;
         if (e <= Ks) {
-            ex[xpos(2 * e)] = g1[m];
-            ex[xpos(2 * e + 1)] = g2[m];
+            ex[e] = g1[m];
+            ex[e + Ks + 1] = g2[m];
         }
     }
     xsync<G::TPF>();
@@ -111,7 +116,7 @@ __device__ __forceinline__ void xi_extend(cd* v, const cd* g1, const cd* g2, int
         cd z{0.0, 0.0};
         if (e <= Ks || e >= N - Ks) {
             const int k = e <= Ks ? e : N - e;
-            const cd x = ex[xpos(2 * k)], y = two ? ex[xpos(2 * k + 1)] : cd{0.0, 0.0};
+            const cd x = ex[k], y = two ? ex[k + Ks + 1] : cd{0.0, 0.0};
             z = e <= Ks ? cd{x.x - y.y, x.y + y.x} : cd{x.x + y.y, y.x - x.y};
         }
         v[m] = z;
@@ -120,25 +125,26 @@ __device__ __forceinline__ void xi_extend(cd* v, const cd* g1, const cd* g2, int
 }
 
 template <int N>
-__device__ __forceinline__ void xi_store_pair(const XiColPos& p, const Shape& sh, const cd* v, double* X) {
+__device__ __forceinline__ void xi_store_pair(const XiColPos<N>& p, const cd* v, double* X) {
     using G = ColG<N>;
-    if (!p.active) return;
-    double* x1 = X + ((size_t)p.l * sh.Kx + p.j1) * N;
+    if (!p.active_t) return;
+    double* x1 = X + p.col_t * N;
 #pragma unroll
     for (int m = 0; m < G::PT; ++m) {
-        x1[p.t + m * G::TPF] = v[m].x;
-        if (p.two) x1[N + p.t + m * G::TPF] = v[m].y;
+        const int n = p.p.point(m);
+        x1[n] = v[m].x;
+        if (p.two_t) x1[N + n] = v[m].y;
     }
 }
 
 template <int N>
-__device__ __forceinline__ void xi_load_pair(const XiColPos& p, const Shape& sh, const double* X, cd* v) {
+__device__ __forceinline__ void xi_load_pair(const XiColPos<N>& p, const double* X, cd* v) {
     using G = ColG<N>;
-    const double* x1 = X + ((size_t)p.l * sh.Kx + p.j1) * N;
+    const double* x1 = X + p.col_t * N;
 #pragma unroll
     for (int m = 0; m < G::PT; ++m) {
-        const int n = p.t + m * G::TPF;
-        v[m] = p.active ? cd{x1[n], p.two ? x1[N + n] : 0.0} : cd{0.0, 0.0};
+        const int n = p.p.point(m);
+        v[m] = p.active_t ? cd{x1[n], p.two_t ? x1[N + n] : 0.0} : cd{0.0, 0.0};
     }
 }
 
@@ -147,17 +153,17 @@ template <int N>
 __device__ __forceinline__ void xi_col_pass_A(const Shape& sh, int block, const XiWork& w, cd* ex,
                                               const cd* __restrict__ tw) {
     using G = ColG<N>;
-    const XiColPos p = xi_col_pos<N>(sh, block);
+    const XiColPos<N> p(sh, block);
     TwCache<N, G::PT> twc;
-    tw_cache_load<N, G::PT>(twc, p.t, tw);
+    tw_cache_load<N, G::PT>(twc, p.p, tw);
     const int K1 = sh.Ks + 1;
     const cd* b1 = w.U + ((size_t)p.l * sh.Kx + p.j1) * K1;
     cd v[G::PT];
 #pragma unroll
     for (int m = 0; m < G::PT; ++m)
         v[m] = p.active ? xi_pack(b1, b1 + K1, p.t + m * G::TPF, N, sh.Ks, p.two) : cd{0.0, 0.0};
-    fft<N, G::PT, true>(v, p.t, ex + p.f * xlen<N>(), twc);
-    xi_store_pair<N>(p, sh, v, w.A);
+    fft_inv<N, G::PT>(v, ex, twc, p.p);
+    xi_store_pair<N>(p, v, w.A);
 }
 
 // Pass C: residual, the partial sums of J and dJ/dT, U1, and the inverse transform of r_x.
@@ -166,13 +172,13 @@ __device__ __forceinline__ void xi_col_pass_C(const Shape& sh, int block, const 
                                               const XiWork& w, double dtau, int scheme, cd* ex, double* red,
                                               const cd* __restrict__ tw) {
     using G = ColG<N>;
-    const XiColPos p = xi_col_pos<N>(sh, block);
-    cd* exf = ex + p.f * xlen<N>();
+    const XiColPos<N> p(sh, block);
+    cd* exf = ex + p.p.xs * Fft<N, G::PT>::XS;  // the spectrum side's region, for split and extension
     TwCache<N, G::PT> twc;
-    tw_cache_load<N, G::PT>(twc, p.t, tw);
+    tw_cache_load<N, G::PT>(twc, p.p, tw);
     cd v[G::PT];
-    xi_load_pair<N>(p, sh, w.BD, v);
-    fft<N, G::PT, false>(v, p.t, exf, twc);
+    xi_load_pair<N>(p, w.BD, v);
+    fft_fwd<N, G::PT>(v, ex, twc, p.p);
     cd p1[G::PT], p2[G::PT];
     xi_split<N>(v, p.t, exf, 1.0 / N, p1, p2);
 
@@ -222,7 +228,7 @@ __device__ __forceinline__ void xi_col_pass_C(const Shape& sh, int block, const 
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         double jp = Jp[c], tp = dTp[c];
-        col_sum2<G::TPF>(jp, tp, red);
+        col_sum2<N>(jp, tp, red);
         if (p.active && p.t == 0 && (c == 0 || p.two)) {
             double* part = w.partial + ((size_t)p.l * sh.Kx + p.j1 + c) * 2;
             part[0] = jp;
@@ -230,8 +236,8 @@ __device__ __forceinline__ void xi_col_pass_C(const Shape& sh, int block, const 
         }
     }
     xi_extend<N>(v, g1, g2, p.t, sh.Ks, p.two, exf);
-    fft<N, G::PT, true>(v, p.t, exf, twc);
-    xi_store_pair<N>(p, sh, v, w.Cb);
+    fft_inv<N, G::PT>(v, ex, twc, p.p);
+    xi_store_pair<N>(p, v, w.Cb);
 }
 
 // Pass E: the new state U1 - dtau sigma (u r_x)_hat, then the next step's A from it.
@@ -239,13 +245,13 @@ template <int N>
 __device__ __forceinline__ void xi_col_pass_E(const Shape& sh, int block, const XiWork& w, double dtau, int scheme,
                                               bool fuseA, cd* ex, const cd* __restrict__ tw) {
     using G = ColG<N>;
-    const XiColPos p = xi_col_pos<N>(sh, block);
-    cd* exf = ex + p.f * xlen<N>();
+    const XiColPos<N> p(sh, block);
+    cd* exf = ex + p.p.xs * Fft<N, G::PT>::XS;  // the spectrum side's region, for split and extension
     TwCache<N, G::PT> twc;
-    tw_cache_load<N, G::PT>(twc, p.t, tw);
+    tw_cache_load<N, G::PT>(twc, p.p, tw);
     cd v[G::PT];
-    xi_load_pair<N>(p, sh, w.BD, v);
-    fft<N, G::PT, false>(v, p.t, exf, twc);
+    xi_load_pair<N>(p, w.BD, v);
+    fft_fwd<N, G::PT>(v, ex, twc, p.p);
     cd p1[G::PT], p2[G::PT];
     xi_split<N>(v, p.t, exf, 1.0 / N, p1, p2);
     const double Tl = p.active ? w.Told[p.l] : 1.0;
@@ -283,68 +289,71 @@ __device__ __forceinline__ void xi_col_pass_E(const Shape& sh, int block, const 
     }
     if (!fuseA) return;
     xi_extend<N>(v, g1, g2, p.t, sh.Ks, p.two, exf);
-    fft<N, G::PT, true>(v, p.t, exf, twc);
-    xi_store_pair<N>(p, sh, v, w.A);
+    fft_inv<N, G::PT>(v, ex, twc, p.p);
+    xi_store_pair<N>(p, v, w.A);
 }
 
 // -------------------------------------------------------------------------------- rows
-// Element e of the x-spectrum of an odd field (i b_j, j >= 1, conjugate for negative
-// frequencies) and of an even field (real c_j), from real tiles [j-1][r].
-__device__ __forceinline__ cd xi_herm_odd(const double* tile, int TS, int r, int e, int M, int Kx) {
-    const int j = e <= M / 2 ? e : M - e;
-    const bool in = j >= 1 && j <= Kx;
-    const double v = tile[(in ? j - 1 : 0) * TS + r];
-    return in ? cd{0.0, e <= M / 2 ? v : -v} : cd{0.0, 0.0};
-}
-__device__ __forceinline__ cd xi_herm_even(const double* tile, int TS, int r, int e, int M, int Kx) {
-    const int j = e <= M / 2 ? e : M - e;
-    const bool in = j >= 1 && j <= Kx;
-    const double v = tile[(in ? j - 1 : 0) * TS + r];
-    return in ? cd{v, 0.0} : cd{0.0, 0.0};
-}
-
-// Rows [g0, g0 + ROWS) of NT real intermediates into real tiles tile + q * TILE, [j-1][r].
-template <int ROWS, int CMAX, int TS, int TILE, int NT>
-__device__ __forceinline__ void xi_load_rows(double* tile, const double* const (&X)[NT], size_t g0, const Shape& sh,
-                                             size_t nrows) {
-    constexpr int NL = (ROWS * CMAX + kBlock - 1) / kBlock;
-    const int n = ROWS * sh.Kx;
-    double buf[NT][NL];
+// The rows of NT real intermediates for this thread's items (RowLoad for real columns j = 1..Kx):
+// field 0 is odd in x (spectrum i f_j), field 1 even (f_j); their packed spectra are staged.
+template <class G, int NT>
+struct XiRowLoad {
+    double fa[NT][G::NL], fb[NT][G::NL];
+    __device__ __forceinline__ void issue(const double* const (&X)[NT], size_t g0, const Shape& sh, size_t nrows) {
 #pragma unroll
-    for (int k = 0; k < NL; ++k) {
-        const int i = threadIdx.x + k * kBlock;
-        const int j = i / ROWS, r = i % ROWS;
-        const size_t g = g0 + r;
-        const bool ok = i < n && g < nrows;
-        const size_t off = ok ? ((g >> sh.logN) * sh.Kx + j) * sh.N + (g & (size_t)(sh.N - 1)) : 0;
+        for (int k = 0; k < G::NL; ++k) {
+            int p, j;
+            const bool item = row_item<G>(k, p, j) && j > 0;
+            const size_t ga = g0 + p, gb = ga + G::P;
+            const bool oka = item && ga < nrows, okb = item && gb < nrows;
+            const size_t a = oka ? xi_row_offset(ga, j, sh) : 0, b = okb ? xi_row_offset(gb, j, sh) : 0;
 #pragma unroll
-        for (int q = 0; q < NT; ++q) buf[q][k] = ok ? X[q][off] : 0.0;
-    }
-#pragma unroll
-    for (int k = 0; k < NL; ++k) {
-        const int i = threadIdx.x + k * kBlock;
-        if (i < n) {
-            const int j = i / ROWS, r = i % ROWS;
-#pragma unroll
-            for (int q = 0; q < NT; ++q) tile[q * TILE + j * TS + r] = buf[q][k];
+            for (int q = 0; q < NT; ++q) {
+                fa[q][k] = oka ? X[q][a] : 0.0;
+                fb[q][k] = okb ? X[q][b] : 0.0;
+            }
         }
     }
-}
-
-// The imaginary parts of the output tile (an odd product: its real parts vanish) for
-// j = 1..Kx into the real intermediate X.
-template <int ROWS, int CMAX>
-__device__ __forceinline__ void xi_store_rows(const cd* tile, int TS, double* X, size_t g0, const Shape& sh,
-                                              size_t nrows) {
-    constexpr int NL = (ROWS * CMAX + kBlock - 1) / kBlock;
-    const int n = ROWS * sh.Kx;
+    static __device__ __forceinline__ size_t xi_row_offset(size_t g, int j, const Shape& sh) {
+        return ((g >> sh.logN) * sh.Kx + (j - 1)) * sh.N + (g & (size_t)(sh.N - 1));
+    }
+    template <int WR>
+    __device__ __forceinline__ void commit(cd* lds) const {
 #pragma unroll
-    for (int k = 0; k < NL; ++k) {
-        const int i = threadIdx.x + k * kBlock;
-        const int j = i / ROWS, r = i % ROWS;
-        const size_t g = g0 + r;
-        if (i < n && g < nrows)
-            X[((g >> sh.logN) * sh.Kx + j) * sh.N + (g & (size_t)(sh.N - 1))] = tile[(j + 1) * TS + r].y;
+        for (int k = 0; k < G::NL; ++k) {
+            int p, j;
+            if (!row_item<G>(k, p, j)) continue;
+#pragma unroll
+            for (int q = 0; q < NT; ++q) {
+                cd* z = lds + stage_base<G, WR>(p, q);
+                const double f = fa[q][k], g = fb[q][k];  // zero for j = 0: that column vanishes
+                const int neg = j == 0 ? 0 : G::ROW_M - G::SH - j;
+                if (q == 0) {
+                    z[neg] = cd{g, -f};
+                    z[j] = cd{-g, f};
+                } else {
+                    z[neg] = cd{f, g};
+                    z[j] = cd{f, g};
+                }
+            }
+        }
+    }
+};
+
+// The imaginary parts of the rows' half spectra (an odd product: its real parts vanish) for
+// j = 1..Kx, from the staged products, into the real intermediate X.
+template <class G, int WR>
+__device__ __forceinline__ void xi_row_store(const cd* lds, double* X, size_t g0, const Shape& sh, size_t nrows) {
+    constexpr double s = 0.5 / G::ROW_M;
+#pragma unroll
+    for (int k = 0; k < G::NL; ++k) {
+        int p, j;
+        if (!row_item<G>(k, p, j) || j == 0) continue;
+        const cd* z = lds + stage_base<G, WR>(p, 0);
+        const cd a = z[j], b = z[G::ROW_M - G::SH - j];
+        const size_t ga = g0 + p, gb = ga + G::P;
+        if (ga < nrows) X[XiRowLoad<G, 1>::xi_row_offset(ga, j, sh)] = (a.y - b.y) * s;
+        if (gb < nrows) X[XiRowLoad<G, 1>::xi_row_offset(gb, j, sh)] = (b.x - a.x) * s;
     }
 }
 
@@ -352,46 +361,38 @@ template <int M>
 __device__ __forceinline__ void xi_row_pass_B(const Shape& sh, int block, const XiWork& w, cd* lds,
                                               const cd* __restrict__ tw) {
     using G = RowG<M>;
+    constexpr int WR = G::wave_region(1);
     const size_t nrows = (size_t)sh.nloops * sh.N;
     const size_t g0 = (size_t)block * G::ROWS;
-    const int t = threadIdx.x % G::TPF, p = threadIdx.x / G::TPF;
+    const FftPos<M, G::PT> pos(threadIdx.x);
     TwCache<M, G::PT> twc;
-    tw_cache_load<M, G::PT>(twc, t, tw);
-    double* tl = reinterpret_cast<double*>(lds);
-    {
-        const double* const src[1] = {w.A};
-        xi_load_rows<G::ROWS, G::CMAX, G::TS, G::TILE, 1>(tl, src, g0, sh, nrows);
-    }
+    tw_cache_load<M, G::PT>(twc, pos, tw);
+    const double* const src[1] = {w.A};
+    XiRowLoad<G, 1> ld;
+    ld.issue(src, g0, sh, nrows);
+    ld.template commit<WR>(lds);
     __syncthreads();
-    const double dq = kTwoPi / sh.L;
     cd va[G::PT], vb[G::PT];
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) {
-        const int e = t + m * G::TPF;
-        const double q = dq * (double)((e <= M / 2) ? e : e - M);
-        const cd a = xi_herm_odd(tl, G::TS, p, e, M, sh.Kx), b = xi_herm_odd(tl, G::TS, G::P + p, e, M, sh.Kx);
-        va[m] = pack2(a, b);
-        vb[m] = pack2(cd{-q * a.y, q * a.x}, cd{-q * b.y, q * b.x});
-    }
-    row_products<M>(sh, va, vb, lds, t, p, twc);
-    xi_store_rows<G::ROWS, G::CMAX>(lds, G::TS, w.BD, g0, sh, nrows);
+    row_gather<G>(lds + stage_base<G, WR>(pos.xs, 0), pos.t, va);
+    wave_lds_order();
+    row_dx<M, G::PT>(va, pos.t, kTwoPi / sh.L, vb);
+    row_transforms<M, G::PT, 1, WR, false>(sh, lds, pos, twc, va, vb);
+    xi_row_store<G, WR>(lds, w.BD, g0, sh, nrows);
 }
 
 template <int M>
 __device__ __forceinline__ void xi_row_pass_D(const Shape& sh, int block, const XiWork& w, double* T,
                                               double dtau, double* J_hist, cd* lds, const cd* __restrict__ tw) {
     using G = RowG<M>;
+    constexpr int WR = G::wave_region(2);
     const size_t nrows = (size_t)sh.nloops * sh.N;
     const size_t g0 = (size_t)block * G::ROWS;
-    const int t = threadIdx.x % G::TPF, p = threadIdx.x / G::TPF;
+    const FftPos<M, G::PT> pos(threadIdx.x);
     TwCache<M, G::PT> twc;
-    tw_cache_load<M, G::PT>(twc, t, tw);
-    double* tA = reinterpret_cast<double*>(lds);
-    double* tC = tA + G::TILE;
-    {
-        const double* const src[2] = {w.A, w.Cb};
-        xi_load_rows<G::ROWS, G::CMAX, G::TS, G::TILE, 2>(tA, src, g0, sh, nrows);
-    }
+    tw_cache_load<M, G::PT>(twc, pos, tw);
+    const double* const src[2] = {w.A, w.Cb};
+    XiRowLoad<G, 2> ld;
+    ld.issue(src, g0, sh, nrows);
     // loops whose first row lies in this block are finished here (partials from pass C)
     if (threadIdx.x < 64) {
         Shape sx = sh;
@@ -406,16 +407,14 @@ __device__ __forceinline__ void xi_row_pass_D(const Shape& sh, int block, const 
         for (size_t l = l0; (l << sh.logN) < g0 + G::ROWS && l < (size_t)sh.nloops; ++l)
             finalize_loop(sx, (int)l, wf, T, MODE_STEP, dtau, J_hist, nullptr, nullptr);
     }
+    ld.template commit<WR>(lds);
     __syncthreads();
     cd va[G::PT], vb[G::PT];
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) {
-        const int e = t + m * G::TPF;
-        va[m] = pack2(xi_herm_odd(tA, G::TS, p, e, M, sh.Kx), xi_herm_odd(tA, G::TS, G::P + p, e, M, sh.Kx));
-        vb[m] = pack2(xi_herm_even(tC, G::TS, p, e, M, sh.Kx), xi_herm_even(tC, G::TS, G::P + p, e, M, sh.Kx));
-    }
-    row_products<M>(sh, va, vb, lds, t, p, twc);
-    xi_store_rows<G::ROWS, G::CMAX>(lds, G::TS, w.BD, g0, sh, nrows);
+    row_gather<G>(lds + stage_base<G, WR>(pos.xs, 0), pos.t, va);
+    row_gather<G>(lds + stage_base<G, WR>(pos.xs, 1), pos.t, vb);
+    wave_lds_order();
+    row_transforms<M, G::PT, 2, WR, false>(sh, lds, pos, twc, va, vb);
+    xi_row_store<G, WR>(lds, w.BD, g0, sh, nrows);
 }
 
 }  // namespace lo
