@@ -3,24 +3,22 @@
 // the norm ||u||(t) (eq. conventinal_L2norm) recorded along the runs, pairs of its maxima
 // that nearly repeat, and the temporal low-pass that turns a segment into a loop.
 //
-// One wavefront advances one run: a run's state is a few dozen modes, so the whole state,
-// the ETDRK4 coefficients and the stage values stay in registers, and the two transforms of
-// each nonlinear evaluation are direct sums through LDS (the band and the grid of one run
-// fit in a few KB). Thousands of runs fill the chip; HBM sees only the samples.
+// A run's state is a few dozen modes, so the whole state, the ETDRK4 coefficients and the stage
+// values stay in registers, NX/8 lanes per run, and the two transforms of each nonlinear
+// evaluation run through fft.hpp. HBM sees only the samples.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdint>
 
+#include "fft.hpp"
 #include "ks_initial_loops.h"
 
 namespace {
 
-constexpr double kTwoPi = 6.283185307179586476925286766559;
+using lo::cd;
 
-struct cd {
-    double x, y;
-};
+constexpr double kTwoPi = 6.283185307179586476925286766559;
 
 // ----------------------------------------------------------------------------- ETDRK4
 // phi_1..3 of z (phi_k(z) = sum_n z^n / (n + k)!): the series below |z| = 1, the recurrence
@@ -75,172 +73,207 @@ __device__ Etd etd_coeffs(int j, double L, double h) {
     return e;
 }
 
-// Per-run LDS: the band spectrum (K+1 complex), the grid (NX reals), the twiddles
-// e^{2 pi i m / NX} (NX complex), and the partial sums of the forward transform.
-// The forward transform is split into S segments of the grid per mode, so that S (K+1)
-// lanes share its NX (K+1) terms instead of K+1 lanes.
+// Runs of NX points on TPF = NX/8 lanes each, one wavefront per block. Lane t of a run holds the
+// modes e = t + TPF m, m = 0, 1, 2 (NX/3 > K >= e covers no more), zero beyond K.
+//
+// What bounds a step is the chain of its eight transforms in one wavefront: instruction
+// issue (about 930 vector instructions of 4 cycles) and the latency of one LDS exchange per
+// transform; even 4096 runs are only two wavefronts per CU. So the transforms leave out what
+// is known to vanish: the field is the real part of U_0 + 2 sum_{j>=1} U_j e^{i q x}, so the
+// inverse takes five zero slots of eight and only its real part is formed; the forward of
+// the real square is needed in the same three slots. Runs do not share a transform (two
+// rows as real and imaginary part would): a run that overflows leaves its neighbours alone.
+// 4096 runs of 64 modes: 3.4 us per step; as direct sums, one wavefront per run, 18.1.
 template <int NX>
 struct Dns {
     static constexpr int K = (NX - 1) / 3;
     static constexpr int H = NX / 2 + 1;
-    static constexpr int R = (K + 1 + 63) / 64;  // modes per lane
-    static constexpr int P = (NX + 63) / 64;     // grid points per lane
-    static constexpr int S = (2 * (K + 1) <= 64) ? (4 * (K + 1) <= 64 ? (8 * (K + 1) <= 64 ? 8 : 4) : 2) : 1;
-    static constexpr int SEG = NX / S;           // grid points per segment
-    static constexpr int WI = S * (K + 1);       // (segment, mode) partial sums
-    static constexpr int RF = (WI + 63) / 64;    // partial sums per lane
+    using E = lo::Fft<NX, 8>;
+    static constexpr int TPF = E::TPF, RUNS = E::XPW;  // lanes per run, runs per wavefront
+    static constexpr int R = 3;                        // modes per lane
+    static_assert(3 * TPF > K && TPF <= 64, "the band fits three slots");
 };
 
-// N_hat_j = -(i q_j / 2) FFT(u^2)_j for the lane's modes, from the lane's band values v.
-template <int NX>
-__device__ __forceinline__ void nonlinear(const cd (&v)[Dns<NX>::R], const Etd (&co)[Dns<NX>::R], cd (&out)[Dns<NX>::R],
-                                          cd* spec, double* grid, const cd* tw, cd* part) {
-    using D = Dns<NX>;
-    const int lane = threadIdx.x;
-#pragma unroll
-    for (int r = 0; r < D::R; ++r) {
-        const int j = lane + 64 * r;
-        if (j <= D::K) spec[j] = v[r];
-    }
-    __syncthreads();
-    // grid values u(x_m) = Re u_0 + 2 sum_{j=1..K} Re(u_j e^{2 pi i j m / NX}), squared
-#pragma unroll
-    for (int p = 0; p < D::P; ++p) {
-        const int m = lane + 64 * p;
-        if (m < NX) {
-            double s = 0.0;
-            for (int j = 1; j <= D::K; ++j) {
-                const cd a = spec[j];
-                const cd w = tw[(j * m) & (NX - 1)];
-                s += a.x * w.x - a.y * w.y;
-            }
-            const double u = spec[0].x + 2.0 * s;
-            grid[m] = u * u;
-        }
-    }
-    __syncthreads();
-    // W_j = (1/NX) sum_m grid_m e^{-2 pi i j m / NX}: partial sums over segments of m, then
-    // their sum in segment order; N_j = -(i q_j / 2) W_j
-#pragma unroll
-    for (int rr = 0; rr < D::RF; ++rr) {
-        const int wi = lane + 64 * rr;
-        if (wi < D::WI) {
-            const int sg = wi / (D::K + 1), j = wi % (D::K + 1);
-            double wx = 0.0, wy = 0.0;
-            for (int m = sg * D::SEG; m < (sg + 1) * D::SEG; ++m) {
-                const double g = grid[m];
-                const cd w = tw[(j * m) & (NX - 1)];
-                wx += g * w.x;
-                wy -= g * w.y;
-            }
-            part[wi] = cd{wx, wy};
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < D::R; ++r) {
-        const int j = lane + 64 * r;
-        double wx = 0.0, wy = 0.0;
-        if (j <= D::K) {
-#pragma unroll
-            for (int sg = 0; sg < D::S; ++sg) {
-                const cd pw = part[sg * (D::K + 1) + j];
-                wx += pw.x;
-                wy += pw.y;
-            }
-        }
-        const double s = 0.5 * co[r].q / NX;
-        out[r] = cd{s * wy, -s * wx};
-    }
-    __syncthreads();  // spec, grid and the partial sums are free for the next evaluation
+// Inverse DFT of 8 values whose inputs 3 .. 7 are zero (v[0..2] in, v[0..7] out).
+__device__ __forceinline__ void dft8_inv_low3(cd* v) {
+    const cd x0 = v[0], x1 = v[1], x2 = v[2], r2 = lo::rot90<true>(x2);
+    const cd e0 = lo::cadd(x0, x2), e2 = lo::csub(x0, x2), e1 = lo::cadd(x0, r2), e3 = lo::csub(x0, r2);
+    const cd o1 = lo::w16<true, 2>(x1), o2 = lo::rot90<true>(x1), o3 = lo::w16<true, 6>(x1);
+    v[0] = lo::cadd(e0, x1);
+    v[4] = lo::csub(e0, x1);
+    v[1] = lo::cadd(e1, o1);
+    v[5] = lo::csub(e1, o1);
+    v[2] = lo::cadd(e2, o2);
+    v[6] = lo::csub(e2, o2);
+    v[3] = lo::cadd(e3, o3);
+    v[7] = lo::csub(e3, o3);
 }
 
-template <int NX>
-__device__ __forceinline__ void record(int lane, const cd (&u)[Dns<NX>::R], double L, size_t row, double* norms,
-                                       cd* snaps) {
-    using D = Dns<NX>;
-    double e = 0.0;
-#pragma unroll
-    for (int r = 0; r < D::R; ++r) {
-        const int j = lane + 64 * r;
-        if (j <= D::K) e += (j == 0 ? 1.0 : 2.0) * (u[r].x * u[r].x + u[r].y * u[r].y);
-    }
-    for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o, 64);
-    if (norms && lane == 0) norms[row] = sqrt(L * e);
-    if (snaps) {
-        cd* s = snaps + row * D::H;
-        for (int j = lane; j < D::H; j += 64) {
-            cd x{0.0, 0.0};
-#pragma unroll
-            for (int r = 0; r < D::R; ++r)
-                if (j == lane + 64 * r && j <= D::K) x = u[r];
-            s[j] = x;
-        }
-    }
+// Forward DFT of 8 real values (g in, v out).
+__device__ __forceinline__ void dft8_fwd_real(const double* g, cd* v) {
+    const double a0 = g[0] + g[4], a1 = g[0] - g[4], a2 = g[2] + g[6], a3 = g[2] - g[6];
+    const double b0 = g[1] + g[5], b1 = g[1] - g[5], b2 = g[3] + g[7], b3 = g[3] - g[7];
+    const double e0 = a0 + a2, e2 = a0 - a2, o0 = b0 + b2, o2 = b0 - b2;
+    const double c = (b1 - b3) * lo::kSqrtHalf, d = (b1 + b3) * lo::kSqrtHalf;
+    v[0] = cd{e0 + o0, 0.0};
+    v[4] = cd{e0 - o0, 0.0};
+    v[2] = cd{e2, -o2};
+    v[6] = cd{e2, o2};
+    v[1] = cd{a1 + c, -a3 - d};
+    v[7] = cd{a1 + c, a3 + d};
+    v[5] = cd{a1 - c, d - a3};
+    v[3] = cd{a1 - c, a3 - d};
 }
 
-// One block (one wavefront) per run: nsteps ETDRK4 steps of run blockIdx.x.
+// N_hat_j = -(i q_j / 2) FFT(u^2)_j for the lane's modes, from its band values v. hs: q_j / (2 NX).
 template <int NX>
-__global__ __launch_bounds__(64) void k_ks_etdrk4(double L, int sym, double h, int nsteps, int every, cd* uhat,
-                                                  double* norms, cd* snaps, int stride) {
-    using D = Dns<NX>;
-    __shared__ cd spec[D::K + 1];
-    __shared__ double grid[NX];
-    __shared__ cd tw[NX];
-    __shared__ cd part[D::WI];
-    const int lane = threadIdx.x;
-    const size_t run = blockIdx.x;
-    for (int m = lane; m < NX; m += 64) {
-        double s, c;
-        sincospi(2.0 * m / NX, &s, &c);
-        tw[m] = cd{c, s};
+__device__ __forceinline__ void nonlinear(const cd (&v)[3], const double (&hs)[3], const double two0, cd (&out)[3],
+                                          cd* ex, const lo::TwCache<NX, 8>& c, const lo::FftPos<NX, 8>& p) {
+    using E = lo::Fft<NX, 8>;
+    cd w[8];
+    w[0] = cd{two0 * v[0].x, two0 * v[0].y};  // 2 U_j, and U_0
+    w[1] = cd{2.0 * v[1].x, 2.0 * v[1].y};
+    w[2] = cd{2.0 * v[2].x, 2.0 * v[2].y};
+    // lo::fft_inv with the zero inputs left out
+    dft8_inv_low3(w);
+    if constexpr (E::L >= 2) {
+        lo::apply_twiddles<8, 1, true>(w, 0, c.w[1]);
+        lo::exchange<NX, 8, false, 1, false>(w, ex, p);
+        lo::dft_pt<8, true>(w);
     }
-    Etd co[D::R];
-    cd u[D::R];
-    cd* ur = uhat + run * D::H;
+    if constexpr (E::F > 1) {
+        lo::apply_twiddles<8, 1, true>(w, 0, c.w[0]);
+        lo::swap_f<8, E::F>(w);
+        lo::dft_f<8, E::F, true>(w);
+    }
+    if constexpr (E::F == 1) {  // lo::fft_fwd of the real squares
+        double g[8];
 #pragma unroll
-    for (int r = 0; r < D::R; ++r) {
-        const int j = lane + 64 * r;
-        co[r] = etd_coeffs(j <= D::K ? j : 0, L, h);
-        u[r] = j <= D::K ? ur[j] : cd{0.0, 0.0};
+        for (int m = 0; m < 8; ++m) g[m] = w[m].x * w[m].x;
+        dft8_fwd_real(g, w);
+        if constexpr (E::L >= 2) {
+            lo::exchange<NX, 8, false, 1, true>(w, ex, p);
+            lo::apply_twiddles<8, 1, false>(w, 0, c.w[1]);
+            lo::dft_pt<8, false>(w);
+        }
+    } else {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) w[m] = cd{w[m].x * w[m].x, 0.0};
+        lo::fft_fwd<NX, 8>(w, ex, c, p);
+    }
+#pragma unroll
+    for (int r = 0; r < 3; ++r) out[r] = cd{hs[r] * w[r].y, -hs[r] * w[r].x};
+}
+
+// Stores the modes of a run (zero beyond K) into a row of H values; y0: imaginary part of the mean.
+template <int NX>
+__device__ __forceinline__ void store_modes(const cd (&u)[3], double y0, int t, cd* row) {
+    using D = Dns<NX>;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const int j = t + r * D::TPF;
+        if (j <= D::K) row[j] = cd{u[r].x, j == 0 ? y0 : u[r].y};
+    }
+    for (int j = D::K + 1 + t; j < D::H; j += D::TPF) row[j] = cd{0.0, 0.0};
+}
+
+// nsteps ETDRK4 steps of the runs of one wavefront.
+template <int NX>
+__global__ __launch_bounds__(64) void k_ks_etdrk4(double L, int sym, double h, int nsteps, int every, int ntraj,
+                                                  cd* uhat, double* norms, cd* snaps, int stride) {
+    using D = Dns<NX>;
+    __shared__ __align__(16) cd ex[D::RUNS * D::E::XS];
+    __shared__ Etd tab[D::K + 1];
+    const int lane = threadIdx.x;
+    const lo::FftPos<NX, 8> p(lane);
+    const int t = p.t;
+    const size_t run = (size_t)blockIdx.x * D::RUNS + p.xs;
+    const bool live = run < (size_t)ntraj;
+    for (int j = lane; j <= D::K; j += 64) tab[j] = etd_coeffs(j, L, h);
+    lo::TwCache<NX, 8> twc;
+#pragma unroll
+    for (int i = 0; i < D::E::L; ++i) {
+        const int span = i == 0 ? D::E::F : D::E::F * 8;  // as lo::tw_cache_load, at most two stages
+        const int ti = i == D::E::L - 1 ? p.t : p.f0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            double sn, cs;
+            sincospi(-2.0 * (double)(ti << b) / (double)(span * 8), &sn, &cs);
+            twc.w[i][b] = cd{cs, sn};
+        }
+    }
+    __syncthreads();
+    Etd co[3];
+    double hs[3];
+    cd u[3];
+    double y0 = 0.0;
+    cd* ur = uhat + (live ? run : 0) * D::H;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const int j = t + r * D::TPF;
+        const bool in = live && j <= D::K;
+        co[r] = in ? tab[j] : Etd{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        hs[r] = 0.5 * co[r].q / NX;
+        u[r] = in ? ur[j] : cd{0.0, 0.0};
         if (sym) u[r].x = 0.0;
     }
-    __syncthreads();
+    // the field takes the real part of the mean mode; its imaginary part, which no step changes,
+    // is only handed on
+    const double two0 = t == 0 ? 1.0 : 2.0;
+    if (t == 0) {
+        y0 = u[0].y;
+        u[0].y = 0.0;
+    }
+    int left = 0, i_s = 0;  // steps to the next sample, its index
     for (int i = 0; i < nsteps; ++i) {
-        if (i % every == 0) record<NX>(lane, u, L, run * (size_t)stride + i / every, norms, snaps);
-        cd Nu[D::R], Na[D::R], Nb[D::R], Nc[D::R], a[D::R], b[D::R], c[D::R];
-        nonlinear<NX>(u, co, Nu, spec, grid, tw, part);
+        if (left == 0) {
+            left = every;
+            if (norms || snaps) {
+                double e = 0.0;
 #pragma unroll
-        for (int r = 0; r < D::R; ++r)
+                for (int r = 0; r < 3; ++r) {
+                    const bool mean = r == 0 && t == 0;
+                    const double y = mean ? y0 : u[r].y;
+                    e += (mean ? 1.0 : 2.0) * (u[r].x * u[r].x + y * y);
+                }
+                if constexpr (D::E::L == 1) {  // a run's lanes are equal modulo RUNS
+                    for (int o = 32; o >= 64 / D::TPF; o >>= 1) e += __shfl_xor(e, o, 64);
+                } else {
+                    for (int o = D::TPF / 2; o > 0; o >>= 1) e += __shfl_xor(e, o, 64);
+                }
+                const size_t row = run * (size_t)stride + i_s;
+                if (live && norms && t == 0) norms[row] = sqrt(L * e);
+                if (live && snaps) store_modes<NX>(u, y0, t, snaps + row * D::H);
+            }
+            ++i_s;
+        }
+        --left;
+        cd Nu[3], Na[3], Nb[3], Nc[3], a[3], b[3], c[3];
+        nonlinear<NX>(u, hs, two0, Nu, ex, twc, p);
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
             a[r] = cd{co[r].E2 * u[r].x + co[r].Q * Nu[r].x, co[r].E2 * u[r].y + co[r].Q * Nu[r].y};
-        nonlinear<NX>(a, co, Na, spec, grid, tw, part);
+        nonlinear<NX>(a, hs, two0, Na, ex, twc, p);
 #pragma unroll
-        for (int r = 0; r < D::R; ++r)
+        for (int r = 0; r < 3; ++r)
             b[r] = cd{co[r].E2 * u[r].x + co[r].Q * Na[r].x, co[r].E2 * u[r].y + co[r].Q * Na[r].y};
-        nonlinear<NX>(b, co, Nb, spec, grid, tw, part);
+        nonlinear<NX>(b, hs, two0, Nb, ex, twc, p);
 #pragma unroll
-        for (int r = 0; r < D::R; ++r)
+        for (int r = 0; r < 3; ++r)
             c[r] = cd{co[r].E2 * a[r].x + co[r].Q * (2.0 * Nb[r].x - Nu[r].x),
                       co[r].E2 * a[r].y + co[r].Q * (2.0 * Nb[r].y - Nu[r].y)};
-        nonlinear<NX>(c, co, Nc, spec, grid, tw, part);
+        nonlinear<NX>(c, hs, two0, Nc, ex, twc, p);
 #pragma unroll
-        for (int r = 0; r < D::R; ++r) {
+        for (int r = 0; r < 3; ++r) {
             const Etd& e = co[r];
             cd n;
             n.x = e.E * u[r].x + e.f1 * Nu[r].x + 2.0 * e.f2 * (Na[r].x + Nb[r].x) + e.f3 * Nc[r].x;
             n.y = e.E * u[r].y + e.f1 * Nu[r].y + 2.0 * e.f2 * (Na[r].y + Nb[r].y) + e.f3 * Nc[r].y;
             if (sym) n.x = 0.0;
-            const int j = lane + 64 * r;
-            u[r] = j <= D::K ? n : cd{0.0, 0.0};
+            u[r] = n;
         }
     }
-    for (int j = lane; j < D::H; j += 64) {
-        cd x{0.0, 0.0};
-#pragma unroll
-        for (int r = 0; r < D::R; ++r)
-            if (j == lane + 64 * r && j <= D::K) x = u[r];
-        ur[j] = x;
-    }
+    if (live) store_modes<NX>(u, y0, t, ur);
 }
 
 // ------------------------------------------------------------------------- recurrences
@@ -335,6 +368,14 @@ __global__ __launch_bounds__(256) void k_ks_segments(const cd* snaps, int H, int
 
 bool pow2_size(int n, int lo, int hi) { return n >= lo && n <= hi && (n & (n - 1)) == 0; }
 
+template <int NX>
+void launch_runs(double L, int sym, double dt, int nsteps, int every, int ntraj, cd* u, double* norms, cd* snaps,
+                 int stride, hipStream_t st) {
+    constexpr int R = Dns<NX>::RUNS;
+    hipLaunchKernelGGL(k_ks_etdrk4<NX>, dim3((ntraj + R - 1) / R), dim3(64), 0, st, L, sym, dt, nsteps, every, ntraj, u,
+                       norms, snaps, stride);
+}
+
 int hip_status() { return hipGetLastError() == hipSuccess ? LOOP_OK : LOOP_EHIP; }
 
 }  // namespace
@@ -357,11 +398,11 @@ int ks_integrate(double L, int Nx, int ntraj, int symmetric, double dt, int nste
     cd* sn = reinterpret_cast<cd*>(snaps);
     const int sym = symmetric ? 1 : 0;
     switch (Nx) {
-        case 16: hipLaunchKernelGGL(k_ks_etdrk4<16>, dim3(ntraj), dim3(64), 0, st, L, sym, dt, nsteps, sample_every, u, norms, sn, sample_stride); break;
-        case 32: hipLaunchKernelGGL(k_ks_etdrk4<32>, dim3(ntraj), dim3(64), 0, st, L, sym, dt, nsteps, sample_every, u, norms, sn, sample_stride); break;
-        case 64: hipLaunchKernelGGL(k_ks_etdrk4<64>, dim3(ntraj), dim3(64), 0, st, L, sym, dt, nsteps, sample_every, u, norms, sn, sample_stride); break;
-        case 128: hipLaunchKernelGGL(k_ks_etdrk4<128>, dim3(ntraj), dim3(64), 0, st, L, sym, dt, nsteps, sample_every, u, norms, sn, sample_stride); break;
-        case 256: hipLaunchKernelGGL(k_ks_etdrk4<256>, dim3(ntraj), dim3(64), 0, st, L, sym, dt, nsteps, sample_every, u, norms, sn, sample_stride); break;
+        case 16: launch_runs<16>(L, sym, dt, nsteps, sample_every, ntraj, u, norms, sn, sample_stride, st); break;
+        case 32: launch_runs<32>(L, sym, dt, nsteps, sample_every, ntraj, u, norms, sn, sample_stride, st); break;
+        case 64: launch_runs<64>(L, sym, dt, nsteps, sample_every, ntraj, u, norms, sn, sample_stride, st); break;
+        case 128: launch_runs<128>(L, sym, dt, nsteps, sample_every, ntraj, u, norms, sn, sample_stride, st); break;
+        case 256: launch_runs<256>(L, sym, dt, nsteps, sample_every, ntraj, u, norms, sn, sample_stride, st); break;
     }
     return hip_status();
 }
