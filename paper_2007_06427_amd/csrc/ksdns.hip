@@ -298,46 +298,128 @@ __device__ int scan_from(const double* n, int a, int ns, double dt_s, double tol
 }
 
 constexpr int kScanBlock = 256;
+constexpr int kMaxList = 2048;  // maxima of a run kept in LDS
 
-// One block per run. Tiles of 256 consecutive candidate samples a: each thread counts its
-// pairs, an exclusive scan over the tile (in order of a) places them, then they are written.
+// Exclusive prefix sum of v over the block (in thread order); total: the block's sum.
+__device__ __forceinline__ int block_scan(int v, int* sums, int& total) {
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    int x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) sums[wave] = x;
+    __syncthreads();
+    int before = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < kScanBlock / 64; ++w) {
+        if (w < wave) before += sums[w];
+        total += sums[w];
+    }
+    __syncthreads();
+    return before + x - v;
+}
+
+// One block per run. The run's maxima (one sample in tens) are listed in LDS, in order; a
+// wavefront then tests the pairs of one maximum a against 64 later ones at a time, once to
+// count them, and once more, after a prefix sum over the maxima, to write them. Walking every
+// sample after each maximum instead is a chain of dependent loads: with ks_segments_to_loops on
+// 128 runs of 2000 samples and 256 loops it took 3539 us for the two, against 47.
+// A run of more than kMaxList maxima takes that walk: tiles of 256 candidate samples a, each
+// thread counts its pairs, an exclusive scan over the tile places them.
 __global__ __launch_bounds__(kScanBlock) void k_ks_recurrences(const double* norms, int stride, int ns, double dt_s,
                                                                double tol, double Tmin, double Tmax, int cap,
                                                                int2* pairs, int* counts) {
-    __shared__ int sc[kScanBlock];
-    __shared__ int base_s;
+    __shared__ int sums[kScanBlock / 64];
+    __shared__ double val[kMaxList];
+    __shared__ int idx[kMaxList], cnt[kMaxList];
     const double* n = norms + (size_t)blockIdx.x * stride;
     int2* out = pairs + (size_t)blockIdx.x * cap;
-    const int t = threadIdx.x;
-    if (t == 0) base_s = 0;
+    const int t = threadIdx.x, lane = t % 64, wave = t / 64;
+    int nm = 0;  // maxima so far
+    for (int a0 = 0; a0 < ns; a0 += kScanBlock) {
+        const int a = a0 + t;
+        const bool m = a < ns && is_max(n, a, ns);
+        int total;
+        const int at = nm + block_scan(m, sums, total);
+        if (m && at < kMaxList) {
+            idx[at] = a;
+            val[at] = n[a];
+        }
+        nm += total;
+    }
     __syncthreads();
+    if (nm <= kMaxList) {
+        // pairs (a, b) of the maximum at position i of the list with later ones, in order of b;
+        // write >= 0: stored from pair number write on. Returns their count (all lanes).
+        auto scan = [&](int i, int write) {
+            const int a = idx[i];
+            const double va = val[i];
+            int c = 0;
+            for (int k0 = i + 1; k0 < nm; k0 += 64) {
+                const int k = k0 + lane;
+                const double T = k < nm ? (double)(idx[k] - a) * dt_s : 0.0;
+                const bool in = k < nm && !(T > Tmax);
+                const bool hit = in && T >= Tmin && fabs(val[k] - va) <= tol * va;
+                const unsigned long long hits = __ballot(hit);
+                if (write >= 0 && hit) {
+                    const int at = write + c + __popcll(hits & ((1ull << lane) - 1));
+                    if (at < cap) out[at] = make_int2(a, idx[k]);
+                }
+                c += __popcll(hits);
+                if (__ballot(in) != ~0ull) break;  // the rest lies beyond Tmax, or past the list
+            }
+            return c;
+        };
+        for (int i = wave; i < nm; i += kScanBlock / 64) {
+            const int c = scan(i, -1);
+            if (lane == 0) cnt[i] = c;
+        }
+        __syncthreads();
+        int base = 0;
+        for (int i0 = 0; i0 < nm; i0 += kScanBlock) {  // counts -> first pair numbers
+            const int i = i0 + t;
+            int total;
+            const int c = i < nm ? cnt[i] : 0;
+            const int at = base + block_scan(c, sums, total);
+            if (i < nm) cnt[i] = c > 0 ? at : -1;
+            base += total;
+        }
+        __syncthreads();
+        for (int i = wave; i < nm; i += kScanBlock / 64)
+            if (cnt[i] >= 0 && cnt[i] < cap) scan(i, cnt[i]);
+        if (t == 0) counts[blockIdx.x] = base;
+        return;
+    }
+    int base = 0;
     for (int a0 = 0; a0 < ns; a0 += kScanBlock) {
         const int a = a0 + t;
         const bool m = a < ns && is_max(n, a, ns);
         const int c = m ? scan_from(n, a, ns, dt_s, tol, Tmin, Tmax, nullptr, 0, 0) : 0;
-        sc[t] = c;
-        __syncthreads();
-        for (int o = 1; o < kScanBlock; o <<= 1) {  // inclusive Hillis-Steele scan
-            const int v = t >= o ? sc[t - o] : 0;
-            __syncthreads();
-            sc[t] += v;
-            __syncthreads();
-        }
-        const int base = base_s;
-        if (m && c > 0) scan_from(n, a, ns, dt_s, tol, Tmin, Tmax, out, base + sc[t] - c, cap);
-        __syncthreads();
-        if (t == kScanBlock - 1) base_s = base + sc[t];
-        __syncthreads();
+        int total;
+        const int at = base + block_scan(c, sums, total);
+        if (m && c > 0) scan_from(n, a, ns, dt_s, tol, Tmin, Tmax, out, at, cap);
+        base += total;
     }
-    if (t == 0) counts[blockIdx.x] = base_s;
+    if (t == 0) counts[blockIdx.x] = base;
 }
 
 // ------------------------------------------------------------------- segments to loops
-// One block per loop; each thread forms loop entries (k, j) of the rfft layout:
-// c_{j,k} = (1/n) sum_i u_hat_j(t_{a+i}) e^{-2 pi i k i / n} for |k| <= kc, j <= Kx, else 0.
-__global__ __launch_bounds__(256) void k_ks_segments(const cd* snaps, int H, int ntraj, int ns, int stride,
-                                                     const int* triples, double dt_s, int Ns, int kc, cd* loops,
-                                                     double* T) {
+// One block per loop. c_{j,k} = (1/n) sum_i u_hat_j(t_{a+i}) e^{-2 pi i k i / n} for |k| <= kc,
+// j <= Kx (0 elsewhere) from the sums C_jk = sum_i u_hat_j cos and S_jk = sum_i u_hat_j sin of
+// 2 pi k i / n, which give both signs of k: c_{j,+-k} = (C -+ i S) / n. Eight lanes share an item,
+// (j, four k's), each taking every eighth sample, so a sample is loaded once for four k's
+// and the lanes' sums are added in a fixed order. The n roots of unity sit in LDS: evaluating
+// sincospi per term, as one thread per (j, k) did, costs two hundred instructions instead of one
+// LDS read, and is kept only where the roots do not fit (n > kRoots).
+constexpr int kSegBlock = 1024, kSegLanes = 8, kSegK = 4, kRoots = 4096;
+
+__global__ __launch_bounds__(kSegBlock) void k_ks_segments(const cd* snaps, int H, int ntraj, int ns, int stride,
+                                                           const int* triples, double dt_s, int Ns, int kc, cd* loops,
+                                                           double* T) {
+    __shared__ __align__(16) cd root[kRoots];  // e^{2 pi i m / n}
     const int l = blockIdx.x;
     const int tr = triples[3 * l], a = triples[3 * l + 1], b = triples[3 * l + 2];
     const int n = b - a;
@@ -345,24 +427,76 @@ __global__ __launch_bounds__(256) void k_ks_segments(const cd* snaps, int H, int
     const int Kx = (2 * (H - 1) - 1) / 3;
     cd* out = loops + (size_t)l * Ns * H;
     if (threadIdx.x == 0) T[l] = ok ? (double)n * dt_s : 0.0;
-    const cd* seg = ok ? snaps + ((size_t)tr * stride + a) * H : nullptr;
-    for (int e = threadIdx.x; e < Ns * H; e += blockDim.x) {
+    for (int e = threadIdx.x; e < Ns * H; e += kSegBlock) {  // entries outside the low-pass
         const int row = e / H, j = e % H;
         const int k = row <= Ns / 2 ? row : row - Ns;
-        cd v{0.0, 0.0};
-        if (ok && j <= Kx && k >= -kc && k <= kc) {
-            const long long km = ((long long)k % n + n) % n;
-            double sx = 0.0, sy = 0.0;
-            for (int i = 0; i < n; ++i) {
-                const cd x = seg[(size_t)i * H + j];
-                double s, c;
-                sincospi(2.0 * (double)((km * i) % n) / n, &s, &c);  // e^{+2 pi i k i / n}
-                sx += x.x * c + x.y * s;                              // x * conj(e)
-                sy += x.y * c - x.x * s;
-            }
-            v = cd{sx / n, sy / n};
+        if (!ok || j > Kx || k < -kc || k > kc) out[e] = cd{0.0, 0.0};
+    }
+    if (!ok) return;
+    const bool table = n <= kRoots;
+    auto root_of = [&](int m) {
+        double s, c;
+        sincospi(2.0 * (double)m / n, &s, &c);
+        return cd{c, s};
+    };
+    if (table)
+        for (int m = threadIdx.x; m < n; m += kSegBlock) root[m] = root_of(m);
+    __syncthreads();
+    const cd* seg = snaps + ((size_t)tr * stride + a) * H;
+    const int lane = threadIdx.x % kSegLanes;
+    const int items = (Kx + 1) * ((kc + kSegK) / kSegK);
+    for (int it0 = 0; it0 < items; it0 += kSegBlock / kSegLanes) {
+        const int it = it0 + threadIdx.x / kSegLanes;
+        if (it >= items) continue;  // all lanes of the item
+        const int j = it % (Kx + 1), k0 = it / (Kx + 1) * kSegK;
+        int m[kSegK], step[kSegK];  // (k i) mod n of the lane's next sample
+        cd C[kSegK], S[kSegK];
+#pragma unroll
+        for (int q = 0; q < kSegK; ++q) {
+            m[q] = (int)((long long)(k0 + q) * lane % n);
+            step[q] = (int)((long long)(k0 + q) * kSegLanes % n);
+            C[q] = S[q] = cd{0.0, 0.0};
         }
-        out[e] = v;
+        auto term = [&](const cd x, const cd w, int q) {
+            C[q] = cd{__builtin_fma(x.x, w.x, C[q].x), __builtin_fma(x.y, w.x, C[q].y)};
+            S[q] = cd{__builtin_fma(x.x, w.y, S[q].x), __builtin_fma(x.y, w.y, S[q].y)};
+        };
+        if (table) {
+#pragma unroll 2
+            for (int i = lane; i < n; i += kSegLanes) {
+                const cd x = seg[(size_t)i * H + j];
+#pragma unroll
+                for (int q = 0; q < kSegK; ++q) {
+                    term(x, root[m[q]], q);
+                    m[q] += step[q];
+                    m[q] -= m[q] >= n ? n : 0;
+                }
+            }
+        } else {
+            for (int i = lane; i < n; i += kSegLanes) {
+                const cd x = seg[(size_t)i * H + j];
+#pragma unroll
+                for (int q = 0; q < kSegK; ++q) {
+                    term(x, root_of(m[q]), q);
+                    m[q] = (int)(((long long)m[q] + step[q]) % n);
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kSegK; ++q) {
+#pragma unroll
+            for (int o = 1; o < kSegLanes; o <<= 1) {
+                C[q].x += __shfl_xor(C[q].x, o, 64);
+                C[q].y += __shfl_xor(C[q].y, o, 64);
+                S[q].x += __shfl_xor(S[q].x, o, 64);
+                S[q].y += __shfl_xor(S[q].y, o, 64);
+            }
+            const int k = k0 + q;
+            if (lane == q && k <= kc) {
+                out[(size_t)k * H + j] = cd{(C[q].x + S[q].y) / n, (C[q].y - S[q].x) / n};
+                if (k > 0) out[(size_t)(Ns - k) * H + j] = cd{(C[q].x - S[q].y) / n, (C[q].y + S[q].x) / n};
+            }
+        }
     }
 }
 
@@ -430,7 +564,7 @@ int ks_segments_to_loops(int Nx, int ntraj, int nsamples, const double* snaps, i
         reinterpret_cast<uintptr_t>(triples) % 4 || reinterpret_cast<uintptr_t>(uhat_loops) % 16 ||
         reinterpret_cast<uintptr_t>(T_loops) % 8)
         return LOOP_EINVAL;
-    hipLaunchKernelGGL(k_ks_segments, dim3(nloops), dim3(256), 0, (hipStream_t)stream,
+    hipLaunchKernelGGL(k_ks_segments, dim3(nloops), dim3(kSegBlock), 0, (hipStream_t)stream,
                        reinterpret_cast<const cd*>(snaps), Nx / 2 + 1, ntraj, nsamples, sample_stride, triples, dt_s,
                        Ns, kc, reinterpret_cast<cd*>(uhat_loops), T_loops);
     return hip_status();
