@@ -51,11 +51,7 @@ __device__ __forceinline__ void col_pass_XA(const Shape& sh, int block, const Wo
     tw_cache_load<N, G::PT>(twc, p.p, tw);
     const cd* u = w.U + ((size_t)p.l * sh.C + p.j) * sh.NB;
     cd v[G::PT];
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) {
-        const int kk = band_row(p.t + m * G::TPF, N, sh.Ks);
-        v[m] = (p.active && kk >= 0) ? u[kk] : cd{0.0, 0.0};
-    }
+    band_prefetch<N>(p, u, 0, v);
     x_inverse_pair<N>(sh, p, v, w, ex, twc);
 }
 
@@ -121,10 +117,11 @@ template <int M, int PT>
 __device__ __forceinline__ double points_sum(double x) {
     using E = Fft<M, PT>;
     if constexpr (E::L <= 2) {  // the lanes of k0 (L = 2) and of the radix-F digit
-        for (int o = 32; o >= 64 / E::F; o >>= 1) x += __shfl_xor(x, o, 64);
-        return E::L == 2 ? wsum_lanes(x, PT) : x;
+        x = sum_lanes<32, 64 / E::F>(x);
+        if constexpr (E::L == 2) x = sum_lanes<PT / 2>(x);
+        return x;
     } else {
-        return wsum_lanes(x, E::TPF);
+        return sum_lanes<E::TPF / 2>(x);
     }
 }
 

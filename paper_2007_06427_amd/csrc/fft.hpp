@@ -31,6 +31,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace lo {
 
 struct cd {
@@ -380,6 +382,55 @@ __device__ __forceinline__ void swap_lane_bit(cd& a, cd& b) {
     __builtin_memcpy(&a, u, sizeof(cd));
     __builtin_memcpy(&b, v, sizeof(cd));
 }
+// x + (x of lane ^ O), O a power of two up to 32, without the LDS unit: swaps across rows of 16
+// lanes, DPP moves within them. Every lane of the wavefront must be active.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x) {
+    unsigned u[2];
+    __builtin_memcpy(u, &x, sizeof(x));
+#pragma unroll
+    for (int i = 0; i < 2; ++i) u[i] = __builtin_amdgcn_update_dpp(0u, u[i], CTRL, 0xf, 0xf, true);
+    __builtin_memcpy(&x, u, sizeof(x));
+    return x;
+}
+template <int O>
+__device__ __forceinline__ double add_lane_xor(double x) {
+    if constexpr (O >= 16) {
+        unsigned a[2], b[2];
+        __builtin_memcpy(a, &x, sizeof(x));
+        __builtin_memcpy(b, &x, sizeof(x));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) swap_dword<O>(a[i], b[i]);
+        double p, q;  // the lane's value and its partner's, in the order of the lane bit
+        __builtin_memcpy(&p, a, sizeof(p));
+        __builtin_memcpy(&q, b, sizeof(q));
+        return p + q;
+    } else if constexpr (O == 8) {
+        return x + dpp_move<0x128>(x);  // row_ror:8
+    } else if constexpr (O == 4) {
+        return x + dpp_move<0x1B>(dpp_move<0x141>(x));  // row_half_mirror (xor 7), quad_perm (xor 3)
+    } else if constexpr (O == 2) {
+        return x + dpp_move<0x4E>(x);  // quad_perm [2, 3, 0, 1]
+    } else {
+        return x + dpp_move<0xB1>(x);  // quad_perm [1, 0, 3, 2]
+    }
+}
+// Sum over the lanes that agree in all lane bits but FROM, FROM/2 .. TO (xor tree, FROM first).
+template <int FROM, int TO = 1>
+__device__ __forceinline__ double sum_lanes(double x) {
+    if constexpr (FROM >= TO) return sum_lanes<FROM / 2, TO>(add_lane_xor<FROM>(x));
+    return x;
+}
+
+// Calls f(std::integral_constant<int, m>) for m = 0 .. N-1, unrolled.
+template <int N, int M = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (M < N) {
+        f(std::integral_constant<int, M>{});
+        static_for<N, M + 1>(static_cast<F&&>(f));
+    }
+}
+
 // The low bits of the slot index (F values) against the top lane bits; its own inverse.
 template <int PT, int F>
 __device__ __forceinline__ void swap_f(cd* v) {

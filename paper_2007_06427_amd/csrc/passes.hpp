@@ -109,12 +109,6 @@ __device__ __forceinline__ int band_row(int e, int N, int Ks) {
     return -1;
 }
 
-__device__ __forceinline__ double wsum_lanes(double x, int width) {
-    // sum over aligned groups of `width` lanes (a power of two <= 64), fixed xor-tree order
-    for (int o = width / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
-
 // ---------------------------------------------------------------------------- column passes
 // TPF = N/PT threads per column transform, F = kBlock / TPF columns per block, each thread's
 // columns and positions from FftPos (its spectrum side: column js, band values at t + m TPF; its
@@ -142,13 +136,12 @@ template <int N>
 __device__ __forceinline__ void col_sum2(double& a, double& b, double* red) {
     using G = ColG<N>;
     if constexpr (Fft<N, G::PT>::L == 1) {  // a transform's threads are the lanes equal modulo 64 / TPF
-        for (int o = 32; o >= 64 / G::TPF; o >>= 1) {
-            a += __shfl_xor(a, o, 64);
-            b += __shfl_xor(b, o, 64);
-        }
+        a = sum_lanes<32, 64 / G::TPF>(a);
+        b = sum_lanes<32, 64 / G::TPF>(b);
     } else {
-        a = wsum_lanes(a, G::TPF < 64 ? G::TPF : 64);
-        b = wsum_lanes(b, G::TPF < 64 ? G::TPF : 64);
+        constexpr int W = G::TPF < 64 ? G::TPF : 64;
+        a = sum_lanes<W / 2>(a);
+        b = sum_lanes<W / 2>(b);
     }
     if constexpr (G::TPF > 64) {
         static_assert(G::TPF == 128, "transforms span at most two wavefronts");
@@ -186,18 +179,78 @@ struct ColPos {
     }
 };
 
+// Slot m of a column's spectrum, e = t + m TPF: whether it lies in the band, its band index kk
+// and signed mode k. N fixes the band limit, so most slots are resolved at compile time: only the
+// two that straddle an edge of the band test t. The column passes of the step are bound by
+// vector instructions and memory about equally; with the index arithmetic gone, fused
+// multiply-adds in the band functions below and one division per mode instead of two (pass E),
+// pass C of 64 loops of 256 x 1024 took 64 us instead of 75 and pass E with the next A 58
+// instead of 69.
+template <int N, int m>
+struct BandSlot {
+    static constexpr int TPF = ColG<N>::TPF, Ks = (N - 1) / 3, NB = 2 * Ks + 1;
+    static constexpr int lo = m * TPF, hi = lo + TPF - 1;
+    static constexpr bool neg = lo >= N / 2;
+    static constexpr bool out = lo > Ks && hi < N - Ks;
+    static constexpr bool full = hi <= Ks || lo >= N - Ks;
+    static __device__ __forceinline__ bool in(int t) {
+        return !out && (full || (neg ? lo + t >= N - Ks : lo + t <= Ks));
+    }
+    static __device__ __forceinline__ int kk(int t) { return neg ? lo + t - (N - NB) : lo + t; }
+    static __device__ __forceinline__ int k(int t) { return neg ? lo + t - N : lo + t; }
+};
+
 // The band values of this thread's slots of column (l, j) (zero outside the band or for an
 // inactive column), read through band_get. Column passes issue these loads before their
 // transforms, so that their latency overlaps the transform instead of following it.
 template <int N>
-__device__ __forceinline__ void band_prefetch(const Shape& sh, const ColPos<N>& p, const cd* u, int herm0,
-                                              cd* out) {
-    using G = ColG<N>;
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) {
-        const int kk = band_row(p.t + m * G::TPF, N, sh.Ks);
-        out[m] = (p.active && kk >= 0) ? band_get(u, p.j, kk, sh.NB, herm0) : cd{0.0, 0.0};
+__device__ __forceinline__ void band_prefetch(const ColPos<N>& p, const cd* u, int herm0, cd* out) {
+    static_for<ColG<N>::PT>([&](auto mc) {
+        using B = BandSlot<N, decltype(mc)::value>;
+        out[mc] = (p.active && B::in(p.t)) ? band_get(u, p.j, B::kk(p.t), B::NB, herm0) : cd{0.0, 0.0};
+    });
+}
+
+// The spectral factors of column j, q = 2 pi j / L.
+struct ColCoef {
+    double q;
+    double c;     // q^2 - q^4, of -d_xx - d_xxxx
+    double lamx;  // -q^8 + 2 q^6 - q^4, the x part of lambda
+    __device__ __forceinline__ ColCoef(int j, double L) {
+        q = kTwoPi * j / L;
+        const double q2 = q * q, q4 = q2 * q2;
+        c = q2 - q4;
+        lamx = -q4 * q4 + 2.0 * q4 * q2 - q4;
     }
+};
+
+// The residual (eq. KS_R) of mode (j, k): r = -(i om/T) u - (u u_x)_hat + (q^2 - q^4) u, with a =
+// om / T and w = N (u u_x)_hat. Every form of the step and of the gradient forms its band values
+// through these functions, so that they agree bit for bit.
+__device__ __forceinline__ cd band_residual(const ColCoef& f, double a, double invN, cd u, cd w) {
+    return cd{__builtin_fma(-invN, w.x, __builtin_fma(a, u.y, f.c * u.x)),
+              __builtin_fma(-invN, w.y, __builtin_fma(-a, u.x, f.c * u.y))};
+}
+// G_lin = (-i om/T - q^2 + q^4) r
+__device__ __forceinline__ cd band_glin(const ColCoef& f, double a, cd r) {
+    return cd{__builtin_fma(a, r.y, -(f.c * r.x)), __builtin_fma(-a, r.x, -(f.c * r.y))};
+}
+// dtau sigma: sigma = 1 (explicit) or 1 / (1 - dtau lambda), lambda = lamx - (om/T)^2
+__device__ __forceinline__ double band_step(const ColCoef& f, double a, double dtau, int scheme) {
+    return scheme ? dtau / __builtin_fma(dtau, __builtin_fma(a, a, -f.lamx), 1.0) : dtau;
+}
+// G_1 = G_lin - p_hat and u_hat' = U1 - dtau sigma p_hat, p = N p_hat, p_hat = (u r_x)_hat; s =
+// dtau sigma / N (N is a power of two: the division is exact)
+__device__ __forceinline__ cd band_g1(cd gl, cd p, double invN) {
+    return cd{__builtin_fma(-invN, p.x, gl.x), __builtin_fma(-invN, p.y, gl.y)};
+}
+__device__ __forceinline__ cd band_update(cd u1, cd p, double s) {
+    return cd{__builtin_fma(-s, p.x, u1.x), __builtin_fma(-s, p.y, u1.y)};
+}
+// Adds |r|^2 to J and Re(u_s conj r), u_s = i om u, to dT.
+__device__ __forceinline__ void band_sums(double om, cd u, cd r, double& J, double& dT) {
+    J = __builtin_fma(r.x, r.x, __builtin_fma(r.y, r.y, J));
+    dT = __builtin_fma(om, __builtin_fma(u.x, r.y, -(u.y * r.x)), dT);
 }
 
 // The s-grid values of this thread's slots of its points-side column of X.
@@ -231,7 +284,7 @@ __device__ __forceinline__ void col_pass_A(const Shape& sh, int block, const Wor
     tw_cache_load<N, G::PT>(twc, p.p, tw);
     const cd* u = w.U + ((size_t)p.l * sh.C + p.j) * sh.NB;
     cd v[G::PT];
-    band_prefetch<N>(sh, p, u, w.herm0, v);
+    band_prefetch<N>(p, u, w.herm0, v);
     col_inverse_store<N>(sh, p, v, w.A, ex, twc);
 }
 
@@ -250,9 +303,9 @@ __device__ __forceinline__ void col_pass_AC(const Shape& sh, int block, const Wo
     const cd* r = w.R + col * sh.NB;
     const double q = kTwoPi * p.j / sh.L;
     cd v[G::PT], rv[G::PT];
-    band_prefetch<N>(sh, p, r, 0, rv);  // with WITH_U, in flight during the first transform
+    band_prefetch<N>(p, r, 0, rv);  // with WITH_U, in flight during the first transform
     if constexpr (WITH_U) {
-        band_prefetch<N>(sh, p, w.U + col * sh.NB, w.herm0, v);
+        band_prefetch<N>(p, w.U + col * sh.NB, w.herm0, v);
         col_inverse_store<N>(sh, p, v, w.A, ex, twc);
     }
 #pragma unroll
@@ -269,55 +322,41 @@ __device__ __forceinline__ void col_pass_C(const Shape& sh, int block, const dou
     const size_t col = (size_t)p.l * sh.C + p.j;
     cd v[G::PT], ub[G::PT];
     col_load<N>(sh, p, w.BD, v);
-    band_prefetch<N>(sh, p, w.U + col * sh.NB, w.herm0, ub);  // in flight during the transform
+    band_prefetch<N>(p, w.U + col * sh.NB, w.herm0, ub);  // in flight during the transform
     TwCache<N, G::PT> twc;
     tw_cache_load<N, G::PT>(twc, p.p, tw);
     fft_fwd<N, G::PT>(v, ex, twc, p.p);
 
-    const double Tl = p.active ? T[p.l] : 1.0;
-    const double invT = 1.0 / Tl;
-    const double q = kTwoPi * p.j / sh.L;
-    const double q2 = q * q, q4 = q2 * q2;
-    const double lamx = -q4 * q4 + 2.0 * q4 * q2 - q4;
-    const double invN = 1.0 / N;
-    const double wj = (p.j == 0) ? 1.0 : 2.0;
+    const double invT = 1.0 / (p.active ? T[p.l] : 1.0);
+    const ColCoef f(p.j, sh.L);
+    constexpr double invN = 1.0 / N;
     double Jp = 0.0, dTp = 0.0;
     cd* g = w.G + col * sh.NB;
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) {
-        const int e = p.t + m * G::TPF;
-        const int kk = band_row(e, N, sh.Ks);
+    static_for<G::PT>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        using B = BandSlot<N, m>;
         cd x{0.0, 0.0};
-        if (p.active && kk >= 0) {
-            const int k = (e < N / 2) ? e : e - N;
-            const double om = kTwoPi * k;
-            const cd wh = cscale(v[m], invN);  // (u u_x)_hat
-            const cd uu = ub[m];
-            const double a = om * invT;
-            // r = -(i om/T) u - (u u_x)_hat + (q^2 - q^4) u
-            cd r;
-            r.x = a * uu.y - wh.x + (q2 - q4) * uu.x;
-            r.y = -a * uu.x - wh.y + (q2 - q4) * uu.y;
-            Jp += wj * (r.x * r.x + r.y * r.y);
-            dTp += wj * om * (uu.x * r.y - uu.y * r.x);  // Re(u_s conj r), u_s = i om u
+        if (p.active && B::in(p.t)) {
+            const double om = kTwoPi * B::k(p.t), a = om * invT;
+            const cd r = band_residual(f, a, invN, ub[m], v[m]);
+            band_sums(om, ub[m], r, Jp, dTp);
             if (mode == MODE_RESIDUAL) {
-                g[kk] = r;
+                g[B::kk(p.t)] = r;
             } else if (mode >= MODE_GRAD) {
-                // G_lin = (-i om/T - q^2 + q^4) r
-                cd gl;
-                gl.x = a * r.y + (q4 - q2) * r.x;
-                gl.y = -a * r.x + (q4 - q2) * r.y;
+                cd gl = band_glin(f, a, r);
                 if (mode == MODE_STEP) {
-                    const double sig = scheme ? 1.0 / (1.0 - dtau * (lamx - a * a)) : 1.0;
-                    const double s = dtau * sig;
-                    gl = cd{uu.x + s * gl.x, uu.y + s * gl.y};  // U1
+                    const double s = band_step(f, a, dtau, scheme);
+                    gl = cd{__builtin_fma(s, gl.x, ub[m].x), __builtin_fma(s, gl.y, ub[m].y)};  // U1
                 }
-                g[kk] = gl;
+                g[B::kk(p.t)] = gl;
             }
-            x = cd{-q * r.y, q * r.x};  // i q r
+            x = cd{-f.q * r.y, f.q * r.x};  // i q r
         }
         v[m] = x;
-    }
+    });
+    const double wj = (p.j == 0) ? 1.0 : 2.0;
+    Jp *= wj;
+    dTp *= wj;
     col_sum2<N>(Jp, dTp, red);
     if (p.active && p.t == 0) {
         w.partial[2 * col] = Jp;
@@ -338,17 +377,16 @@ __device__ __forceinline__ void col_pass_E(const Shape& sh, int block, const Wor
     // G_lin or (reverse mode) the saved residual, in flight during the transform. In the step
     // (U1, then the next step's pass A on the new column) the loads issued after the transform
     // measured faster: pass E at 256 x 1024 took 70.4 us against 75.8 with them in flight.
-    if (mode != MODE_STEP) band_prefetch<N>(sh, p, (mode == MODE_ADJOINT ? w.R : w.G) + col * sh.NB, 0, gb);
+    if (mode != MODE_STEP) band_prefetch<N>(p, (mode == MODE_ADJOINT ? w.R : w.G) + col * sh.NB, 0, gb);
     TwCache<N, G::PT> twc;
     tw_cache_load<N, G::PT>(twc, p.p, tw);
     fft_fwd<N, G::PT>(v, ex, twc, p.p);
-    if (mode == MODE_STEP) band_prefetch<N>(sh, p, w.G + col * sh.NB, 0, gb);
+    if (mode == MODE_STEP) band_prefetch<N>(p, w.G + col * sh.NB, 0, gb);
 
-    const double invN = 1.0 / N;
-    const double q = kTwoPi * p.j / sh.L;
-    const double q2 = q * q, q4 = q2 * q2;
-    const double lamx = -q4 * q4 + 2.0 * q4 * q2 - q4;
-    const double Tl = (mode == MODE_STEP && p.active) ? w.Told[p.l] : (mode == MODE_ADJOINT && p.active) ? T[p.l] : 1.0;
+    constexpr double invN = 1.0 / N;
+    const ColCoef f(p.j, sh.L);
+    const double invT =
+        1.0 / ((mode == MODE_STEP && p.active) ? w.Told[p.l] : (mode == MODE_ADJOINT && p.active) ? T[p.l] : 1.0);
     // reverse mode: G_1 scaled by -gJ_l w_j L, the gradient of sum_l gJ_l J_l in torch's
     // complex convention (gJ folded in by the caller as scale_l = -gJ_l L)
     const double sc = (mode == MODE_ADJOINT && p.active) ? (w.gJ ? -w.gJ[p.l] : -1.0) * sh.L * (p.j == 0 ? 1.0 : 2.0)
@@ -357,43 +395,25 @@ __device__ __forceinline__ void col_pass_E(const Shape& sh, int block, const Wor
     cd* u = w.U + col * sh.NB;
     if (mode == MODE_ADJOINT && w.grad_T && p.active && p.j == 0 && p.t == 0)
         w.grad_T[p.l] = (w.gJ ? w.gJ[p.l] : 1.0) * w.dJdT_in[p.l];
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) {
-        const int e = p.t + m * G::TPF;
-        const int kk = band_row(e, N, sh.Ks);
+    static_for<G::PT>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        using B = BandSlot<N, m>;
         cd x{0.0, 0.0};
-        if (p.active && kk >= 0) {
-            const cd ph = cscale(v[m], invN);  // (u r_x)_hat
+        if (p.active && B::in(p.t)) {
+            const double a = kTwoPi * B::k(p.t) * invT;
             if (mode == MODE_ADJOINT) {
-                // G_lin = (-i om/T - q^2 + q^4) r, as pass C forms it, then G_1 = G_lin - p_hat
-                const cd rr = gb[m];
-                const int k = (e < N / 2) ? e : e - N;
-                const double a = kTwoPi * k * (1.0 / Tl);
-                cd gl;
-                gl.x = a * rr.y + (q4 - q2) * rr.x;
-                gl.y = -a * rr.x + (q4 - q2) * rr.y;
-                const cd g1 = csub(gl, ph);
-                g[kk] = cd{sc * g1.x, sc * g1.y};
-                v[m] = x;
-                continue;
-            }
-            const cd gg = gb[m];
-            if (mode == MODE_STEP) {
-                double sig = 1.0;
-                if (scheme) {
-                    const int k = (e < N / 2) ? e : e - N;
-                    const double a = kTwoPi * k / Tl;
-                    sig = 1.0 / (1.0 - dtau * (lamx - a * a));
-                }
-                const double s = dtau * sig;
-                x = cd{gg.x - s * ph.x, gg.y - s * ph.y};  // u_hat' = U1 - dtau sigma p_hat
-                u[kk] = x;
+                // G_lin as pass C forms it, then G_1 = G_lin - p_hat, p_hat = (u r_x)_hat
+                const cd g1 = band_g1(band_glin(f, a, gb[m]), v[m], invN);
+                g[B::kk(p.t)] = cd{sc * g1.x, sc * g1.y};
+            } else if (mode == MODE_STEP) {
+                x = band_update(gb[m], v[m], band_step(f, a, dtau, scheme) * invN);
+                u[B::kk(p.t)] = x;
             } else {
-                g[kk] = csub(gg, ph);  // G_1 = G_lin - p_hat
+                g[B::kk(p.t)] = band_g1(gb[m], v[m], invN);
             }
         }
         v[m] = x;
-    }
+    });
     if (mode == MODE_STEP && fuseA) col_inverse_store<N>(sh, p, v, w.A, ex, twc);
 }
 
@@ -616,28 +636,32 @@ __device__ __forceinline__ void load_rows_lds(cd* tile, const cd* const (&X)[NT]
     if constexpr (WAIT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// Element e of the Hermitian extension of half spectrum tile[j][r] (j < C; X_0 read as real):
-// tile[e] for e <= Kx, conj(tile[M - e]) for e >= M - Kx, zero between. Written without
-// branches (one read of a valid element, then selects), since e differs across the lanes of
-// a transform.
-__device__ __forceinline__ cd herm_ext(const cd* tile, int TS, int r, int e, int M, int Kx) {
-    const int j = e <= M / 2 ? e : M - e;  // |frequency|
-    const bool in = j <= Kx;
-    const cd v = tile[(in ? j : 0) * TS + r];
-    const double y = e == 0 ? 0.0 : (e > M / 2 ? -v.y : v.y);
-    return in ? cd{v.x, y} : cd{0.0, 0.0};
-}
-
-// Spectrum of f + i g for two real rows f, g given by their half spectra (packed complex).
-__device__ __forceinline__ cd pack2(cd f, cd g) { return cd{f.x - g.y, f.y + g.x}; }
-
-// herm_pack for raw tiles: va[m] = pack2 of rows ra and rb of a tile at e = t + m TPF.
-template <int M, int PT>
-__device__ __forceinline__ void herm_pack(const cd* tile, int TS, int ra, int rb, int t, cd* va) {
-    constexpr int TPF = M / PT, Kx = (M - 1) / 3;
-#pragma unroll
-    for (int m = 0; m < PT; ++m)
-        va[m] = pack2(herm_ext(tile, TS, ra, t + m * TPF, M, Kx), herm_ext(tile, TS, rb, t + m * TPF, M, Kx));
+// F + i G of rows ra (F) and rb (G) of an array X[j][r] (stride ld) of half spectra, in the slots of thread
+// t; slots outside the band are zero. B_ROW false: row b is empty. The values are those that
+// RowLoad stages.
+template <class G, bool B_ROW, int m = 0>
+__device__ __forceinline__ void row_gather_raw(const cd* X, int ld, int ra, int rb, int t, cd* v) {
+    if constexpr (m < G::PT) {
+        constexpr int lo = m * G::TPF, hi = lo + G::TPF - 1, Kx = G::Kx, M = G::ROW_M;
+        auto get = [&](int j, bool conj, bool zero_im) {
+            const cd f = X[j * ld + ra], g = B_ROW ? X[j * ld + rb] : cd{0.0, 0.0};
+            const double fy = zero_im ? 0.0 : f.y, gy = zero_im ? 0.0 : g.y;  // X_0 is read as real
+            return conj ? cd{f.x + gy, g.x - fy} : cd{f.x - gy, fy + g.x};
+        };
+        if constexpr (hi <= Kx) {
+            v[m] = get(lo + t, false, lo == 0 && t == 0);
+        } else if constexpr (lo >= M - Kx) {
+            v[m] = get(M - lo - t, true, false);
+        } else if constexpr (lo > Kx && hi < M - Kx) {
+            v[m] = cd{0.0, 0.0};
+        } else {
+            const int e = lo + t;
+            const bool neg = lo >= M / 2, in = neg ? e >= M - Kx : e <= Kx;
+            const cd x = get(in ? (neg ? M - e : e) : 0, neg, lo == 0 && t == 0);
+            v[m] = in ? x : cd{0.0, 0.0};
+        }
+        row_gather_raw<G, B_ROW, m + 1>(X, ld, ra, rb, t, v);
+    }
 }
 
 // Pass B forms u u_x as (1/2) (u^2)_x (two transforms per pair of rows) for rows of up to
@@ -732,7 +756,7 @@ __device__ __forceinline__ void row_pass_B(const Shape& sh, int block, const Wor
         if constexpr (DMA) {
             load_rows_lds<G::ROWS, G::CMAX, G::TS, G::TILE, 1>(lds, src, g0, sh, nrows);
             __syncthreads();
-            herm_pack<M, PT>(lds, G::TS, pos.xs, G::P + pos.xs, pos.t, va);
+            row_gather_raw<G, true>(lds, G::TS, pos.xs, G::P + pos.xs, pos.t, va);
             __syncthreads();  // every wavefront has read the tile: its regions are free
         } else {
             RowLoad<G, 1> ld;
@@ -770,8 +794,8 @@ __device__ __forceinline__ void finalize_loop(const Shape& sh, int l, const Work
         sj += pp[2 * j];
         st += pp[2 * j + 1];
     }
-    sj = wsum_lanes(sj, 64);
-    st = wsum_lanes(st, 64);
+    sj = sum_lanes<32>(sj);
+    st = sum_lanes<32>(st);
     if (lane != 0) return;
     const double Tl = T[l];
     const double J = 0.5 * sh.L * sj;
@@ -820,8 +844,8 @@ __device__ __forceinline__ void row_pass_D(const Shape& sh, int block, const Wor
             if (first) finalize();
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            herm_pack<M, PT>(lds, G::TS, pos.xs, G::P + pos.xs, pos.t, va);
-            herm_pack<M, PT>(lds + G::TILE, G::TS, pos.xs, G::P + pos.xs, pos.t, vb);
+            row_gather_raw<G, true>(lds, G::TS, pos.xs, G::P + pos.xs, pos.t, va);
+            row_gather_raw<G, true>(lds + G::TILE, G::TS, pos.xs, G::P + pos.xs, pos.t, vb);
             __syncthreads();  // every wavefront has read the tiles: its regions are free
         } else {
             RowLoad<G, 2> ld;

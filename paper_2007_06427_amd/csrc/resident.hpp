@@ -49,17 +49,19 @@ struct ResG {
     static constexpr int ROW_ROUNDS = (N + RowG<M>::ROWS - 1) / RowG<M>::ROWS;
 };
 
-// The packed spectrum (the Hermitian extensions of rows a and b of a resident [j][n] array, zero
-// for rows past the loop, as the HBM form stages them) in the slots of a thread.
+// F + i G of rows a and b of a resident [j][n] array (zero for rows past the loop, as the HBM
+// form stages them) in the slots of a thread.
 template <int M>
 __device__ __forceinline__ void res_gather(const Shape& sh, const cd* X, int t, int a, int b, bool oka, bool okb,
                                            cd* v) {
     using G = RowG<M>;
+    if (okb) {
+        row_gather_raw<G, true>(X, sh.ld, a, b, t, v);
+    } else {
+        row_gather_raw<G, false>(X, sh.ld, oka ? a : 0, 0, t, v);
+        if (!oka)
 #pragma unroll
-    for (int m = 0; m < G::PT; ++m) {
-        const int e = t + m * G::TPF;
-        const cd f = herm_ext(X, sh.ld, oka ? a : 0, e, M, G::Kx), g = herm_ext(X, sh.ld, okb ? b : 0, e, M, G::Kx);
-        v[m] = pack2(oka ? f : cd{0.0, 0.0}, okb ? g : cd{0.0, 0.0});
+            for (int m = 0; m < G::PT; ++m) v[m] = cd{0.0, 0.0};
     }
 }
 

@@ -182,49 +182,42 @@ __device__ __forceinline__ void xi_col_pass_C(const Shape& sh, int block, const 
     cd p1[G::PT], p2[G::PT];
     xi_split<N>(v, p.t, exf, 1.0 / N, p1, p2);
 
-    const double Tl = p.active ? T[p.l] : 1.0;
-    const double invT = 1.0 / Tl;
+    const double invT = 1.0 / (p.active ? T[p.l] : 1.0);
     const int K1 = sh.Ks + 1;
+    const ColCoef f[2] = {ColCoef(p.j1 + 1, sh.L), ColCoef(p.j1 + 2, sh.L)};
     double Jp[2] = {0.0, 0.0}, dTp[2] = {0.0, 0.0};
     cd g1[G::PT], g2[G::PT];
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) {
+    static_for<G::PT>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        using B = BandSlot<N, m>;
         g1[m] = cd{0.0, 0.0};
         g2[m] = cd{0.0, 0.0};
+        if (B::neg || !p.active || !B::in(p.t)) return;  // k = 0 .. Ks
         const int e = p.t + m * G::TPF;
-        if (!p.active || e > sh.Ks) continue;
         const double om = kTwoPi * e;
         const double a = om * invT;
-        const double wk = (e == 0) ? 2.0 : 4.0;  // w_j = 2 (j >= 1), k > 0 counted twice
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             if (c == 1 && !p.two) break;
-            const int jj = p.j1 + c;  // j - 1
-            const double q = kTwoPi * (jj + 1) / sh.L;
-            const double q2 = q * q, q4 = q2 * q2;
-            const double lamx = -q4 * q4 + 2.0 * q4 * q2 - q4;
-            const size_t at = ((size_t)p.l * sh.Kx + jj) * K1 + e;
+            const size_t at = ((size_t)p.l * sh.Kx + p.j1 + c) * K1 + e;
             const cd b = w.U[at];
-            const cd wh = c == 0 ? p1[m] : p2[m];
-            // r = -(i om/T) b - (u u_x) + (q^2 - q^4) b in the b form
-            cd r;
-            r.x = a * b.y - wh.x + (q2 - q4) * b.x;
-            r.y = -a * b.x - wh.y + (q2 - q4) * b.y;
-            Jp[c] += wk * (r.x * r.x + r.y * r.y);
-            dTp[c] += wk * om * (b.x * r.y - b.y * r.x);
-            cd gl;
-            gl.x = a * r.y + (q4 - q2) * r.x;
-            gl.y = -a * r.x + (q4 - q2) * r.y;
-            const double sig = scheme ? 1.0 / (1.0 - dtau * (lamx - a * a)) : 1.0;
-            const double st = dtau * sig;
-            w.G[at] = cd{b.x + st * gl.x, b.y + st * gl.y};  // U1
-            const cd rx = cd{-q * r.x, -q * r.y};            // (r_x)_hat in the real-column form
+            // the residual, sums and update in the b form; w_j = 2 (j >= 1), k > 0 counted twice
+            const cd r = band_residual(f[c], a, 1.0, b, c == 0 ? p1[m] : p2[m]);
+            double j = 0.0, t = 0.0;
+            band_sums(om, b, r, j, t);
+            const double wk = (e == 0) ? 2.0 : 4.0;
+            Jp[c] = __builtin_fma(wk, j, Jp[c]);
+            dTp[c] = __builtin_fma(wk, t, dTp[c]);
+            const cd gl = band_glin(f[c], a, r);
+            const double st = band_step(f[c], a, dtau, scheme);
+            w.G[at] = cd{__builtin_fma(st, gl.x, b.x), __builtin_fma(st, gl.y, b.y)};  // U1
+            const cd rx = cd{-f[c].q * r.x, -f[c].q * r.y};  // (r_x)_hat in the real-column form
             if (c == 0)
                 g1[m] = rx;
             else
                 g2[m] = rx;
         }
-    }
+    });
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         double jp = Jp[c], tp = dTp[c];
@@ -254,39 +247,30 @@ __device__ __forceinline__ void xi_col_pass_E(const Shape& sh, int block, const 
     fft_fwd<N, G::PT>(v, ex, twc, p.p);
     cd p1[G::PT], p2[G::PT];
     xi_split<N>(v, p.t, exf, 1.0 / N, p1, p2);
-    const double Tl = p.active ? w.Told[p.l] : 1.0;
+    const double invT = 1.0 / (p.active ? w.Told[p.l] : 1.0);
     const int K1 = sh.Ks + 1;
+    const ColCoef f[2] = {ColCoef(p.j1 + 1, sh.L), ColCoef(p.j1 + 2, sh.L)};
     cd g1[G::PT], g2[G::PT];
-#pragma unroll
-    for (int m = 0; m < G::PT; ++m) {
+    static_for<G::PT>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        using B = BandSlot<N, m>;
         g1[m] = cd{0.0, 0.0};
         g2[m] = cd{0.0, 0.0};
+        if (B::neg || !p.active || !B::in(p.t)) return;
         const int e = p.t + m * G::TPF;
-        if (!p.active || e > sh.Ks) continue;
+        const double a = kTwoPi * e * invT;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             if (c == 1 && !p.two) break;
-            const int jj = p.j1 + c;
-            const double q = kTwoPi * (jj + 1) / sh.L;
-            const double q2 = q * q, q4 = q2 * q2;
-            const double lamx = -q4 * q4 + 2.0 * q4 * q2 - q4;
-            double sig = 1.0;
-            if (scheme) {
-                const double a = kTwoPi * e / Tl;
-                sig = 1.0 / (1.0 - dtau * (lamx - a * a));
-            }
-            const double st = dtau * sig;
-            const size_t at = ((size_t)p.l * sh.Kx + jj) * K1 + e;
-            const cd gg = w.G[at];
-            const cd ph = c == 0 ? p1[m] : p2[m];
-            const cd x = cd{gg.x - st * ph.x, gg.y - st * ph.y};
+            const size_t at = ((size_t)p.l * sh.Kx + p.j1 + c) * K1 + e;
+            const cd x = band_update(w.G[at], c == 0 ? p1[m] : p2[m], band_step(f[c], a, dtau, scheme));
             w.U[at] = x;
             if (c == 0)
                 g1[m] = x;
             else
                 g2[m] = x;
         }
-    }
+    });
     if (!fuseA) return;
     xi_extend<N>(v, g1, g2, p.t, sh.Ks, p.two, exf);
     fft_inv<N, G::PT>(v, ex, twc, p.p);
