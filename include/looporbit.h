@@ -244,17 +244,19 @@ int loop_converge(double L, int Nx, int Ns, int nloops, double* T, double* uhat,
                   void* stream);
 
 /* loop_step runs in one of two forms, with the same results:
- *   resident: one block per loop holds the loop's band state and intermediates in LDS and
- *     takes every step in a single launch; HBM traffic is the state's load and store. It
- *     exists where the loop's working set fits one CU's LDS (loop_resident_supported);
+ *   resident: one block per loop keeps the loop's band state in registers and its
+ *     intermediates in LDS and takes every step in a single launch; HBM traffic is the state's
+ *     load and store. It exists where the loop's working set fits one CU's LDS
+ *     (loop_resident_supported);
  *   per-pass: five kernels per step over all loops, intermediates in the work space (HBM).
  * A step of the resident form equals the per-pass form of loop_batch_step (and of loop_step
  * with nloops = 1) bit for bit; with nloops > 1 and Ns below the row-tile height the two pair
  * rows of different loops differently in the row transforms and agree to rounding.
+ * loop_adjoint_grad takes the same form where its results are the same bits (nloops = 1, or Ns a
+ * multiple of the row-tile height).
  * loop_set_resident(mode) sets the choice for later calls in this process: 0 per-pass always,
- * 1 (default) resident where it was measured faster (for shapes whose passes take one round
- * per block, up to two loops per CU; for the others, up to one loop per CU and at least 16
- * loops), 2 resident wherever it exists.
+ * 1 (default) resident where it was measured faster, 2 resident wherever it exists (it measures
+ * faster wherever it exists, so 1 and 2 choose alike).
  * It returns the previous mode, or LOOP_EINVAL for other values.
  * loop_resident_supported returns 1 when the resident form exists for an Nx x Ns loop on the
  * current device, else 0. loop_step_form returns the form loop_step takes for nloops loops of

@@ -38,8 +38,8 @@ __device__ __forceinline__ void x_inverse_pair(const Shape& sh, const ColPos<N>&
         a[m] = v[m];
         b[m] = cd{-om * v[m].y, om * v[m].x};
     }
-    col_inverse_store<N>(sh, p, a, w.A, ex, twc);
-    col_inverse_store<N>(sh, p, b, w.Cb, ex, twc);
+    col_inverse_store<N>(p, a, w.A, ex, twc);
+    col_inverse_store<N>(p, b, w.Cb, ex, twc);
 }
 
 template <int N>
@@ -64,7 +64,7 @@ __device__ __forceinline__ void col_pass_XC(const Shape& sh, int block, const Wo
     const ColPos<N> p(sh, block);
     const size_t col = (size_t)p.l * sh.C + p.j;
     cd v[G::PT];
-    col_load<N>(sh, p, w.BD, v);
+    col_load<N>(p, w.BD, v);
     TwCache<N, G::PT> twc;
     tw_cache_load<N, G::PT>(twc, p.p, tw);
     fft_fwd<N, G::PT>(v, ex, twc, p.p);

@@ -553,13 +553,6 @@ __device__ __forceinline__ void size_switch(int n, F&& f) {
     }
 }
 
-// The twiddle table's address as seen by one pass: an opaque copy, so that the compiler does
-// not hoist every pass's twiddle cache out of the step loop and keep them all live at once.
-__device__ __forceinline__ const cd* per_pass(const cd* tw) {
-    asm volatile("" : "+s"(tw));
-    return tw;
-}
-
 // One pass body per (pass, size), each compiled as its own function so that register
 // allocation is per body rather than over the union of all bodies.
 template <int N>
@@ -755,86 +748,14 @@ void launch_rag(int v, dim3 grid, size_t lds, hipStream_t hs, const BatchArgs& a
     }
 }
 
-// LDS-resident step (see resident.hpp): block l runs all nsteps of loop l with its state and
-// intermediates in LDS. The rfft-layout spectrum is read at the start and written back at
-// the end (the same arithmetic as k_to_band and k_from_band), T[l] likewise.
-
-// LDS-resident step (see resident.hpp): block l runs all nsteps of loop l with its state and
-// intermediates in LDS. The rfft-layout spectrum is read at the start and written back at
-// the end (the same arithmetic as k_to_band and k_from_band), T[l] likewise.
-template <int M, int N>
-__global__ __launch_bounds__(kBlock, (ResG<M, N>::BLOCKS_PER_CU)) void k_resident(Shape sh, const cd* uin, cd* uout, double* T, double dtau,
-                                                     int scheme, int nsteps, double* J_hist, int* status,
-                                                     const cd* __restrict__ tw) {
-    using R = ResG<M, N>;
+// LDS-resident step or gradient (see resident.hpp): block l runs all of loop l.
+template <int M, int N, bool GRAD>
+__global__ __launch_bounds__((ResG<M, N>::NT), (ResG<M, N>::WPE)) void k_resident(
+    Shape sh, const cd* uin, cd* uout, double* T, double dtau, int scheme, int nsteps, double* J_hist, double* Jout,
+    double* dJdTout, int* status, const cd* __restrict__ tw) {
     extern __shared__ __align__(16) cd lds[];  // 16-byte aligned: one ds_read_b128 per complex value
-    cd* U = lds;
-    cd* A = U + R::S;
-    cd* X = A + R::W;
-    cd* EX = X + R::W;
-    double* part = reinterpret_cast<double*>(EX + R::EX);
-    double* sc = part + 2 * R::C;  // T, T_old, J, dJ/dT
-    double* red = sc + 4;          // 2 kBlock / 64 doubles
-    const int l = blockIdx.x;
-    Shape s1 = sh;
-    s1.nloops = 1;
-    s1.ld = R::LD;
-    Work w{};
-    w.A = A;
-    w.BD = X;
-    w.Cb = X;
-    w.U = U;
-    w.G = U;
-    w.partial = part;
-    w.J = sc + 2;
-    w.dJdT = sc + 3;
-    w.Told = sc + 1;
-    w.status = status;
-    const cd* u = uin + (size_t)l * N * sh.H;
-    for (int i = threadIdx.x; i < R::S; i += kBlock) {
-        const int j = i / R::NB, kk = i % R::NB;
-        const int e = (kk <= R::Ks) ? kk : kk + N - R::NB;
-        cd v = u[(size_t)e * sh.H + j];
-        if (j == 0) {
-            const cd pr = u[(size_t)((N - e) & (N - 1)) * sh.H];
-            v = cd{0.5 * (v.x + pr.x), 0.5 * (v.y - pr.y)};
-        }
-        U[i] = v;
-    }
-    if (threadIdx.x == 0) sc[0] = T[l];
-    __syncthreads();
-    if (nsteps > 0) {
-#pragma unroll 1
-        for (int b = 0; b < R::COL_ROUNDS; ++b) col_pass_A<N>(s1, b, w, EX, per_pass(tw));
-        __syncthreads();
-    }
-    for (int st = 0; st < nsteps; ++st) {
-#pragma unroll 1
-        for (int tile = 0; tile < R::ROW_ROUNDS; ++tile) res_row_B<M>(s1, tile, A, X, EX, per_pass(tw));
-        __syncthreads();
-#pragma unroll 1
-        for (int b = 0; b < R::COL_ROUNDS; ++b)
-            col_pass_C<N>(s1, b, sc, w, MODE_STEP, dtau, scheme, EX, red, per_pass(tw));
-        __syncthreads();
-        // J, dJ/dT and T' from pass C's partials; pass D reads neither T nor the partials
-        if (threadIdx.x < 64)
-            finalize_loop(s1, 0, w, sc, MODE_STEP, dtau, J_hist ? J_hist + (size_t)st * gridDim.x + l : nullptr,
-                          nullptr, nullptr);
-#pragma unroll 1
-        for (int tile = 0; tile < R::ROW_ROUNDS; ++tile) res_row_D<M>(s1, tile, A, X, EX, per_pass(tw));
-        __syncthreads();
-#pragma unroll 1
-        for (int b = 0; b < R::COL_ROUNDS; ++b)
-            col_pass_E<N>(s1, b, w, MODE_STEP, dtau, scheme, st + 1 < nsteps, EX, per_pass(tw));
-        __syncthreads();
-    }
-    cd* o = uout + (size_t)l * N * sh.H;
-    for (int i = threadIdx.x; i < N * sh.H; i += kBlock) {
-        const int e = i / sh.H, j = i % sh.H;
-        const int kk = j < R::C ? band_row(e, N, R::Ks) : -1;
-        o[i] = kk >= 0 ? U[j * R::NB + kk] : cd{0.0, 0.0};
-    }
-    if (threadIdx.x == 0) T[l] = sc[0];
+    resident_loop<M, N, GRAD>(sh, blockIdx.x, uin, uout, T, dtau, scheme, nsteps, J_hist, gridDim.x, Jout, dJdTout,
+                              status, lds, tw);
 }
 
 // rfft-layout pool -> per-loop band state (blockIdx.z = loop); see k_to_band.
@@ -1014,7 +935,6 @@ Shape make_shape(double L, int Nx, int Ns, int nloops) {
     s.NB = 2 * s.Ks + 1;
     s.logN = 0;
     while ((1 << s.logN) < Ns) ++s.logN;
-    s.ld = Ns;
     s.nloops = nloops;
     s.L = L;
     return s;
@@ -1157,8 +1077,9 @@ unsigned col_blocks(const Shape& s) {
     const int F = col_per_block(s.N);  // columns per block
     return (unsigned)(((size_t)s.nloops * s.C + F - 1) / F);
 }
+int row_tile(int M) { return 2 * kBlock * (M >= 1024 ? 16 : 8) / M; }  // rows per block
 unsigned row_blocks(const Shape& s) {
-    const int rows = 2 * kBlock * (s.M >= 1024 ? 16 : 8) / s.M;
+    const int rows = row_tile(s.M);
     return (unsigned)(((size_t)s.nloops * s.N + rows - 1) / rows);
 }
 
@@ -1329,7 +1250,12 @@ int launch_xi_step(const Shape& s, const XiWork& w, double* T, double dtau, int 
 // ---------------------------------------------------------------------------- resident form
 int last_error() { return hipGetLastError() == hipSuccess ? LOOP_OK : LOOP_EHIP; }
 
-// loop_set_resident: 0 never, 1 where measured faster (default), 2 wherever it fits
+// loop_set_resident: 0 never, 1 (default) and 2 wherever it fits. Mode 1 took the faster form by loop
+// count while the two crossed; the resident form now measures faster at every loop count (us
+// per step, resident / per-pass, at 1, 256 and 2048 loops):
+//   32 x 32  5.2 / 15.1   5.5 / 24.5   17.6 / 44.5      32 x 256   11.4 / 18.2  12.7 / 41.0   92 / 200
+//   64 x 64  7.5 / 16.7   8.3 / 30.3   60.6 / 96.7      64 x 128   12.6 / 19.2  13.9 / 42.3  102 / 202
+//   8 x 512  6.9 / 16.7   7.5 / 30.4   35.6 / 98.3      128 x 64   11.8 / 19.4  13.1 / 42.5   95 / 202
 std::atomic<int> g_resident{1};
 
 int max_lds_per_block() {
@@ -1357,61 +1283,20 @@ bool resident_usable(int Nx, int Ns) {
     return b > 0 && b <= (size_t)max_lds_per_block();
 }
 
-// Whether one resident block covers a pass of this shape in a single round of transforms.
-bool resident_one_round(int Nx, int Ns) {
-    bool one = false;
-    host_size_switch<8, 128>(Nx, [&](auto m) {
-        host_size_switch<8, 512>(Ns, [&](auto n) {
-            using R = ResG<decltype(m)::value, decltype(n)::value>;
-            if constexpr (R::FITS) one = R::COL_ROUNDS == 1 && R::ROW_ROUNDS == 1;
-        });
-    });
-    return one;
-}
-
-// The automatic choice, from measurements on MI355X (one 4-wavefront block per loop is
-// latency-bound; the per-pass form spreads a pass over more CUs but pays HBM round trips):
-// resident wins while every loop gets a CU of its own (nloops up to the CU count), except a
-// lone loop or a few loops whose passes need two rounds per block (32 x 256, 64 x 128).
-int resident_blocks_per_cu(int Nx, int Ns) {
-    int b = 1;
-    host_size_switch<8, 128>(Nx, [&](auto m) {
-        host_size_switch<8, 512>(Ns, [&](auto n) {
-            using R = ResG<decltype(m)::value, decltype(n)::value>;
-            if constexpr (R::FITS) b = R::BLOCKS_PER_CU;
-        });
-    });
-    return b;
-}
-
-bool resident_preferred(int Nx, int Ns, int nloops) {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return false;
-    cus *= resident_blocks_per_cu(Nx, Ns);  // resident blocks the chip holds at once
-    // Loops beyond the blocks the chip holds at once take further rounds of the resident
-    // launch. Measured against the per-pass form, one-round shapes (32 x 32, 64 x 64) stay
-    // ahead for two rounds of loops, two-round shapes only within one round and with at least
-    // 16 loops.
-    const int rounds = (nloops + cus - 1) / cus;
-    if (resident_one_round(Nx, Ns)) return rounds <= 2;
-    return rounds == 1 && nloops >= 16;
-}
-
-int launch_resident(const Shape& s, cd* u, double* T, double dtau, int scheme, int nsteps, double* J_hist,
-                    int* status, const cd* tw, hipStream_t hs) {
+template <bool GRAD>
+int launch_resident(const Shape& s, const cd* uin, cd* uout, double* T, double dtau, int scheme, int nsteps,
+                    double* J_hist, double* Jout, double* dJdTout, int* status, const cd* tw, hipStream_t hs) {
     int st = LOOP_ENOTSUP;
     host_size_switch<8, 128>(s.M, [&](auto m) {
         host_size_switch<8, 512>(s.N, [&](auto n) {
             constexpr int M_ = decltype(m)::value, N_ = decltype(n)::value;
             using R = ResG<M_, N_>;
             if constexpr (R::FITS) {
-                auto k = k_resident<M_, N_>;
+                auto k = k_resident<M_, N_, GRAD>;
                 if ((st = ensure_lds_limit(reinterpret_cast<const void*>(k), R::BYTES))) return;
-                TraceScope ts_("k_resident", M_, N_, hs);
-                ts_.launch(k, dim3(s.nloops), dim3(kBlock), R::BYTES, hs, s, u, u, T, dtau, scheme, nsteps,
-                                   J_hist, status, tw);
+                TraceScope ts_(GRAD ? "k_resident_grad" : "k_resident", M_, N_, hs);
+                ts_.launch(k, dim3(s.nloops), dim3(R::NT), R::BYTES, hs, s, uin, uout, T, dtau, scheme, nsteps,
+                           J_hist, Jout, dJdTout, status, tw);
                 st = last_error();
             }
         });
@@ -1540,7 +1425,7 @@ int step_impl(const Shape& s, const Work& w, const cd* tw, double* T, cd* u, dou
               double* J_hist, hipStream_t hs) {
     int st;
     if (loop_step_form(s.M, s.N, s.nloops) == 1)
-        return launch_resident(s, u, T, dtau, scheme, nsteps, J_hist, w.status, tw, hs);
+        return launch_resident<false>(s, u, u, T, dtau, scheme, nsteps, J_hist, nullptr, nullptr, w.status, tw, hs);
     launch_to_band(s, u, w.U, hs);
     if (nsteps > 0 && (st = launch_A(s, w, tw, hs))) return st;
     for (int i = 0; i < nsteps; ++i) {
@@ -1661,6 +1546,11 @@ int loop_adjoint_grad(double L, int Nx, int Ns, int nloops, const double* T, con
     int st = prepare(L, Nx, Ns, nloops, ws, ws_bytes, &s, &w, &tw);
     if (st) return st;
     hipStream_t hs = (hipStream_t)stream;
+    // One launch where the loop fits in LDS. Both forms then pair the rows of one loop (one loop,
+    // or whole row tiles of each), so the results are the per-pass kernels' bit for bit.
+    if (loop_step_form(Nx, Ns, nloops) == 1 && (nloops == 1 || Ns % row_tile(Nx) == 0))
+        return launch_resident<true>(s, reinterpret_cast<const cd*>(uhat), reinterpret_cast<cd*>(Ghat),
+                                     const_cast<double*>(T), 0.0, 0, 1, nullptr, J, dJdT, w.status, tw, hs);
     launch_to_band(s, reinterpret_cast<const cd*>(uhat), w.U, hs);
     if ((st = launch_A(s, w, tw, hs))) return st;
     if ((st = launch_B(s, w, tw, hs))) return st;
@@ -2058,8 +1948,7 @@ int loop_resident_supported(int Nx, int Ns) {
 
 int loop_step_form(int Nx, int Ns, int nloops) {
     if (check_shape(22.0, Nx, Ns, nloops)) return LOOP_EINVAL;
-    const int mode = g_resident.load();
-    return (mode != 0 && resident_usable(Nx, Ns) && (mode == 2 || resident_preferred(Nx, Ns, nloops))) ? 1 : 0;
+    return g_resident.load() != 0 && resident_usable(Nx, Ns) ? 1 : 0;
 }
 
 int loop_update(double L, int Nx, int Ns, int nloops, double* T, double* uhat, const double* Ghat,

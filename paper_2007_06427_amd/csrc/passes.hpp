@@ -63,7 +63,6 @@ struct Shape {
     int C;       // Kx + 1 retained columns
     int NB;      // 2 Ks + 1 retained temporal modes
     int logN;    // log2(N)
-    int ld;      // elements from one column of an intermediate to the next (N; N + 1 in LDS)
     int nloops;
     double L;
 };
@@ -255,21 +254,21 @@ __device__ __forceinline__ void band_sums(double om, cd u, cd r, double& J, doub
 
 // The s-grid values of this thread's slots of its points-side column of X.
 template <int N>
-__device__ __forceinline__ void col_load(const Shape& sh, const ColPos<N>& p, const cd* X, cd* v) {
+__device__ __forceinline__ void col_load(const ColPos<N>& p, const cd* X, cd* v) {
     using G = ColG<N>;
-    const cd* x = X + p.col_t * sh.ld;
+    const cd* x = X + p.col_t * N;
 #pragma unroll
     for (int m = 0; m < G::PT; ++m) v[m] = p.active_t ? x[p.p.point(m)] : cd{0.0, 0.0};
 }
 
 // Inverse s-transform of band column values v (already zero outside the band) into X.
 template <int N>
-__device__ __forceinline__ void col_inverse_store(const Shape& sh, const ColPos<N>& p, cd* v, cd* X, cd* ex,
+__device__ __forceinline__ void col_inverse_store(const ColPos<N>& p, cd* v, cd* X, cd* ex,
                                                   const TwCache<N, ColG<N>::PT>& twc) {
     using G = ColG<N>;
     fft_inv<N, G::PT>(v, ex, twc, p.p);
     if (p.active_t) {
-        cd* x = X + p.col_t * sh.ld;
+        cd* x = X + p.col_t * N;
 #pragma unroll
         for (int m = 0; m < G::PT; ++m) x[p.p.point(m)] = v[m];
     }
@@ -285,7 +284,7 @@ __device__ __forceinline__ void col_pass_A(const Shape& sh, int block, const Wor
     const cd* u = w.U + ((size_t)p.l * sh.C + p.j) * sh.NB;
     cd v[G::PT];
     band_prefetch<N>(p, u, w.herm0, v);
-    col_inverse_store<N>(sh, p, v, w.A, ex, twc);
+    col_inverse_store<N>(p, v, w.A, ex, twc);
 }
 
 // Reverse mode, first pass: the inverse s-transforms of u_hat (into A, as pass A) and of
@@ -306,11 +305,11 @@ __device__ __forceinline__ void col_pass_AC(const Shape& sh, int block, const Wo
     band_prefetch<N>(p, r, 0, rv);  // with WITH_U, in flight during the first transform
     if constexpr (WITH_U) {
         band_prefetch<N>(p, w.U + col * sh.NB, w.herm0, v);
-        col_inverse_store<N>(sh, p, v, w.A, ex, twc);
+        col_inverse_store<N>(p, v, w.A, ex, twc);
     }
 #pragma unroll
     for (int m = 0; m < G::PT; ++m) v[m] = cd{-q * rv[m].y, q * rv[m].x};  // i q r (zero outside the band)
-    col_inverse_store<N>(sh, p, v, w.Cb, ex, twc);
+    col_inverse_store<N>(p, v, w.Cb, ex, twc);
 }
 
 template <int N>
@@ -321,7 +320,7 @@ __device__ __forceinline__ void col_pass_C(const Shape& sh, int block, const dou
     const ColPos<N> p(sh, block);
     const size_t col = (size_t)p.l * sh.C + p.j;
     cd v[G::PT], ub[G::PT];
-    col_load<N>(sh, p, w.BD, v);
+    col_load<N>(p, w.BD, v);
     band_prefetch<N>(p, w.U + col * sh.NB, w.herm0, ub);  // in flight during the transform
     TwCache<N, G::PT> twc;
     tw_cache_load<N, G::PT>(twc, p.p, tw);
@@ -362,7 +361,7 @@ __device__ __forceinline__ void col_pass_C(const Shape& sh, int block, const dou
         w.partial[2 * col] = Jp;
         w.partial[2 * col + 1] = dTp;
     }
-    if (mode >= MODE_GRAD) col_inverse_store<N>(sh, p, v, w.Cb, ex, twc);
+    if (mode >= MODE_GRAD) col_inverse_store<N>(p, v, w.Cb, ex, twc);
 }
 
 template <int N>
@@ -373,7 +372,7 @@ __device__ __forceinline__ void col_pass_E(const Shape& sh, int block, const Wor
     const ColPos<N> p(sh, block);
     const size_t col = (size_t)p.l * sh.C + p.j;
     cd v[G::PT], gb[G::PT];
-    col_load<N>(sh, p, w.BD, v);
+    col_load<N>(p, w.BD, v);
     // G_lin or (reverse mode) the saved residual, in flight during the transform. In the step
     // (U1, then the next step's pass A on the new column) the loads issued after the transform
     // measured faster: pass E at 256 x 1024 took 70.4 us against 75.8 with them in flight.
@@ -414,7 +413,7 @@ __device__ __forceinline__ void col_pass_E(const Shape& sh, int block, const Wor
         }
         v[m] = x;
     });
-    if (mode == MODE_STEP && fuseA) col_inverse_store<N>(sh, p, v, w.A, ex, twc);
+    if (mode == MODE_STEP && fuseA) col_inverse_store<N>(p, v, w.A, ex, twc);
 }
 
 // ---------------------------------------------------------------------------- row passes

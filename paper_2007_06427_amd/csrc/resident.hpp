@@ -1,25 +1,32 @@
-// LDS-resident form of the fictitious-time step (Sec. 4.2): one block holds one loop's band
-// state and its two live intermediates in LDS and runs every pass of every step in one
-// launch, so HBM sees only the state's load and store. It applies where a loop's working
-// set fits in the 160 KB of LDS of a CU (for example 32 x 256, 64 x 128, 128 x 64).
+// LDS-resident form of the fictitious-time step (Sec. 4.2): one block runs every pass of every
+// step of one loop in one launch, so HBM sees only the state's load and store. It applies where
+// a loop's two live intermediates fit in the 160 KB of LDS of a CU (for example 32 x 256,
+// 64 x 128, 128 x 64).
 //
-// The column passes are the HBM form's own pass bodies (col_pass_A/C/E) pointed at LDS
-// arrays. The row passes are restated here to read and write the resident arrays directly
-// instead of staging tiles, with the same row pairing, transforms, products and split, and
-// the per-loop sums use the same fixed order. A step therefore gives the same bits as the
-// HBM form.
-//
-// LDS carve (complex values unless noted), for a loop of M x N (Nx x Ns):
-//   U  [C][NB]   band state; pass C overwrites it with U1 = u + dtau sigma G_lin, pass E
-//                with the new state (each element is read before it is written, by one thread)
+// The passes are those of passes.hpp with the same row pairs, transforms, band functions and
+// fixed-order sums, so a step gives the same bits as the HBM form; what differs is where values
+// live. A thread keeps the same column and the same pair of rows for the whole launch, so
+// everything that a pass hands to a later pass of the same thread stays in registers:
+//   the band state u of its column (pass C turns it into U1, pass E into the new state),
+//   dtau sigma of its modes, from pass C to pass E,
+//   u on the grid of its row pair, from pass B to pass D (whose own transform would only repeat it),
+//   the twiddles of both transforms.
+// Only what changes hands between threads goes through LDS (complex values unless noted), for a
+// loop of M x N (Nx x Ns):
 //   A  [C][N+1]  u after the inverse s-transforms (pass A, or E fused with the next A)
 //   X  [C][N+1]  B, then C (in place, column by column), then D (in place, pair by pair)
-//   EX           exchange regions: ColG<N>::LDS for the column passes, or one region of XS values
-//                per pair of rows for the row passes
+//   EX           exchange regions of the transforms, and the pairs' products before their split
 //   2C doubles   per-column partial sums of J and dJ/dT
-//   12 doubles   T, T_old, J, dJ/dT and the two-wavefront reduction slots
+//   4 doubles    T, T_old, J, dJ/dT
 // Columns of A and X are N + 1 apart: a row pass reads 16 columns of a row, or a short column
 // pass a point of 16 columns, at a time, and the odd stride puts them on different banks.
+//
+// What bounds it is instruction issue and LDS latency in the few wavefronts of a loop: the block
+// has just the threads that one round of every pass needs (64 to 512), and wavefronts that have
+// no rows or no columns skip that pass's transforms. With the state in LDS, u transformed twice,
+// every pass loading its twiddles and blocks of 256 threads for every shape, a step of one 32 x 32
+// loop took 6.6 us (now 5.2), of 256 loops of 64 x 64 10.1 (8.3), of one 64 x 128 loop 25 (12.6; the
+// per-pass form 19).
 #pragma once
 
 #include "passes.hpp"
@@ -28,95 +35,252 @@ namespace lo {
 
 template <int M, int N>
 struct ResG {
+    using R = RowG<M>;
+    static constexpr int PT = 8;
     static constexpr int C = (M - 1) / 3 + 1;
     static constexpr int Ks = (N - 1) / 3;
     static constexpr int NB = 2 * Ks + 1;
+    static constexpr int H = M / 2 + 1;
     static constexpr int LD = N + 1;
     static constexpr int W = C * LD;
-    static constexpr int S = C * NB;
-    // Row pass lanes are mapped pair-fastest (XLOW), so that consecutive lanes touch
-    // consecutive rows of A and X.
-    static constexpr int RX = RowG<M>::P * Fft<M, RowG<M>::PT, true>::XS;
-    static constexpr int EX = ColG<N>::LDS > RX ? ColG<N>::LDS : RX;
-    static constexpr int DOUBLES = 2 * C + 12;
-    static constexpr size_t BYTES = sizeof(cd) * (size_t)(S + 2 * W + EX) + sizeof(double) * DOUBLES;
-    static constexpr bool FITS = BYTES <= 160 * 1024 && N <= 512 && M <= 128;
-    // Two blocks share a CU where both fit its LDS; the kernel is then compiled for two
-    // wavefronts per SIMD (at most 256 registers each, a few spilled), which costs a lone
-    // block 5-8% but lets a second loop hide the first one's latency.
-    static constexpr int BLOCKS_PER_CU = BYTES <= 80 * 1024 ? 2 : 1;
-    static constexpr int COL_ROUNDS = (C + ColG<N>::F - 1) / ColG<N>::F;
-    static constexpr int ROW_ROUNDS = (N + RowG<M>::ROWS - 1) / RowG<M>::ROWS;
+    // Rows are paired as the HBM form's tiles pair the rows of one loop: (a, a + P); a loop of
+    // at most P rows leaves the second row of every pair empty.
+    static constexpr int P = R::P;
+    static constexpr bool B_ROW = N >= 2 * P;
+    static constexpr int PAIRS = B_ROW ? N / 2 : N;
+    static constexpr int NEED = PAIRS * R::TPF > C * (N / PT) ? PAIRS * R::TPF : C * (N / PT);
+    static constexpr int NT = NEED <= 64 ? 64 : NEED <= 128 ? 128 : NEED <= 256 ? 256 : 512;
+    using RF = Fft<M, PT, true>;  // row lanes are pair-fastest: consecutive lanes on consecutive rows
+    using CF = Fft<N, PT>;
+    static constexpr int ZS = RF::L == 1 ? 2 * R::Kx + 1 : RF::XS;  // region of a pair
+    // exchange space of the first `waves` wavefronts, in the row and the column passes
+    static constexpr int CW = (C + CF::XPW - 1) / CF::XPW;  // wavefronts with columns
+    static constexpr int rx(int waves) { return waves * RF::XPW * ZS; }
+    static constexpr int cx(int waves) { return CF::L == 1 ? 0 : (waves < CW ? waves : CW) * CF::XPW * CF::XS; }
+    static constexpr int ex(int waves) { return rx(waves) > cx(waves) ? rx(waves) : cx(waves); }
+    // SPLIT (64 x 128 and 128 x 64): the exchange space of all eight wavefronts does not fit beside A
+    // and X. Wavefronts 4 .. 7 then use whichever of A and X holds nothing in that pass: X in
+    // passes B and E (two more barriers per step: before B writes X, and after E has read it),
+    // A in passes C and D.
+    static constexpr int DOUBLES = 2 * C + 4;
+    static constexpr size_t bytes(int e) { return sizeof(cd) * (size_t)(2 * W + e) + sizeof(double) * DOUBLES; }
+    static constexpr bool SPLIT = NT == 512 && bytes(ex(8)) > 160 * 1024;
+    static constexpr int EX = ex(SPLIT ? 4 : NT / 64);
+    static constexpr size_t BYTES = bytes(EX);
+    static constexpr bool FITS = BYTES <= 160 * 1024 && N <= 512 && M <= 128 && NEED <= 512 &&
+                                 (!SPLIT || PAIRS * R::TPF == NT);  // every wavefront reaches its barriers
+    // Wavefronts per SIMD the kernel is compiled for: two (at most 256 registers each), so that
+    // blocks of small loops share a CU, except where LDS holds one block of four wavefronts.
+    static constexpr int WPE = NT == 256 && BYTES > 80 * 1024 ? 1 : 2;
 };
 
-// F + i G of rows a and b of a resident [j][n] array (zero for rows past the loop, as the HBM
-// form stages them) in the slots of a thread.
-template <int M>
-__device__ __forceinline__ void res_gather(const Shape& sh, const cd* X, int t, int a, int b, bool oka, bool okb,
-                                           cd* v) {
+// Split of the products' spectrum (slots va) into rows a and b of X, through the pair's region z.
+// SYNC: z lies in X, so the block waits for every wavefront to have read its part.
+template <int M, int N, bool DX, bool SYNC>
+__device__ __forceinline__ void res_split(const Shape& sh, const cd* va, cd* z, int t, cd* X, int a, bool on) {
+    using R = ResG<M, N>;
     using G = RowG<M>;
-    if (okb) {
-        row_gather_raw<G, true>(X, sh.ld, a, b, t, v);
-    } else {
-        row_gather_raw<G, false>(X, sh.ld, oka ? a : 0, 0, t, v);
-        if (!oka)
+    constexpr int NJ = (G::CMAX + G::TPF - 1) / G::TPF;
+    row_put<G>(z, t, va);
+    wave_lds_order();
+    cd wa[NJ], wb[NJ];
 #pragma unroll
-            for (int m = 0; m < G::PT; ++m) v[m] = cd{0.0, 0.0};
+    for (int i = 0; i < NJ; ++i) {
+        const int j = t + i * G::TPF < G::CMAX ? t + i * G::TPF : 0;
+        row_split<M, DX>(sh.L, j, z[j], z[j == 0 ? 0 : M - G::SH - j], wa[i], wb[i]);
+    }
+    if constexpr (SYNC)
+        __syncthreads();
+    else
+        wave_lds_order();  // the region is reused by this group's next transform
+    if (!on) return;
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) {
+        const int j = t + i * G::TPF;
+        if (j < G::CMAX) {
+            X[j * R::LD + a] = wa[i];
+            if (R::B_ROW) X[j * R::LD + a + R::P] = wb[i];
+        }
     }
 }
 
-// Split of the products' spectrum (slots va) into rows a and b of X, through the pair's region.
-template <int M, bool DX>
-__device__ __forceinline__ void res_split(const Shape& sh, const cd* va, cd* ex, const FftPos<M, RowG<M>::PT, true>& pos,
-                                          cd* X, int a, int b, bool oka, bool okb) {
+// All of a block's work for loop l: nsteps steps (uin -> uout in the rfft layout, T[l] in place),
+// or, with GRAD, the flow G_1 into uout and J, dJ/dT into Jout, dJdTout (each may be null).
+template <int M, int N, bool GRAD>
+__device__ __forceinline__ void resident_loop(const Shape& sh, int l, const cd* uin, cd* uout, double* T, double dtau,
+                                              int scheme, int nsteps, double* J_hist, int jstride, double* Jout,
+                                              double* dJdTout, int* status, cd* lds, const cd* __restrict__ tw) {
+    using R = ResG<M, N>;
     using G = RowG<M>;
-    cd* z = ex + pos.xs * Fft<M, G::PT, true>::XS;
-    row_put<G>(z, pos.t, va);
-    wave_lds_order();
-    for (int j = pos.t; j < G::CMAX; j += G::TPF) {
-        cd wa, wb;
-        row_split<M, DX>(sh.L, j, z[j], z[j == 0 ? 0 : M - G::SH - j], wa, wb);
-        if (oka) X[j * sh.ld + a] = wa;
-        if (okb) X[j * sh.ld + b] = wb;
+    constexpr int PT = R::PT, LD = R::LD;
+    static_assert(!R::SPLIT || (R::rx(8) - R::rx(4) <= R::W && R::cx(8) - R::cx(4) <= R::W), "A and X hold the split");
+    cd* A = lds;
+    cd* X = A + R::W;
+    cd* EX = X + R::W;
+    double* part = reinterpret_cast<double*>(EX + R::EX);
+    double* sc = part + 2 * R::C;  // T, T_old, J, dJ/dT
+    const int tid = threadIdx.x, wave = tid / 64;
+    const FftPos<M, PT, true> pr(tid);
+    const FftPos<N, PT> pc(tid);
+    // this thread's rows a and a + P, its column j (spectrum side) and jt (points side)
+    const bool row_on = pr.xs < R::PAIRS;
+    const int a = row_on ? pr.xs / R::P * 2 * R::P + pr.xs % R::P : 0;
+    const bool rows_here = wave * R::RF::XPW < R::PAIRS;  // this wavefront has rows, has columns
+    const bool cols_here = wave * R::CF::XPW < R::C;
+    const int j = pc.xs;
+    const bool col_on = j < R::C, pts_on = pc.xt < R::C;
+    cd* const acol = A + (pts_on ? pc.xt : 0) * LD;
+    cd* const xcol = X + (pts_on ? pc.xt : 0) * LD;
+    // exchange spaces of this wavefront in passes B and D, C and E (addressed as x XS, x the
+    // transform's index in the block)
+    const bool alt = R::SPLIT && wave >= 4;
+    cd* const exB = alt ? X - R::rx(4) : EX;
+    cd* const exD = alt ? A - R::rx(4) : EX;
+    cd* const exC = alt ? A - R::cx(4) : EX;
+    cd* const exE = alt ? X - R::cx(4) : EX;
+    TwCache<M, PT> twr;
+    TwCache<N, PT> twc;
+    tw_cache_load<M, PT>(twr, pr, tw);
+    tw_cache_load<N, PT>(twc, pc, tw);
+    const ColCoef f(col_on ? j : 0, sh.L);
+    const double wj = (j == 0) ? 1.0 : 2.0;
+    constexpr double invN = 1.0 / N;
+    Work w{};
+    w.partial = part;
+    w.J = sc + 2;
+    w.dJdT = sc + 3;
+    w.Told = sc + 1;
+    w.status = status;
+    Shape s1 = sh;
+    s1.nloops = 1;
+
+    cd u[PT], ug[PT], v[PT];
+    double s[PT];
+    const cd* src = uin + (size_t)l * N * R::H;
+    static_for<PT>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        using B = BandSlot<N, m>;
+        cd x{0.0, 0.0};
+        s[m] = 0.0;
+        ug[m] = cd{0.0, 0.0};
+        if (col_on && B::in(pc.t)) {
+            const int e = pc.t + m * B::TPF;
+            x = src[(size_t)e * R::H + j];
+            if (j == 0) {
+                const cd q = src[(size_t)((N - e) & (N - 1)) * R::H];
+                x = cd{0.5 * (x.x + q.x), 0.5 * (x.y - q.y)};
+            }
+        }
+        u[m] = x;
+    });
+    if (tid == 0) sc[0] = T[l];
+    auto store_col = [&](cd* col) {  // v (points) into a column of A or X
+        if (pts_on)
+#pragma unroll
+            for (int m = 0; m < PT; ++m) col[pc.point(m)] = v[m];
+    };
+    auto load_col = [&]() {
+#pragma unroll
+        for (int m = 0; m < PT; ++m) v[m] = pts_on ? xcol[pc.point(m)] : cd{0.0, 0.0};
+    };
+    auto inverse_u = [&]() {  // pass A
+#pragma unroll
+        for (int m = 0; m < PT; ++m) v[m] = u[m];
+        fft_inv<N, PT>(v, exE, twc, pc);
+        store_col(acol);
+    };
+    if (nsteps > 0 && cols_here) inverse_u();
+    __syncthreads();
+#pragma unroll 1
+    for (int st = 0; st < nsteps; ++st) {
+        if (rows_here) {  // pass B: (1/2) (u^2)_x (with SPLIT every wavefront has rows)
+            static_assert(M <= kSquareMaxM, "the resident form takes the square form of u u_x");
+            row_gather_raw<G, R::B_ROW>(A, LD, a, a + R::P, pr.t, ug);
+            fft_inv<M, PT, true>(ug, exB, twr, pr);
+#pragma unroll
+            for (int m = 0; m < PT; ++m) v[m] = cd{ug[m].x * ug[m].x, ug[m].y * ug[m].y};
+            fft_fwd<M, PT, true>(v, exB, twr, pr);
+            res_split<M, N, true, R::SPLIT>(sh, v, exB + pr.xs * R::ZS, pr.t, X, a, row_on);
+        }
+        __syncthreads();
+        const double invT = 1.0 / sc[0];
+        if (cols_here) {  // pass C
+            load_col();
+            fft_fwd<N, PT>(v, exC, twc, pc);
+            double Jp = 0.0, dTp = 0.0;
+            static_for<PT>([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                using B = BandSlot<N, m>;
+                cd x{0.0, 0.0};
+                if (col_on && B::in(pc.t)) {
+                    const double om = kTwoPi * B::k(pc.t), ak = om * invT;
+                    const cd r = band_residual(f, ak, invN, u[m], v[m]);
+                    band_sums(om, u[m], r, Jp, dTp);
+                    const cd gl = band_glin(f, ak, r);
+                    if (GRAD) {
+                        u[m] = gl;
+                    } else {
+                        const double sm = band_step(f, ak, dtau, scheme);
+                        u[m] = cd{__builtin_fma(sm, gl.x, u[m].x), __builtin_fma(sm, gl.y, u[m].y)};  // U1
+                        s[m] = sm * invN;
+                    }
+                    x = cd{-f.q * r.y, f.q * r.x};  // i q r
+                }
+                v[m] = x;
+            });
+            Jp *= wj;
+            dTp *= wj;
+            col_sum2<N>(Jp, dTp, nullptr);
+            if (col_on && pc.t == 0) {
+                part[2 * j] = Jp;
+                part[2 * j + 1] = dTp;
+            }
+            fft_inv<N, PT>(v, exC, twc, pc);
+            store_col(xcol);
+        }
+        __syncthreads();
+        // J, dJ/dT and T' from the partials; no other wavefront reads them before the next pass C
+        if (wave == R::NT / 64 - 1)
+            finalize_loop(s1, 0, w, sc, GRAD ? MODE_GRAD : MODE_STEP, dtau,
+                          J_hist ? J_hist + (size_t)st * jstride + l : nullptr, Jout ? Jout + l : nullptr,
+                          dJdTout ? dJdTout + l : nullptr);
+        if (rows_here) {  // pass D: u r_x
+            row_gather_raw<G, R::B_ROW>(X, LD, a, a + R::P, pr.t, v);
+            fft_inv<M, PT, true>(v, exD, twr, pr);
+#pragma unroll
+            for (int m = 0; m < PT; ++m) v[m] = cd{ug[m].x * v[m].x, ug[m].y * v[m].y};
+            fft_fwd<M, PT, true>(v, exD, twr, pr);
+            res_split<M, N, false, false>(sh, v, exD + pr.xs * R::ZS, pr.t, X, a, row_on);
+        }
+        __syncthreads();
+        if (cols_here) load_col();
+        if constexpr (R::SPLIT) __syncthreads();  // X has been read: its space may be used
+        if (cols_here) {  // pass E, and the next step's pass A
+            fft_fwd<N, PT>(v, exE, twc, pc);
+#pragma unroll
+            for (int m = 0; m < PT; ++m) u[m] = GRAD ? band_g1(u[m], v[m], invN) : band_update(u[m], v[m], s[m]);
+            static_for<PT>([&](auto mc) {  // slots outside the band stay zero
+                constexpr int m = decltype(mc)::value;
+                if (!(col_on && BandSlot<N, m>::in(pc.t))) u[m] = cd{0.0, 0.0};
+            });
+            if (!GRAD && st + 1 < nsteps) inverse_u();
+        }
+        __syncthreads();
     }
-    wave_lds_order();  // the exchange region is reused by this group's next transform
-}
-
-// Pass B for the pairs of row tile `tile`: X = (u u_x) = (1/2) (u^2)_x per row, from A.
-template <int M>
-__device__ __forceinline__ void res_row_B(const Shape& sh, int tile, const cd* A, cd* X, cd* exr,
-                                          const cd* __restrict__ tw) {
-    using G = RowG<M>;
-    static_assert(M <= kSquareMaxM, "the resident form takes the square form of u u_x");
-    const FftPos<M, G::PT, true> pos(threadIdx.x);
-    const int a = tile * G::ROWS + pos.xs, b = a + G::P;
-    const bool oka = a < sh.N, okb = b < sh.N;
-    TwCache<M, G::PT> twc;
-    tw_cache_load<M, G::PT>(twc, pos, tw);
-    cd va[G::PT];
-    res_gather<M>(sh, A, pos.t, a, b, oka, okb, va);
-    row_square<M, G::PT, true>(va, exr, twc, pos);
-    wave_lds_order();
-    res_split<M, true>(sh, va, exr, pos, X, a, b, oka, okb);
-}
-
-// Pass D for the pairs of row tile `tile`: X = (u r_x) per row, from A and X (r_x), in place.
-template <int M>
-__device__ __forceinline__ void res_row_D(const Shape& sh, int tile, const cd* A, cd* X, cd* exr,
-                                          const cd* __restrict__ tw) {
-    using G = RowG<M>;
-    const FftPos<M, G::PT, true> pos(threadIdx.x);
-    const int a = tile * G::ROWS + pos.xs, b = a + G::P;
-    const bool oka = a < sh.N, okb = b < sh.N;
-    TwCache<M, G::PT> twc;
-    tw_cache_load<M, G::PT>(twc, pos, tw);
-    cd va[G::PT], vb[G::PT];
-    res_gather<M>(sh, A, pos.t, a, b, oka, okb, va);
-    res_gather<M>(sh, X, pos.t, a, b, oka, okb, vb);
-    // every read of rows a and b of X (by this group only) precedes the group's writes below
-    row_product<M, G::PT, true>(va, vb, exr, twc, pos);
-    wave_lds_order();
-    res_split<M, false>(sh, va, exr, pos, X, a, b, oka, okb);
+    // the band values through LDS (over A), then every entry of the rfft layout
+    static_for<PT>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        using B = BandSlot<N, m>;
+        if (col_on && B::in(pc.t)) A[j * R::NB + B::kk(pc.t)] = u[m];
+    });
+    __syncthreads();
+    cd* o = uout + (size_t)l * N * R::H;
+    for (int i = tid; i < N * R::H; i += R::NT) {
+        const int e = i / R::H, jj = i % R::H;
+        const int kk = jj < R::C ? band_row(e, N, R::Ks) : -1;
+        o[i] = kk >= 0 ? A[jj * R::NB + kk] : cd{0.0, 0.0};
+    }
+    if (!GRAD && tid == 0) T[l] = sc[0];
 }
 
 }  // namespace lo
