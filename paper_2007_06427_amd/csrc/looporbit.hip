@@ -418,6 +418,7 @@ struct WsHeader {
     int pad;
     uint64_t magic;
 };
+static_assert(sizeof(WsHeader) <= 256, "the header takes one unit of the work space");
 
 __global__ void k_ws_init(WsHeader* h) {
     h->status = 0;
@@ -427,6 +428,50 @@ __global__ void k_ws_init(WsHeader* h) {
 __global__ void k_ws_clear_status(WsHeader* h) { h->status = 0; }
 
 __global__ void k_copy_status(const WsHeader* h, int* status) { *status = h->status; }
+
+Shape make_shape(double L, int Nx, int Ns, int nloops) {
+    Shape s;
+    s.M = Nx;
+    s.N = Ns;
+    s.Kx = (Nx - 1) / 3;
+    s.Ks = (Ns - 1) / 3;
+    s.H = Nx / 2 + 1;
+    s.C = s.Kx + 1;
+    s.NB = 2 * s.Ks + 1;
+    s.logN = ilog2(Ns);
+    s.nloops = nloops;
+    s.L = L;
+    return s;
+}
+
+// Arrays of the work space start at multiples of 256 bytes; the header and one loop's scalars
+// take one such unit each.
+struct WsRegion {
+    char bytes[256];
+};
+size_t round_up(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Work space layout: header | A | BD | Cb | U | G | partial | J | dJdT | Told
+size_t layout(const Shape& s, char* base, Work* w) {
+    size_t off = round_up(sizeof(WsHeader));
+    const size_t inter = (size_t)s.nloops * s.N * s.C * sizeof(cd);
+    const size_t band = (size_t)s.nloops * s.NB * s.C * sizeof(cd);
+    const size_t part = (size_t)s.nloops * s.C * 2 * sizeof(double);
+    const size_t scal = (size_t)s.nloops * sizeof(double);
+    Work ww{};
+    ww.status = reinterpret_cast<int*>(base);
+    ww.A = reinterpret_cast<cd*>(base + off); off = round_up(off + inter);
+    ww.BD = reinterpret_cast<cd*>(base + off); off = round_up(off + inter);
+    ww.Cb = reinterpret_cast<cd*>(base + off); off = round_up(off + inter);
+    ww.U = reinterpret_cast<cd*>(base + off); off = round_up(off + band);
+    ww.G = reinterpret_cast<cd*>(base + off); off = round_up(off + band);
+    ww.partial = reinterpret_cast<double*>(base + off); off = round_up(off + part);
+    ww.J = reinterpret_cast<double*>(base + off); off = round_up(off + scal);
+    ww.dJdT = reinterpret_cast<double*>(base + off); off = round_up(off + scal);
+    ww.Told = reinterpret_cast<double*>(base + off); off = round_up(off + scal);
+    if (w) *w = ww;
+    return off;
+}
 
 // ============================================================================ batched scheduler
 // A batch of loops of uneven shape advances in one persistent launch. Each loop belongs to one
@@ -461,6 +506,7 @@ struct WsOff {  // byte offsets of one loop's regions inside the work space
 struct BatchLoop {
     Shape sh;    // this loop alone (nloops = 1)
     WsOff off;
+    size_t base;  // byte offset of the loop's region (layout() of its shape)
     size_t uoff;  // offset of the loop's spectrum in the rfft-layout pool (complex values)
     int nt[5];    // tiles of passes A, B, C, D, E
     int ipl;      // items per step: B + C + D + E tiles
@@ -698,16 +744,68 @@ constexpr int row_pt() {
     return PT ? PT : RowG<M>::PT;
 }
 
+// Everything a block of k_rag needs to know of its tile, in one 64-byte scalar load: a block
+// lives for about ten microseconds, and reading an item code first and the loop's record after
+// it put a second memory latency in front of every block's own loads (10 steps of 256 ragged
+// loops on three streams: 652 us, with this record 636).
+struct __align__(64) TileDesc {
+    uint64_t base;  // the loop's region in the work space (layout() of its shape), in bytes
+    double L;
+    int l, tile;
+    int M, N, logN, C, NB;
+    uint32_t inter, band, part;  // bytes of an intermediate, a band array and the partial sums there
+};
+
+// The records of a plan's tile lists from their item codes (l, pass, tile), once per plan.
+__global__ void k_fill_tiles(const BatchLoop* __restrict__ loops, const uint32_t* __restrict__ codes, int n,
+                             TileDesc* __restrict__ out) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int l = (int)(codes[i] >> 16);
+    const BatchLoop& b = loops[l];
+    out[i] = TileDesc{b.base, b.sh.L, l, (int)(codes[i] & 0x1fff), b.sh.M, b.sh.N, b.sh.logN, b.sh.C, b.sh.NB,
+                      (uint32_t)(b.off.BD - b.off.A), (uint32_t)(b.off.G - b.off.U),
+                      (uint32_t)(b.off.J - b.off.partial)};
+}
+
+struct RagArgs {
+    const TileDesc* tiles;
+    char* ws;
+    int* status;
+    double* T;
+    double* J_hist;  // [nsteps][nloops] or null
+    const cd* tw;
+    double dtau;
+    int scheme, nsteps, nloops, step;
+};
+
 template <int PASS, int V>
-__global__ __launch_bounds__(kBlock) void k_rag(BatchArgs a, const uint32_t* __restrict__ codes, int s) {
+__global__ __launch_bounds__(kBlock) void k_rag(RagArgs a) {
     constexpr RagVariant var = rag_variant(PASS, V);
     extern __shared__ __align__(16) cd lds[];  // 16-byte aligned: one ds_read_b128 per complex value
     __shared__ double red[2 * kBlock / 64];
-    const uint32_t code = codes[blockIdx.x];
-    const int l = (int)(code >> 16), tile = (int)(code & 0x1fff);
-    const BatchLoop b = a.loops[l];
-    const Work w = batch_work(b, a.ws, a.status);
-    const Shape& sh = b.sh;
+    const TileDesc d = a.tiles[blockIdx.x];
+    const int l = d.l, tile = d.tile, s = a.step;
+    Shape sh{};
+    sh.M = d.M;
+    sh.N = d.N;
+    sh.logN = d.logN;
+    sh.C = d.C;
+    sh.NB = d.NB;
+    sh.nloops = 1;
+    sh.L = d.L;
+    char* p = a.ws + d.base + sizeof(WsRegion);
+    Work w{};
+    w.A = reinterpret_cast<cd*>(p);
+    w.BD = reinterpret_cast<cd*>(p += d.inter);
+    w.Cb = reinterpret_cast<cd*>(p += d.inter);
+    w.U = reinterpret_cast<cd*>(p += d.inter);
+    w.G = reinterpret_cast<cd*>(p += d.band);
+    w.partial = reinterpret_cast<double*>(p += d.band);
+    w.J = reinterpret_cast<double*>(p += d.part);
+    w.dJdT = reinterpret_cast<double*>(p += sizeof(WsRegion));
+    w.Told = reinterpret_cast<double*>(p += sizeof(WsRegion));
+    w.status = a.status;
     if constexpr (PASS == PASS_A) {
         size_switch<var.lo, var.hi>(sh.N, [&](auto c) { col_pass_A<decltype(c)::value>(sh, tile, w, lds, a.tw); });
     } else if constexpr (PASS == PASS_B) {
@@ -735,15 +833,14 @@ __global__ __launch_bounds__(kBlock) void k_rag(BatchArgs a, const uint32_t* __r
 
 // ts: the launch's TraceScope
 template <int PASS, class Scope>
-void launch_rag(int v, dim3 grid, size_t lds, hipStream_t hs, const BatchArgs& a, const uint32_t* c, int step,
-                Scope& ts) {
+void launch_rag(int v, dim3 grid, size_t lds, hipStream_t hs, const RagArgs& a, Scope& ts) {
     const uint32_t sh = (uint32_t)lds;
     switch (v) {
-        case 0: ts.launch(k_rag<PASS, 0>, grid, dim3(kBlock), sh, hs, a, c, step); break;
-        case 1: ts.launch(k_rag<PASS, 1>, grid, dim3(kBlock), sh, hs, a, c, step); break;
-        case 2: ts.launch(k_rag<PASS, 2>, grid, dim3(kBlock), sh, hs, a, c, step); break;
+        case 0: ts.launch(k_rag<PASS, 0>, grid, dim3(kBlock), sh, hs, a); break;
+        case 1: ts.launch(k_rag<PASS, 1>, grid, dim3(kBlock), sh, hs, a); break;
+        case 2: ts.launch(k_rag<PASS, 2>, grid, dim3(kBlock), sh, hs, a); break;
         default:
-            if constexpr (is_row_pass(PASS)) ts.launch(k_rag<PASS, 3>, grid, dim3(kBlock), sh, hs, a, c, step);
+            if constexpr (is_row_pass(PASS)) ts.launch(k_rag<PASS, 3>, grid, dim3(kBlock), sh, hs, a);
             break;
     }
 }
@@ -923,46 +1020,6 @@ int check_shape(double L, int Nx, int Ns, int nloops) {
 }
 
 bool aligned(const void* p, size_t a) { return p != nullptr && (reinterpret_cast<uintptr_t>(p) % a) == 0; }
-
-Shape make_shape(double L, int Nx, int Ns, int nloops) {
-    Shape s;
-    s.M = Nx;
-    s.N = Ns;
-    s.Kx = (Nx - 1) / 3;
-    s.Ks = (Ns - 1) / 3;
-    s.H = Nx / 2 + 1;
-    s.C = s.Kx + 1;
-    s.NB = 2 * s.Ks + 1;
-    s.logN = 0;
-    while ((1 << s.logN) < Ns) ++s.logN;
-    s.nloops = nloops;
-    s.L = L;
-    return s;
-}
-
-size_t round_up(size_t x) { return (x + 255) & ~(size_t)255; }
-
-// Work space layout: header | A | BD | Cb | U | G | partial | J | dJdT | Told
-size_t layout(const Shape& s, char* base, Work* w) {
-    size_t off = round_up(sizeof(WsHeader));
-    const size_t inter = (size_t)s.nloops * s.N * s.C * sizeof(cd);
-    const size_t band = (size_t)s.nloops * s.NB * s.C * sizeof(cd);
-    const size_t part = (size_t)s.nloops * s.C * 2 * sizeof(double);
-    const size_t scal = (size_t)s.nloops * sizeof(double);
-    Work ww{};
-    ww.status = reinterpret_cast<int*>(base);
-    ww.A = reinterpret_cast<cd*>(base + off); off = round_up(off + inter);
-    ww.BD = reinterpret_cast<cd*>(base + off); off = round_up(off + inter);
-    ww.Cb = reinterpret_cast<cd*>(base + off); off = round_up(off + inter);
-    ww.U = reinterpret_cast<cd*>(base + off); off = round_up(off + band);
-    ww.G = reinterpret_cast<cd*>(base + off); off = round_up(off + band);
-    ww.partial = reinterpret_cast<double*>(base + off); off = round_up(off + part);
-    ww.J = reinterpret_cast<double*>(base + off); off = round_up(off + scal);
-    ww.dJdT = reinterpret_cast<double*>(base + off); off = round_up(off + scal);
-    ww.Told = reinterpret_cast<double*>(base + off); off = round_up(off + scal);
-    if (w) *w = ww;
-    return off;
-}
 
 int prepare(double L, int Nx, int Ns, int nloops, void* ws, size_t ws_bytes, Shape* sh, Work* w,
             const cd** tw) {
@@ -1318,8 +1375,8 @@ struct BatchPlan {
     int max_nb = 1, max_c = 1, max_n = 1, max_h = 1;
     size_t lds_bytes = 0;
     int grid = 1;
-    uint32_t* d_pass_codes = nullptr;  // all loops' tiles, pass by pass (A, B, C, D, E)
-    int pass_off[6] = {0, 0, 0, 0, 0, 0};
+    TileDesc* d_tiles = nullptr;  // tile lists: all loops' column tiles and row tiles, then the groups'
+    int tile_off[3] = {0, 0, 0};       // column tiles from [0], row tiles from [1]
     int schedule = 0;                  // LOOP_BATCH_PER_PASS, LOOP_BATCH_PERSISTENT or LOOP_BATCH_STREAMS
     double wait_limit = kDefaultWaitLimit;  // seconds: bound of one dependency wait (persistent)
     int variant[5] = {0, 0, 0, 0, 0};  // k_rag variant of each pass
@@ -1328,8 +1385,7 @@ struct BatchPlan {
     // multi-stream schedule: for K = 2, 3, 4 groups of about equal work, the tiles of each
     // group and pass; group g > 0 runs on the plan's stream sx[g - 1] (default priority)
     int nstreams = 2;
-    uint32_t* d_group_codes = nullptr;
-    int group_off[3][4][6] = {};  // [K - 2][group][pass .. pass + 1]
+    int group_off[3][4][3] = {};  // [K - 2][group][column tiles, row tiles, end]
     hipStream_t sx[3] = {nullptr, nullptr, nullptr};
     hipEvent_t ev_fork = nullptr, ev_lag[3] = {nullptr, nullptr, nullptr}, ev_join[3] = {nullptr, nullptr, nullptr};
 };
@@ -1390,8 +1446,7 @@ void free_plan(BatchPlan* p) {
     if (p->device >= 0) hipSetDevice(p->device);
     if (p->d_loops) hipFree(p->d_loops);
     if (p->d_items) hipFree(p->d_items);
-    if (p->d_pass_codes) hipFree(p->d_pass_codes);
-    if (p->d_group_codes) hipFree(p->d_group_codes);
+    if (p->d_tiles) hipFree(p->d_tiles);
     if (p->ev_fork) hipEventDestroy(p->ev_fork);
     for (int k = 0; k < 3; ++k) {
         if (p->ev_lag[k]) hipEventDestroy(p->ev_lag[k]);
@@ -1998,6 +2053,7 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
         Work w{};
         const size_t sz = layout(b.sh, reinterpret_cast<char*>(off), &w);
         const size_t base = off;
+        b.base = base;
         auto rel = [&](const void* q) { return (size_t)reinterpret_cast<uintptr_t>(q); };
         b.off = WsOff{rel(w.A), rel(w.BD), rel(w.Cb), rel(w.U), rel(w.G), rel(w.partial), rel(w.J), rel(w.dJdT),
                       rel(w.Told)};
@@ -2092,17 +2148,19 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
                     for (int t = 0; t < p->loops[l].nt[pass]; ++t) items.push_back(item_code(l, pass, t));
         p->ips[x] = (int)items.size() - p->xoff[x] - p->nA[x];
     }
-    // per-pass code lists for the launch-per-pass schedule
-    std::vector<uint32_t> pcodes;
-    for (int pass = PASS_A; pass <= PASS_E; ++pass) {
-        p->pass_off[pass] = (int)pcodes.size();
-        for (int l : order)
-            for (int t = 0; t < p->loops[l].nt[pass]; ++t) pcodes.push_back(item_code(l, pass, t));
+    // tile lists of the launch-per-pass schedules: passes A, C and E share the column tiles, B
+    // and D the row tiles
+    std::vector<uint32_t> codes;
+    auto add_tiles = [&](int l, bool row) {
+        const int pass = row ? PASS_B : PASS_A;
+        for (int t = 0; t < p->loops[l].nt[pass]; ++t) codes.push_back(item_code(l, pass, t));
+    };
+    for (int row = 0; row < 2; ++row) {
+        for (int l : order) add_tiles(l, row);
+        p->tile_off[row + 1] = (int)codes.size();
     }
-    p->pass_off[5] = (int)pcodes.size();
     // multi-stream schedule: K groups of about equal bytes per step (larger loops placed first,
     // each on the lightest group so far), for K = 2, 3, 4
-    std::vector<uint32_t> gcodes;
     for (int K = 2; K <= 4; ++K) {
         std::vector<int> group(nloops, 0);
         size_t load[4] = {0, 0, 0, 0};
@@ -2114,14 +2172,14 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
             group[l] = g;
             load[g] += 9 * (size_t)sh.C * sh.N + 4 * (size_t)sh.C * sh.NB;
         }
-        for (int g = 0; g < K; ++g)
-            for (int pass = PASS_A; pass <= PASS_E; ++pass) {
-                p->group_off[K - 2][g][pass] = (int)gcodes.size();
+        for (int g = 0; g < K; ++g) {
+            p->group_off[K - 2][g][0] = (int)codes.size();
+            for (int row = 0; row < 2; ++row) {
                 for (int l : order)
-                    if (group[l] == g)
-                        for (int t = 0; t < p->loops[l].nt[pass]; ++t) gcodes.push_back(item_code(l, pass, t));
-                p->group_off[K - 2][g][pass + 1] = (int)gcodes.size();
+                    if (group[l] == g) add_tiles(l, row);
+                p->group_off[K - 2][g][row + 1] = (int)codes.size();
             }
+        }
     }
     // one resident wave of blocks
     int per_cu = 1, cus = 1;
@@ -2135,15 +2193,23 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
         hipMalloc((void**)&p->d_items, sizeof(uint32_t) * items.size()) != hipSuccess ||
         hipMemcpy(p->d_loops, p->loops.data(), sizeof(BatchLoop) * nloops, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(p->d_items, items.data(), sizeof(uint32_t) * items.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMalloc((void**)&p->d_pass_codes, sizeof(uint32_t) * pcodes.size()) != hipSuccess ||
-        hipMemcpy(p->d_pass_codes, pcodes.data(), sizeof(uint32_t) * pcodes.size(), hipMemcpyHostToDevice) !=
-            hipSuccess ||
-        hipMalloc((void**)&p->d_group_codes, sizeof(uint32_t) * gcodes.size()) != hipSuccess ||
-        hipMemcpy(p->d_group_codes, gcodes.data(), sizeof(uint32_t) * gcodes.size(), hipMemcpyHostToDevice) !=
-            hipSuccess ||
+        hipMalloc((void**)&p->d_tiles, sizeof(TileDesc) * codes.size()) != hipSuccess ||
         hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming) != hipSuccess) {
         free_plan(p);
         return LOOP_EHIP;
+    }
+    {
+        uint32_t* d_codes = nullptr;
+        const int n = (int)codes.size();
+        bool ok = hipMalloc((void**)&d_codes, sizeof(uint32_t) * n) == hipSuccess &&
+                  hipMemcpy(d_codes, codes.data(), sizeof(uint32_t) * n, hipMemcpyHostToDevice) == hipSuccess;
+        if (ok) hipLaunchKernelGGL(k_fill_tiles, dim3((n + 255) / 256), dim3(256), 0, 0, p->d_loops, d_codes, n, p->d_tiles);
+        ok = ok && hipGetLastError() == hipSuccess && hipStreamSynchronize(0) == hipSuccess;
+        if (d_codes) hipFree(d_codes);
+        if (!ok) {
+            free_plan(p);
+            return LOOP_EHIP;
+        }
     }
     for (int k = 0; k < 3; ++k)
         if (hipStreamCreateWithFlags(&p->sx[k], hipStreamNonBlocking) != hipSuccess ||
@@ -2238,30 +2304,31 @@ const char* rag_name(int pass, int v) {
     return names[pass][v];
 }
 
-void launch_pass_codes(const BatchPlan* p, int pass, int step, const BatchArgs& a, hipStream_t hs,
-                       const uint32_t* c, int n) {
+void launch_pass_tiles(const BatchPlan* p, int pass, int step, const BatchArgs& a, hipStream_t hs,
+                       const TileDesc* c, int n) {
     if (n == 0) return;
     const dim3 grid(n);
     const int v = p->variant[pass];
     const size_t lds = p->pass_lds[pass][v];
+    const RagArgs r{c, a.ws, a.status, a.T, a.J_hist, a.tw, a.dtau, a.scheme, a.nsteps, a.nloops, step};
     TraceScope ts_(rag_name(pass, v), 0, hs);
     switch (pass) {
-        case PASS_A: launch_rag<PASS_A>(v, grid, lds, hs, a, c, step, ts_); break;
-        case PASS_B: launch_rag<PASS_B>(v, grid, lds, hs, a, c, step, ts_); break;
-        case PASS_C: launch_rag<PASS_C>(v, grid, lds, hs, a, c, step, ts_); break;
-        case PASS_D: launch_rag<PASS_D>(v, grid, lds, hs, a, c, step, ts_); break;
-        default: launch_rag<PASS_E>(v, grid, lds, hs, a, c, step, ts_); break;
+        case PASS_A: launch_rag<PASS_A>(v, grid, lds, hs, r, ts_); break;
+        case PASS_B: launch_rag<PASS_B>(v, grid, lds, hs, r, ts_); break;
+        case PASS_C: launch_rag<PASS_C>(v, grid, lds, hs, r, ts_); break;
+        case PASS_D: launch_rag<PASS_D>(v, grid, lds, hs, r, ts_); break;
+        default: launch_rag<PASS_E>(v, grid, lds, hs, r, ts_); break;
     }
 }
 
 void launch_pass(const BatchPlan* p, int pass, int step, const BatchArgs& a, hipStream_t hs) {
-    launch_pass_codes(p, pass, step, a, hs, p->d_pass_codes + p->pass_off[pass],
-                      p->pass_off[pass + 1] - p->pass_off[pass]);
+    const int* off = p->tile_off + is_row_pass(pass);
+    launch_pass_tiles(p, pass, step, a, hs, p->d_tiles + off[0], off[1] - off[0]);
 }
 
 void launch_group_pass(const BatchPlan* p, int g, int pass, int step, const BatchArgs& a, hipStream_t hs) {
-    const int* off = p->group_off[p->nstreams - 2][g];
-    launch_pass_codes(p, pass, step, a, hs, p->d_group_codes + off[pass], off[pass + 1] - off[pass]);
+    const int* off = p->group_off[p->nstreams - 2][g] + is_row_pass(pass);
+    launch_pass_tiles(p, pass, step, a, hs, p->d_tiles + off[0], off[1] - off[0]);
 }
 
 // Multi-stream schedule: group 0 on the caller's stream, group g > 0 on the plan's stream

@@ -170,8 +170,8 @@ struct ColPos {
         const int c = block * G::F + p.xs, n = sh.nloops * sh.C;
         t = p.t;
         active = c < n;
-        l = active ? c / sh.C : 0;
-        j = active ? c % sh.C : 0;
+        l = active && sh.nloops > 1 ? c / sh.C : 0;
+        j = active ? c - l * sh.C : 0;
         const int ct = block * G::F + p.xt;
         active_t = ct < n;
         col_t = active_t ? ct : 0;
