@@ -848,18 +848,54 @@ void launch_rag(int v, dim3 grid, size_t lds, hipStream_t hs, const RagArgs& a, 
 // LDS-resident step or gradient (see resident.hpp): block l runs all of loop l.
 template <int M, int N, bool GRAD>
 __global__ __launch_bounds__((ResG<M, N>::NT), (ResG<M, N>::WPE)) void k_resident(
-    Shape sh, const cd* uin, cd* uout, double* T, double dtau, int scheme, int nsteps, double* J_hist, double* Jout,
+    double L, const cd* uin, cd* uout, double* T, double dtau, int scheme, int nsteps, double* J_hist, double* Jout,
     double* dJdTout, int* status, const cd* __restrict__ tw) {
     extern __shared__ __align__(16) cd lds[];  // 16-byte aligned: one ds_read_b128 per complex value
-    resident_loop<M, N, GRAD>(sh, blockIdx.x, uin, uout, T, dtau, scheme, nsteps, J_hist, gridDim.x, Jout, dJdTout,
-                              status, lds, tw);
+    const int l = blockIdx.x;
+    const size_t at = (size_t)l * N * ResG<M, N>::H;
+    resident_loop<M, N, GRAD>(L, uin + at, uout + at, T + l, dtau, scheme, nsteps, J_hist ? J_hist + l : nullptr,
+                              gridDim.x, Jout ? Jout + l : nullptr, dJdTout ? dJdTout + l : nullptr, status, lds, tw);
 }
 
-// rfft-layout pool -> per-loop band state (blockIdx.z = loop); see k_to_band.
-__global__ __launch_bounds__(256) void k_to_band_batch(const BatchLoop* loops, const cd* __restrict__ pool,
-                                                       char* ws) {
+// The loops of a batch that take the resident form, one kernel for the shapes of each block size.
+struct ResDesc {
+    uint64_t uoff;  // offset of the loop's spectrum in the pool (complex values)
+    double L;
+    int l, M, N, pad;
+};
+struct ResArgs {
+    const ResDesc* loops;
+    cd* pool;
+    double* T;
+    double* J_hist;  // [nsteps][nloops] or null
+    int* status;
+    const cd* tw;
+    double dtau;
+    int scheme, nsteps, nloops;
+};
+template <int NT>
+__global__ __launch_bounds__(NT, 2) void k_resident_batch(ResArgs a) {
+    extern __shared__ __align__(16) cd lds[];
+    const ResDesc d = a.loops[blockIdx.x];
+    size_switch<8, 128>(d.M, [&](auto m) {
+        size_switch<8, 512>(d.N, [&](auto n) {
+            constexpr int M_ = decltype(m)::value, N_ = decltype(n)::value;
+            using R = ResG<M_, N_>;
+            if constexpr (R::FITS && R::NT == NT) {
+                cd* u = a.pool + d.uoff;
+                resident_loop<M_, N_, false>(d.L, u, u, a.T + d.l, a.dtau, a.scheme, a.nsteps,
+                                             a.J_hist ? a.J_hist + d.l : nullptr, a.nloops, nullptr, nullptr, a.status,
+                                             lds, a.tw);
+            }
+        });
+    });
+}
+
+// rfft-layout pool -> per-loop band state (blockIdx.z = loop, or its place in ids); see k_to_band.
+__global__ __launch_bounds__(256) void k_to_band_batch(const BatchLoop* loops, const int* ids,
+                                                       const cd* __restrict__ pool, char* ws) {
     __shared__ cd tile[32][33];
-    const BatchLoop& b = loops[blockIdx.z];
+    const BatchLoop& b = loops[ids ? ids[blockIdx.z] : blockIdx.z];
     const Shape& sh = b.sh;
     const int kk0 = blockIdx.x * 32, j0 = blockIdx.y * 32;
     if (kk0 >= sh.NB || j0 >= sh.C) return;
@@ -886,10 +922,10 @@ __global__ __launch_bounds__(256) void k_to_band_batch(const BatchLoop* loops, c
     }
 }
 
-__global__ __launch_bounds__(256) void k_from_band_batch(const BatchLoop* loops, const char* ws,
+__global__ __launch_bounds__(256) void k_from_band_batch(const BatchLoop* loops, const int* ids, const char* ws,
                                                          cd* __restrict__ pool) {
     __shared__ cd tile[32][33];
-    const BatchLoop& b = loops[blockIdx.z];
+    const BatchLoop& b = loops[ids ? ids[blockIdx.z] : blockIdx.z];
     const Shape& sh = b.sh;
     const int e0 = blockIdx.x * 32, j0 = blockIdx.y * 32;
     if (e0 >= sh.N || j0 >= sh.H) return;
@@ -1335,6 +1371,15 @@ size_t resident_bytes(int Nx, int Ns) {
     return b;
 }
 
+// Threads of its block.
+int resident_threads(int Nx, int Ns) {
+    int t = 0;
+    host_size_switch<8, 128>(Nx, [&](auto m) {
+        host_size_switch<8, 512>(Ns, [&](auto n) { t = ResG<decltype(m)::value, decltype(n)::value>::NT; });
+    });
+    return t;
+}
+
 bool resident_usable(int Nx, int Ns) {
     const size_t b = resident_bytes(Nx, Ns);
     return b > 0 && b <= (size_t)max_lds_per_block();
@@ -1352,7 +1397,7 @@ int launch_resident(const Shape& s, const cd* uin, cd* uout, double* T, double d
                 auto k = k_resident<M_, N_, GRAD>;
                 if ((st = ensure_lds_limit(reinterpret_cast<const void*>(k), R::BYTES))) return;
                 TraceScope ts_(GRAD ? "k_resident_grad" : "k_resident", M_, N_, hs);
-                ts_.launch(k, dim3(s.nloops), dim3(R::NT), R::BYTES, hs, s, uin, uout, T, dtau, scheme, nsteps,
+                ts_.launch(k, dim3(s.nloops), dim3(R::NT), R::BYTES, hs, s.L, uin, uout, T, dtau, scheme, nsteps,
                            J_hist, Jout, dJdTout, status, tw);
                 st = last_error();
             }
@@ -1386,6 +1431,16 @@ struct BatchPlan {
     // group and pass; group g > 0 runs on the plan's stream sx[g - 1] (default priority)
     int nstreams = 2;
     int group_off[3][4][3] = {};  // [K - 2][group][column tiles, row tiles, end]
+    // Loops that fit in LDS take the resident form within loop_batch_step (all steps of a loop in one
+    // block), beside the per-pass kernels of the rest. Classes by block size: 64, 128, 256, 512.
+    ResDesc* d_res = nullptr;
+    int res_off[5] = {0, 0, 0, 0, 0};
+    size_t res_lds[4] = {0, 0, 0, 0};
+    int* d_rest = nullptr;  // the other loops
+    int nrest = 0;
+    int rest_off[3] = {0, 0, 0}, rest_group_off[3][4][3] = {};  // their tile lists
+    bool chosen = false;    // a variant was set by hand: every loop then takes the per-pass kernels
+    mutable std::mutex mu;  // held while a call queues work on the plan's streams and events
     hipStream_t sx[3] = {nullptr, nullptr, nullptr};
     hipEvent_t ev_fork = nullptr, ev_lag[3] = {nullptr, nullptr, nullptr}, ev_join[3] = {nullptr, nullptr, nullptr};
 };
@@ -1447,6 +1502,8 @@ void free_plan(BatchPlan* p) {
     if (p->d_loops) hipFree(p->d_loops);
     if (p->d_items) hipFree(p->d_items);
     if (p->d_tiles) hipFree(p->d_tiles);
+    if (p->d_res) hipFree(p->d_res);
+    if (p->d_rest) hipFree(p->d_rest);
     if (p->ev_fork) hipEventDestroy(p->ev_fork);
     for (int k = 0; k < 3; ++k) {
         if (p->ev_lag[k]) hipEventDestroy(p->ev_lag[k]);
@@ -2148,39 +2205,55 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
                     for (int t = 0; t < p->loops[l].nt[pass]; ++t) items.push_back(item_code(l, pass, t));
         p->ips[x] = (int)items.size() - p->xoff[x] - p->nA[x];
     }
-    // tile lists of the launch-per-pass schedules: passes A, C and E share the column tiles, B
-    // and D the row tiles
-    std::vector<uint32_t> codes;
-    auto add_tiles = [&](int l, bool row) {
-        const int pass = row ? PASS_B : PASS_A;
-        for (int t = 0; t < p->loops[l].nt[pass]; ++t) codes.push_back(item_code(l, pass, t));
-    };
-    for (int row = 0; row < 2; ++row) {
-        for (int l : order) add_tiles(l, row);
-        p->tile_off[row + 1] = (int)codes.size();
-    }
-    // multi-stream schedule: K groups of about equal bytes per step (larger loops placed first,
-    // each on the lightest group so far), for K = 2, 3, 4
-    for (int K = 2; K <= 4; ++K) {
-        std::vector<int> group(nloops, 0);
-        size_t load[4] = {0, 0, 0, 0};
+    // the loops that take the resident form, by block size, and the rest
+    std::vector<ResDesc> res;
+    std::vector<int> rest;
+    std::vector<char> is_res(nloops, 0);
+    for (int c = 0; c < 4; ++c) {
+        p->res_off[c] = (int)res.size();
         for (int l : order) {
-            const Shape& sh = p->loops[l].sh;
-            int g = 0;
-            for (int h = 1; h < K; ++h)
-                if (load[h] < load[g]) g = h;
-            group[l] = g;
-            load[g] += 9 * (size_t)sh.C * sh.N + 4 * (size_t)sh.C * sh.NB;
-        }
-        for (int g = 0; g < K; ++g) {
-            p->group_off[K - 2][g][0] = (int)codes.size();
-            for (int row = 0; row < 2; ++row) {
-                for (int l : order)
-                    if (group[l] == g) add_tiles(l, row);
-                p->group_off[K - 2][g][row + 1] = (int)codes.size();
-            }
+            const BatchLoop& b = p->loops[l];
+            if (!resident_usable(b.sh.M, b.sh.N) || resident_threads(b.sh.M, b.sh.N) != 64 << c) continue;
+            is_res[l] = 1;
+            res.push_back(ResDesc{b.uoff, b.sh.L, l, b.sh.M, b.sh.N, 0});
+            p->res_lds[c] = std::max(p->res_lds[c], resident_bytes(b.sh.M, b.sh.N));
         }
     }
+    p->res_off[4] = (int)res.size();
+    for (int l : order)
+        if (!is_res[l]) rest.push_back(l);
+    p->nrest = (int)rest.size();
+    // tile lists of the launch-per-pass schedules: passes A, C and E share the column tiles, B
+    // and D the row tiles. Of all loops, and of the rest; for each also in K groups of about
+    // equal bytes per step (larger loops placed first, each on the lightest group so far), K = 2, 3, 4.
+    std::vector<uint32_t> codes;
+    auto add_tiles = [&](const std::vector<int>& of, int* off) {
+        off[0] = (int)codes.size();
+        for (int row = 0; row < 2; ++row) {
+            const int pass = row ? PASS_B : PASS_A;
+            for (int l : of)
+                for (int t = 0; t < p->loops[l].nt[pass]; ++t) codes.push_back(item_code(l, pass, t));
+            off[row + 1] = (int)codes.size();
+        }
+    };
+    auto add_lists = [&](const std::vector<int>& of, int* off, int (*goff)[4][3]) {
+        add_tiles(of, off);
+        for (int K = 2; K <= 4; ++K) {
+            std::vector<int> group[4];
+            size_t load[4] = {0, 0, 0, 0};
+            for (int l : of) {
+                const Shape& sh = p->loops[l].sh;
+                int g = 0;
+                for (int h = 1; h < K; ++h)
+                    if (load[h] < load[g]) g = h;
+                group[g].push_back(l);
+                load[g] += 9 * (size_t)sh.C * sh.N + 4 * (size_t)sh.C * sh.NB;
+            }
+            for (int g = 0; g < K; ++g) add_tiles(group[g], goff[K - 2][g]);
+        }
+    };
+    add_lists(order, p->tile_off, p->group_off);
+    if (!res.empty()) add_lists(rest, p->rest_off, p->rest_group_off);
     // one resident wave of blocks
     int per_cu = 1, cus = 1;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch, kBlock, p->lds_bytes) != hipSuccess ||
@@ -2197,6 +2270,16 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
         hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming) != hipSuccess) {
         free_plan(p);
         return LOOP_EHIP;
+    }
+    if (!res.empty()) {
+        if (hipMalloc((void**)&p->d_res, sizeof(ResDesc) * res.size()) != hipSuccess ||
+            hipMemcpy(p->d_res, res.data(), sizeof(ResDesc) * res.size(), hipMemcpyHostToDevice) != hipSuccess ||
+            (!rest.empty() &&
+             (hipMalloc((void**)&p->d_rest, sizeof(int) * rest.size()) != hipSuccess ||
+              hipMemcpy(p->d_rest, rest.data(), sizeof(int) * rest.size(), hipMemcpyHostToDevice) != hipSuccess))) {
+            free_plan(p);
+            return LOOP_EHIP;
+        }
     }
     {
         uint32_t* d_codes = nullptr;
@@ -2321,14 +2404,12 @@ void launch_pass_tiles(const BatchPlan* p, int pass, int step, const BatchArgs& 
     }
 }
 
-void launch_pass(const BatchPlan* p, int pass, int step, const BatchArgs& a, hipStream_t hs) {
-    const int* off = p->tile_off + is_row_pass(pass);
+void launch_list(const BatchPlan* p, const int* off, int pass, int step, const BatchArgs& a, hipStream_t hs) {
+    off += is_row_pass(pass);
     launch_pass_tiles(p, pass, step, a, hs, p->d_tiles + off[0], off[1] - off[0]);
 }
-
-void launch_group_pass(const BatchPlan* p, int g, int pass, int step, const BatchArgs& a, hipStream_t hs) {
-    const int* off = p->group_off[p->nstreams - 2][g] + is_row_pass(pass);
-    launch_pass_tiles(p, pass, step, a, hs, p->d_tiles + off[0], off[1] - off[0]);
+void launch_pass(const BatchPlan* p, int pass, int step, const BatchArgs& a, hipStream_t hs) {
+    launch_list(p, p->tile_off, pass, step, a, hs);
 }
 
 // Multi-stream schedule: group 0 on the caller's stream, group g > 0 on the plan's stream
@@ -2336,30 +2417,106 @@ void launch_group_pass(const BatchPlan* p, int g, int pass, int step, const Batc
 // that the GPU runs different passes of different groups side by side, each as its own
 // kernel with its own registers and LDS. Events fork the plan's streams from the caller's and
 // join them back before the caller's next work. Returns LOOP_EHIP if an event could not be
-// recorded or waited on: the groups' order would then not be guaranteed.
-int launch_streams(const BatchPlan* p, int nsteps, const BatchArgs& a, hipStream_t hs) {
-    const int K = p->nstreams;
+// recorded or waited on: the groups' order would then not be guaranteed. off: the tile lists of
+// the K groups. The caller holds p->mu.
+int launch_streams(const BatchPlan* p, int K, const int (*off)[3], int nsteps, const BatchArgs& a, hipStream_t hs) {
     auto st = [&](int g) { return g == 0 ? hs : p->sx[g - 1]; };
     bool ok = hipEventRecord(p->ev_fork, hs) == hipSuccess;
     for (int g = 1; g < K; ++g) ok = ok && hipStreamWaitEvent(st(g), p->ev_fork, 0) == hipSuccess;
     if (!ok) return LOOP_EHIP;
     for (int g = 0; g < K; ++g) {
         if (g > 0 && hipStreamWaitEvent(st(g), p->ev_lag[g - 1], 0) != hipSuccess) return LOOP_EHIP;
-        launch_group_pass(p, g, PASS_A, 0, a, st(g));
-        launch_group_pass(p, g, PASS_B, 0, a, st(g));
+        launch_list(p, off[g], PASS_A, 0, a, st(g));
+        launch_list(p, off[g], PASS_B, 0, a, st(g));
         if (g + 1 < K && hipEventRecord(p->ev_lag[g], st(g)) != hipSuccess) return LOOP_EHIP;
     }
     // queue the groups' launches in turn, one pass each
     for (int i = 0; i < nsteps; ++i)
         for (int pass = PASS_B; pass <= PASS_E; ++pass)
             for (int g = 0; g < K; ++g)
-                if (!(i == 0 && pass == PASS_B)) launch_group_pass(p, g, pass, i, a, st(g));
+                if (!(i == 0 && pass == PASS_B)) launch_list(p, off[g], pass, i, a, st(g));
     for (int g = 1; g < K; ++g) {
         if (hipEventRecord(p->ev_join[g - 1], st(g)) != hipSuccess ||
             hipStreamWaitEvent(hs, p->ev_join[g - 1], 0) != hipSuccess)
             return LOOP_EHIP;
     }
     return LOOP_OK;
+}
+
+// The resident loops of block size 64 << c, all steps, on stream st.
+int launch_resident_class(const BatchPlan* p, int c, const ResArgs& args, hipStream_t st) {
+    const int n = p->res_off[c + 1] - p->res_off[c];
+    ResArgs a = args;
+    a.loops = p->d_res + p->res_off[c];
+    auto go = [&](auto nt) -> int {
+        constexpr int NT = decltype(nt)::value;
+        auto k = k_resident_batch<NT>;
+        if (ensure_lds_limit(reinterpret_cast<const void*>(k), p->res_lds[c])) return LOOP_EHIP;
+        TraceScope ts_("k_resident_batch", NT, st);
+        ts_.launch(k, dim3(n), dim3(NT), (uint32_t)p->res_lds[c], st, a);
+        return LOOP_OK;
+    };
+    switch (c) {
+        case 0: return go(std::integral_constant<int, 64>{});
+        case 1: return go(std::integral_constant<int, 128>{});
+        case 2: return go(std::integral_constant<int, 256>{});
+        default: return go(std::integral_constant<int, 512>{});
+    }
+}
+
+int convert_batch(const BatchPlan* p, bool to_band, const int* ids, int n, cd* pool, char* ws, hipStream_t hs) {
+    if (n == 0) return LOOP_OK;
+    if (to_band) {
+        TraceScope ts_("k_to_band_batch", 0, hs);
+        ts_.launch(k_to_band_batch, dim3((p->max_nb + 31) / 32, (p->max_c + 31) / 32, n), dim3(256), 0, hs, p->d_loops,
+                   ids, (const cd*)pool, ws);
+    } else {
+        TraceScope ts_("k_from_band_batch", 0, hs);
+        ts_.launch(k_from_band_batch, dim3((p->max_n + 31) / 32, (p->max_h + 31) / 32, n), dim3(256), 0, hs, p->d_loops,
+                   ids, (const char*)ws, pool);
+    }
+    return last_error();
+}
+
+// The resident loops take the plan's streams that the schedule leaves free, forked from the
+// caller's stream before anything else and joined back after the rest's last pass. The long
+// resident launches are queued first: each occupies the CUs of its loops from the start, and
+// the per-pass kernels of the rest share the others.
+int step_with_resident(const BatchPlan* p, cd* pool, int nsteps, const BatchArgs& a, hipStream_t hs) {
+    std::lock_guard<std::mutex> lk(p->mu);
+    const int K = p->schedule == LOOP_BATCH_STREAMS ? std::min(p->nstreams, 3) : 1;
+    const ResArgs r{nullptr, pool, a.T, a.J_hist, a.status, a.tw, a.dtau, a.scheme, a.nsteps, a.nloops};
+    int st, last = -1, next = 2;  // classes from the largest blocks down, on sx[2], sx[1], .. sx[K - 1], then again
+    bool used[3] = {false, false, false};
+    if (hipEventRecord(p->ev_fork, hs) != hipSuccess) return LOOP_EHIP;
+    for (int c = 3; c >= 0; --c) {
+        if (p->res_off[c + 1] == p->res_off[c]) continue;
+        if (p->nrest == 0 && last < 0) {  // nothing else on the caller's stream
+            last = c;
+            continue;
+        }
+        if (!used[next] && hipStreamWaitEvent(p->sx[next], p->ev_fork, 0) != hipSuccess) return LOOP_EHIP;
+        used[next] = true;
+        if ((st = launch_resident_class(p, c, r, p->sx[next]))) return st;
+        next = next > K - 1 ? next - 1 : 2;
+    }
+    if (last >= 0 && (st = launch_resident_class(p, last, r, hs))) return st;
+    if (p->nrest > 0) {
+        if ((st = convert_batch(p, true, p->d_rest, p->nrest, pool, a.ws, hs))) return st;
+        if (K > 1) {
+            if ((st = launch_streams(p, K, p->rest_group_off[K - 2], nsteps, a, hs))) return st;
+        } else {
+            launch_list(p, p->rest_off, PASS_A, 0, a, hs);
+            for (int i = 0; i < nsteps; ++i)
+                for (int pass = PASS_B; pass <= PASS_E; ++pass) launch_list(p, p->rest_off, pass, i, a, hs);
+        }
+        if ((st = convert_batch(p, false, p->d_rest, p->nrest, pool, a.ws, hs))) return st;
+    }
+    for (int k = 0; k < 3; ++k)
+        if (used[k] && (hipEventRecord(p->ev_join[k], p->sx[k]) != hipSuccess ||
+                        hipStreamWaitEvent(hs, p->ev_join[k], 0) != hipSuccess))
+            return LOOP_EHIP;
+    return last_error();
 }
 }  // namespace
 
@@ -2369,10 +2526,8 @@ int loop_batch_load(const void* plan, const double* uhat_pool, void* ws, size_t 
     int st = batch_check(p, ws, ws_bytes, &tw);
     if (st) return st;
     if (!aligned(uhat_pool, 16)) return LOOP_EINVAL;
-    TraceScope ts_("k_to_band_batch", 0, (hipStream_t)stream);
-    ts_.launch(k_to_band_batch, dim3((p->max_nb + 31) / 32, (p->max_c + 31) / 32, p->nloops), dim3(256), 0,
-                       (hipStream_t)stream, p->d_loops, reinterpret_cast<const cd*>(uhat_pool), static_cast<char*>(ws));
-    return last_error();
+    return convert_batch(p, true, nullptr, p->nloops, const_cast<cd*>(reinterpret_cast<const cd*>(uhat_pool)),
+                         static_cast<char*>(ws), (hipStream_t)stream);
 }
 
 int loop_batch_store(const void* plan, double* uhat_pool, void* ws, size_t ws_bytes, void* stream) {
@@ -2381,10 +2536,8 @@ int loop_batch_store(const void* plan, double* uhat_pool, void* ws, size_t ws_by
     int st = batch_check(p, ws, ws_bytes, &tw);
     if (st) return st;
     if (!aligned(uhat_pool, 16)) return LOOP_EINVAL;
-    TraceScope ts_("k_from_band_batch", 0, (hipStream_t)stream);
-    ts_.launch(k_from_band_batch, dim3((p->max_n + 31) / 32, (p->max_h + 31) / 32, p->nloops), dim3(256), 0,
-                       (hipStream_t)stream, p->d_loops, static_cast<const char*>(ws), reinterpret_cast<cd*>(uhat_pool));
-    return last_error();
+    return convert_batch(p, false, nullptr, p->nloops, reinterpret_cast<cd*>(uhat_pool), static_cast<char*>(ws),
+                         (hipStream_t)stream);
 }
 
 int loop_batch_pass(const void* plan, int pass, int step, int nsteps, double* T, double dtau, int scheme,
@@ -2412,6 +2565,11 @@ int loop_batch_step(const void* plan, double* T, double* uhat_pool, double dtau,
     if (st) return st;
     hipStream_t hs = (hipStream_t)stream;
     char* base = static_cast<char*>(ws);
+    // the same arithmetic as row variants 0 to 2, so the same bits; variant 3 pairs rows differently
+    if (nsteps > 0 && p->res_off[4] > 0 && p->schedule != LOOP_BATCH_PERSISTENT && !p->chosen &&
+        p->variant[PASS_B] < 3 && p->variant[PASS_D] < 3 && g_resident.load() != 0)
+        return step_with_resident(p, reinterpret_cast<cd*>(uhat_pool), nsteps,
+                                  batch_args(p, base, T, J_hist, nsteps, dtau, scheme, tw), hs);
     if ((st = loop_batch_load(plan, uhat_pool, ws, ws_bytes, stream))) return st;
     if (nsteps > 0) {
         const BatchArgs a = batch_args(p, base, T, J_hist, nsteps, dtau, scheme, tw);
@@ -2422,7 +2580,8 @@ int loop_batch_step(const void* plan, double* T, double* uhat_pool, double dtau,
             TraceScope ts_("k_batch", 0, hs);
             ts_.launch(k_batch, dim3(p->grid), dim3(kBlock), p->lds_bytes, hs, a);
         } else if (p->schedule == LOOP_BATCH_STREAMS) {
-            if ((st = launch_streams(p, nsteps, a, hs))) return st;
+            std::lock_guard<std::mutex> lk(p->mu);
+            if ((st = launch_streams(p, p->nstreams, p->group_off[p->nstreams - 2], nsteps, a, hs))) return st;
         } else {
             launch_pass(p, PASS_A, 0, a, hs);
             for (int i = 0; i < nsteps; ++i)
@@ -2450,6 +2609,7 @@ int loop_batch_set_variant(void* plan, int pass, int variant) {
     BatchPlan* p = static_cast<BatchPlan*>(plan);
     if (!p || pass < PASS_A || pass > PASS_E || !rag_covers(p, pass, variant)) return LOOP_EINVAL;
     p->variant[pass] = variant;
+    p->chosen = true;
     return LOOP_OK;
 }
 

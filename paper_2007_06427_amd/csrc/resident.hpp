@@ -77,7 +77,7 @@ struct ResG {
 // Split of the products' spectrum (slots va) into rows a and b of X, through the pair's region z.
 // SYNC: z lies in X, so the block waits for every wavefront to have read its part.
 template <int M, int N, bool DX, bool SYNC>
-__device__ __forceinline__ void res_split(const Shape& sh, const cd* va, cd* z, int t, cd* X, int a, bool on) {
+__device__ __forceinline__ void res_split(double L, const cd* va, cd* z, int t, cd* X, int a, bool on) {
     using R = ResG<M, N>;
     using G = RowG<M>;
     constexpr int NJ = (G::CMAX + G::TPF - 1) / G::TPF;
@@ -87,7 +87,7 @@ __device__ __forceinline__ void res_split(const Shape& sh, const cd* va, cd* z, 
 #pragma unroll
     for (int i = 0; i < NJ; ++i) {
         const int j = t + i * G::TPF < G::CMAX ? t + i * G::TPF : 0;
-        row_split<M, DX>(sh.L, j, z[j], z[j == 0 ? 0 : M - G::SH - j], wa[i], wb[i]);
+        row_split<M, DX>(L, j, z[j], z[j == 0 ? 0 : M - G::SH - j], wa[i], wb[i]);
     }
     if constexpr (SYNC)
         __syncthreads();
@@ -104,12 +104,13 @@ __device__ __forceinline__ void res_split(const Shape& sh, const cd* va, cd* z, 
     }
 }
 
-// All of a block's work for loop l: nsteps steps (uin -> uout in the rfft layout, T[l] in place),
-// or, with GRAD, the flow G_1 into uout and J, dJ/dT into Jout, dJdTout (each may be null).
+// All of a block's work for one loop: nsteps steps (src -> dst in the rfft layout, *T in place, J of
+// step i into J_hist[i * jstride]), or, with GRAD, the flow G_1 into dst and J, dJ/dT into *Jout,
+// *dJdTout. J_hist, Jout and dJdTout may be null; src and dst may be the same.
 template <int M, int N, bool GRAD>
-__device__ __forceinline__ void resident_loop(const Shape& sh, int l, const cd* uin, cd* uout, double* T, double dtau,
-                                              int scheme, int nsteps, double* J_hist, int jstride, double* Jout,
-                                              double* dJdTout, int* status, cd* lds, const cd* __restrict__ tw) {
+__device__ __forceinline__ void resident_loop(double L, const cd* src, cd* dst, double* T, double dtau, int scheme,
+                                              int nsteps, double* J_hist, int jstride, double* Jout, double* dJdTout,
+                                              int* status, cd* lds, const cd* __restrict__ tw) {
     using R = ResG<M, N>;
     using G = RowG<M>;
     constexpr int PT = R::PT, LD = R::LD;
@@ -142,7 +143,7 @@ __device__ __forceinline__ void resident_loop(const Shape& sh, int l, const cd* 
     TwCache<N, PT> twc;
     tw_cache_load<M, PT>(twr, pr, tw);
     tw_cache_load<N, PT>(twc, pc, tw);
-    const ColCoef f(col_on ? j : 0, sh.L);
+    const ColCoef f(col_on ? j : 0, L);
     const double wj = (j == 0) ? 1.0 : 2.0;
     constexpr double invN = 1.0 / N;
     Work w{};
@@ -151,12 +152,14 @@ __device__ __forceinline__ void resident_loop(const Shape& sh, int l, const cd* 
     w.dJdT = sc + 3;
     w.Told = sc + 1;
     w.status = status;
-    Shape s1 = sh;
+    Shape s1{};
+    s1.C = R::C;
+    s1.N = N;
+    s1.L = L;
     s1.nloops = 1;
 
     cd u[PT], ug[PT], v[PT];
     double s[PT];
-    const cd* src = uin + (size_t)l * N * R::H;
     static_for<PT>([&](auto mc) {
         constexpr int m = decltype(mc)::value;
         using B = BandSlot<N, m>;
@@ -173,7 +176,7 @@ __device__ __forceinline__ void resident_loop(const Shape& sh, int l, const cd* 
         }
         u[m] = x;
     });
-    if (tid == 0) sc[0] = T[l];
+    if (tid == 0) sc[0] = *T;
     auto store_col = [&](cd* col) {  // v (points) into a column of A or X
         if (pts_on)
 #pragma unroll
@@ -200,7 +203,7 @@ __device__ __forceinline__ void resident_loop(const Shape& sh, int l, const cd* 
 #pragma unroll
             for (int m = 0; m < PT; ++m) v[m] = cd{ug[m].x * ug[m].x, ug[m].y * ug[m].y};
             fft_fwd<M, PT, true>(v, exB, twr, pr);
-            res_split<M, N, true, R::SPLIT>(sh, v, exB + pr.xs * R::ZS, pr.t, X, a, row_on);
+            res_split<M, N, true, R::SPLIT>(L, v, exB + pr.xs * R::ZS, pr.t, X, a, row_on);
         }
         __syncthreads();
         const double invT = 1.0 / sc[0];
@@ -242,15 +245,14 @@ __device__ __forceinline__ void resident_loop(const Shape& sh, int l, const cd* 
         // J, dJ/dT and T' from the partials; no other wavefront reads them before the next pass C
         if (wave == R::NT / 64 - 1)
             finalize_loop(s1, 0, w, sc, GRAD ? MODE_GRAD : MODE_STEP, dtau,
-                          J_hist ? J_hist + (size_t)st * jstride + l : nullptr, Jout ? Jout + l : nullptr,
-                          dJdTout ? dJdTout + l : nullptr);
+                          J_hist ? J_hist + (size_t)st * jstride : nullptr, Jout, dJdTout);
         if (rows_here) {  // pass D: u r_x
             row_gather_raw<G, R::B_ROW>(X, LD, a, a + R::P, pr.t, v);
             fft_inv<M, PT, true>(v, exD, twr, pr);
 #pragma unroll
             for (int m = 0; m < PT; ++m) v[m] = cd{ug[m].x * v[m].x, ug[m].y * v[m].y};
             fft_fwd<M, PT, true>(v, exD, twr, pr);
-            res_split<M, N, false, false>(sh, v, exD + pr.xs * R::ZS, pr.t, X, a, row_on);
+            res_split<M, N, false, false>(L, v, exD + pr.xs * R::ZS, pr.t, X, a, row_on);
         }
         __syncthreads();
         if (cols_here) load_col();
@@ -274,13 +276,12 @@ __device__ __forceinline__ void resident_loop(const Shape& sh, int l, const cd* 
         if (col_on && B::in(pc.t)) A[j * R::NB + B::kk(pc.t)] = u[m];
     });
     __syncthreads();
-    cd* o = uout + (size_t)l * N * R::H;
     for (int i = tid; i < N * R::H; i += R::NT) {
         const int e = i / R::H, jj = i % R::H;
         const int kk = jj < R::C ? band_row(e, N, R::Ks) : -1;
-        o[i] = kk >= 0 ? A[jj * R::NB + kk] : cd{0.0, 0.0};
+        dst[i] = kk >= 0 ? A[jj * R::NB + kk] : cd{0.0, 0.0};
     }
-    if (!GRAD && tid == 0) T[l] = sc[0];
+    if (!GRAD && tid == 0) *T = sc[0];
 }
 
 }  // namespace lo
