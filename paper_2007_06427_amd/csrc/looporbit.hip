@@ -777,6 +777,7 @@ struct RagArgs {
     const cd* tw;
     double dtau;
     int scheme, nsteps, nloops, step;
+    int in_place;  // i q r in BD, U1 in U (kInPlaceBytes)
 };
 
 template <int PASS, int V>
@@ -801,6 +802,10 @@ __global__ __launch_bounds__(kBlock) void k_rag(RagArgs a) {
     w.Cb = reinterpret_cast<cd*>(p += d.inter);
     w.U = reinterpret_cast<cd*>(p += d.inter);
     w.G = reinterpret_cast<cd*>(p += d.band);
+    if (a.in_place) {
+        w.Cb = w.BD;
+        w.G = w.U;
+    }
     w.partial = reinterpret_cast<double*>(p += d.band);
     w.J = reinterpret_cast<double*>(p += d.part);
     w.dJdT = reinterpret_cast<double*>(p += sizeof(WsRegion));
@@ -1524,6 +1529,29 @@ unsigned elem_blocks(size_t n) {
 }  // namespace
 
 namespace {
+// Large calls keep fewer arrays: an intermediate or band array that the call reads once is written
+// over by the pass that reads it, whose blocks read all of their own part before they write any of
+// it. Pass C then leaves i q r in BD instead of Cb, and in a step U1 takes u_hat's place: 240 MB
+// for 64 loops of 256 x 1024 instead of 390, and the 256 MB Infinity Cache holds most of what one
+// pass hands to the next. Measured there: a step 217.5 us instead of 240.9, loop_adjoint_grad
+// 294 instead of 313, loop_residual 182 instead of 200. Below about half the Infinity Cache both
+// orders stay in it and writing elsewhere is as fast or faster (64 loops of 256 x 512: 121 either
+// way; 8 of 256 x 1024: 53.8 in place, 52.4 apart), so calls of less than kInPlaceBytes of work
+// space keep the arrays apart.
+constexpr size_t kInPlaceBytes = 128u << 20;
+bool in_place_pays(const Shape& s) { return layout(s, nullptr, nullptr) > kInPlaceBytes; }
+
+// pass C over B's columns, pass D over C's rows; in a step, U1 over u_hat
+void reuse_c(const Shape& s, Work& w, bool step) {
+    if (!in_place_pays(s)) return;
+    w.Cb = w.BD;
+    if (step) w.G = w.U;
+}
+// pass B over A's rows, where pass D does not read them again
+void reuse_a(const Shape& s, Work& w) {
+    if (in_place_pays(s)) w.BD = w.A;
+}
+
 // Argument checks shared by loop_step and loop_step_noalloc.
 int step_args(const double* T, const double* uhat, double dtau, int scheme, int nsteps, const double* J_hist) {
     if (!aligned(T, 8) || !aligned(uhat, 16) || (J_hist && !aligned(J_hist, 8))) return LOOP_EINVAL;
@@ -1533,11 +1561,12 @@ int step_args(const double* T, const double* uhat, double dtau, int scheme, int 
 
 // The steps of loop_step on a prepared work space: the resident form, or the per-pass kernels
 // between the conversions into and out of the band layout.
-int step_impl(const Shape& s, const Work& w, const cd* tw, double* T, cd* u, double dtau, int scheme, int nsteps,
+int step_impl(const Shape& s, Work w, const cd* tw, double* T, cd* u, double dtau, int scheme, int nsteps,
               double* J_hist, hipStream_t hs) {
     int st;
     if (loop_step_form(s.M, s.N, s.nloops) == 1)
         return launch_resident<false>(s, u, u, T, dtau, scheme, nsteps, J_hist, nullptr, nullptr, w.status, tw, hs);
+    reuse_c(s, w, true);
     launch_to_band(s, u, w.U, hs);
     if (nsteps > 0 && (st = launch_A(s, w, tw, hs))) return st;
     for (int i = 0; i < nsteps; ++i) {
@@ -1621,6 +1650,7 @@ int loop_residual(double L, int Nx, int Ns, int nloops, const double* T, const d
     int st = prepare(L, Nx, Ns, nloops, ws, ws_bytes, &s, &w, &tw);
     if (st) return st;
     hipStream_t hs = (hipStream_t)stream;
+    reuse_a(s, w);
     launch_to_band(s, reinterpret_cast<const cd*>(uhat), w.U, hs);
     if ((st = launch_A(s, w, tw, hs))) return st;
     if ((st = launch_B(s, w, tw, hs))) return st;
@@ -1638,6 +1668,7 @@ int loop_cost(double L, int Nx, int Ns, int nloops, const double* T, const doubl
     int st = prepare(L, Nx, Ns, nloops, ws, ws_bytes, &s, &w, &tw);
     if (st) return st;
     hipStream_t hs = (hipStream_t)stream;
+    reuse_a(s, w);
     launch_to_band(s, reinterpret_cast<const cd*>(uhat), w.U, hs);
     if ((st = launch_A(s, w, tw, hs))) return st;
     if ((st = launch_B(s, w, tw, hs))) return st;
@@ -1663,6 +1694,7 @@ int loop_adjoint_grad(double L, int Nx, int Ns, int nloops, const double* T, con
     if (loop_step_form(Nx, Ns, nloops) == 1 && (nloops == 1 || Ns % row_tile(Nx) == 0))
         return launch_resident<true>(s, reinterpret_cast<const cd*>(uhat), reinterpret_cast<cd*>(Ghat),
                                      const_cast<double*>(T), 0.0, 0, 1, nullptr, J, dJdT, w.status, tw, hs);
+    reuse_c(s, w, false);
     launch_to_band(s, reinterpret_cast<const cd*>(uhat), w.U, hs);
     if ((st = launch_A(s, w, tw, hs))) return st;
     if ((st = launch_B(s, w, tw, hs))) return st;
@@ -1684,6 +1716,7 @@ int loop_cost_grad(double L, int Nx, int Ns, int nloops, const double* T, const 
     int st = prepare(L, Nx, Ns, nloops, ws, ws_bytes, &s, &w, &tw);
     if (st) return st;
     hipStream_t hs = (hipStream_t)stream;
+    reuse_c(s, w, false);
     launch_to_band(s, reinterpret_cast<const cd*>(uhat), w.U, hs);
     if ((st = launch_A(s, w, tw, hs))) return st;
     if ((st = launch_B(s, w, tw, hs))) return st;
@@ -1746,7 +1779,10 @@ int loop_cost_fwd(double L, int Nx, int Ns, int nloops, int layout, const double
     hipStream_t hs = (hipStream_t)stream;
     if ((st = bind_state(s, w, layout, u, hs))) return st;
     w.G = reinterpret_cast<cd*>(rsave);  // pass C writes the residual there
-    if (usave) w.A = reinterpret_cast<cd*>(usave);  // pass A leaves u on the s grid there
+    if (usave)
+        w.A = reinterpret_cast<cd*>(usave);  // pass A leaves u on the s grid there
+    else
+        reuse_a(s, w);
     if ((st = launch_A(s, w, tw, hs))) return st;
     if ((st = launch_B(s, w, tw, hs))) return st;
     if ((st = launch_C(s, T, w, MODE_RESIDUAL, 0.0, 0, tw, hs))) return st;
@@ -1774,6 +1810,7 @@ int loop_cost_bwd(double L, int Nx, int Ns, int nloops, int layout, const double
     hipStream_t hs = (hipStream_t)stream;
     // the spectrum itself is read only to recompute u on the s grid
     if (!usave && (st = bind_state(s, w, layout, u, hs))) return st;
+    reuse_c(s, w, false);
     w.R = reinterpret_cast<const cd*>(rsave);
     w.gJ = gJ;
     w.dJdT_in = dJdT;
@@ -1861,6 +1898,7 @@ int loop_expanded_grad(double L, int Nx, int Ns, int nloops, const double* T, co
     if (st) return st;
     if (Nx > 512 || (size_t)s.C * s.NB < (size_t)s.N) return LOOP_ENOTSUP;
     hipStream_t hs = (hipStream_t)stream;
+    reuse_c(s, w, false);
     launch_to_band(s, reinterpret_cast<const cd*>(uhat), w.U, hs);
     if ((st = launch_x_grad_or_step(s, w, const_cast<double*>(T), MODE_GRAD, 0.0, 0, 1, nullptr, J, dJdT, tw, hs)))
         return st;
@@ -1880,6 +1918,7 @@ int loop_step_expanded(double L, int Nx, int Ns, int nloops, double* T, double* 
     if (Nx > 512 || (size_t)s.C * s.NB < (size_t)s.N) return LOOP_ENOTSUP;
     hipStream_t hs = (hipStream_t)stream;
     cd* u = reinterpret_cast<cd*>(uhat);
+    reuse_c(s, w, false);
     launch_to_band(s, u, w.U, hs);
     if (nsteps > 0 &&
         (st = launch_x_grad_or_step(s, w, T, MODE_STEP, dtau, scheme, nsteps, J_hist, nullptr, nullptr, tw, hs)))
@@ -2388,12 +2427,12 @@ const char* rag_name(int pass, int v) {
 }
 
 void launch_pass_tiles(const BatchPlan* p, int pass, int step, const BatchArgs& a, hipStream_t hs,
-                       const TileDesc* c, int n) {
+                       const TileDesc* c, int n, int in_place) {
     if (n == 0) return;
     const dim3 grid(n);
     const int v = p->variant[pass];
     const size_t lds = p->pass_lds[pass][v];
-    const RagArgs r{c, a.ws, a.status, a.T, a.J_hist, a.tw, a.dtau, a.scheme, a.nsteps, a.nloops, step};
+    const RagArgs r{c, a.ws, a.status, a.T, a.J_hist, a.tw, a.dtau, a.scheme, a.nsteps, a.nloops, step, in_place};
     TraceScope ts_(rag_name(pass, v), 0, hs);
     switch (pass) {
         case PASS_A: launch_rag<PASS_A>(v, grid, lds, hs, r, ts_); break;
@@ -2404,12 +2443,15 @@ void launch_pass_tiles(const BatchPlan* p, int pass, int step, const BatchArgs& 
     }
 }
 
-void launch_list(const BatchPlan* p, const int* off, int pass, int step, const BatchArgs& a, hipStream_t hs) {
+void launch_list(const BatchPlan* p, const int* off, int pass, int step, const BatchArgs& a, hipStream_t hs,
+                 bool repeatable = false) {
     off += is_row_pass(pass);
-    launch_pass_tiles(p, pass, step, a, hs, p->d_tiles + off[0], off[1] - off[0]);
+    launch_pass_tiles(p, pass, step, a, hs, p->d_tiles + off[0], off[1] - off[0],
+                      !repeatable && p->ws_bytes > kInPlaceBytes);
 }
+// One pass of all loops, for loop_batch_pass and the tuner: what it reads stays as it was.
 void launch_pass(const BatchPlan* p, int pass, int step, const BatchArgs& a, hipStream_t hs) {
-    launch_list(p, p->tile_off, pass, step, a, hs);
+    launch_list(p, p->tile_off, pass, step, a, hs, true);
 }
 
 // Multi-stream schedule: group 0 on the caller's stream, group g > 0 on the plan's stream
@@ -2583,9 +2625,9 @@ int loop_batch_step(const void* plan, double* T, double* uhat_pool, double dtau,
             std::lock_guard<std::mutex> lk(p->mu);
             if ((st = launch_streams(p, p->nstreams, p->group_off[p->nstreams - 2], nsteps, a, hs))) return st;
         } else {
-            launch_pass(p, PASS_A, 0, a, hs);
+            launch_list(p, p->tile_off, PASS_A, 0, a, hs);
             for (int i = 0; i < nsteps; ++i)
-                for (int pass = PASS_B; pass <= PASS_E; ++pass) launch_pass(p, pass, i, a, hs);
+                for (int pass = PASS_B; pass <= PASS_E; ++pass) launch_list(p, p->tile_off, pass, i, a, hs);
         }
     }
     return loop_batch_store(plan, uhat_pool, ws, ws_bytes, stream);
