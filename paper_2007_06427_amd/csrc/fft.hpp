@@ -248,16 +248,39 @@ struct FftPos {
 // every transform it runs. The cache holds w, w^2, w^4 (and w^8) as read from the table, and
 // the other powers are formed by one or two complex products, each within a few units in the
 // last place. The inverse transform uses the conjugates, after its butterflies.
-template <int N, int PT>
+//
+// With ALL it holds every power instead, formed once by the same products (equal bit for bit): 16
+// registers more per stage, and four products (16 instructions of about 100) less per stage
+// of every transform.
+template <int N, int PT, bool ALL_ = false>
 struct TwCache {
-    static constexpr int NB = ilog2(PT);
+    static_assert(!ALL_ || PT == 8, "tw_powers");
+    static constexpr bool ALL = ALL_;
+    static constexpr int NB = ALL ? PT - 1 : ilog2(PT);
     static constexpr int L = Fft<N, PT>::L;
     cd w[L][NB];
 };
 
+// An opaque copy of a cached twiddle: products formed from it are not merged with products
+// formed for another transform, so the derived powers do not stay live between transforms.
+__device__ __forceinline__ cd opaque(cd w) {
+    asm volatile("" : "+v"(w.x), "+v"(w.y));
+    return w;
+}
+
+// w^3, w^5, w^6, w^7 from w, w^2, w^4 (w[m - 1] = w^m), formed as apply_twiddles forms them
+__device__ __forceinline__ void tw_powers(cd* w) {
+    w[2] = cmul(w[0], w[1]);
+    w[4] = cmul(w[0], w[3]);
+    w[5] = cmul(w[1], w[3]);
+    w[6] = cmul(w[2], w[3]);
+#pragma unroll
+    for (int b = 0; b < 7; ++b) w[b] = opaque(w[b]);
+}
+
 // Table entries of stage i, whose input spectrum positions run over [0, F PT^(i-1)).
-template <int N, int PT, int I, class Pos>
-__device__ __forceinline__ void tw_cache_fill(TwCache<N, PT>& c, const Pos& p, const cd* __restrict__ tw) {
+template <int N, int PT, int I, bool ALL, class Pos>
+__device__ __forceinline__ void tw_cache_fill(TwCache<N, PT, ALL>& c, const Pos& p, const cd* __restrict__ tw) {
     using E = Fft<N, PT>;
     constexpr int span = I == 1 ? E::F : I == 2 ? E::F * PT : E::F * PT * PT;
     if constexpr (span > 1) {
@@ -271,21 +294,15 @@ __device__ __forceinline__ void tw_cache_fill(TwCache<N, PT>& c, const Pos& p, c
             ti = p.f1;  // the middle stage of three
         }
 #pragma unroll
-        for (int b = 0; b < TwCache<N, PT>::NB; ++b) c.w[I - 1][b] = tw[((ti << b) * step) & (TW_N - 1)];
+        for (int b = 0; b < ilog2(PT); ++b) c.w[I - 1][ALL ? (1 << b) - 1 : b] = tw[((ti << b) * step) & (TW_N - 1)];
+        if constexpr (ALL) tw_powers(c.w[I - 1]);
     }
-    if constexpr (I < E::L) tw_cache_fill<N, PT, I + 1>(c, p, tw);
+    if constexpr (I < E::L) tw_cache_fill<N, PT, I + 1, ALL>(c, p, tw);
 }
 
-template <int N, int PT, class Pos>
-__device__ __forceinline__ void tw_cache_load(TwCache<N, PT>& c, const Pos& p, const cd* __restrict__ tw) {
-    tw_cache_fill<N, PT, 1>(c, p, tw);
-}
-
-// An opaque copy of a cached twiddle: products formed from it are not merged with products
-// formed for another transform, so the derived powers do not stay live between transforms.
-__device__ __forceinline__ cd opaque(cd w) {
-    asm volatile("" : "+v"(w.x), "+v"(w.y));
-    return w;
+template <int N, int PT, bool ALL, class Pos>
+__device__ __forceinline__ void tw_cache_load(TwCache<N, PT, ALL>& c, const Pos& p, const cd* __restrict__ tw) {
+    tw_cache_fill<N, PT, 1, ALL>(c, p, tw);
 }
 
 template <bool INV>
@@ -294,8 +311,13 @@ __device__ __forceinline__ cd cmul_tw(cd a, cd w) {
 }
 
 // Apply w^(k r) to element r of butterfly i (elements in slots i + r NB), from the cache.
-template <int R, int NB, bool INV>
+template <int R, int NB, bool INV, bool ALL = false>
 __device__ __forceinline__ void apply_twiddles(cd* v, int i, const cd* base) {
+    if constexpr (ALL) {
+#pragma unroll
+        for (int m = 1; m < R; ++m) v[i + m * NB] = cmul_tw<INV>(v[i + m * NB], base[m - 1]);
+        return;
+    }
     const cd w1 = opaque(base[0]);
     v[i + NB] = cmul_tw<INV>(v[i + NB], w1);
     if constexpr (R >= 4) {
@@ -488,44 +510,44 @@ __device__ __forceinline__ void exchange(cd* v, cd* ex, const Pos& p) {
 
 // Forward transform, points layout in, spectrum layout out. All threads of a wavefront (of
 // the block, for transforms of two wavefronts) must call; ex: the block's exchange space.
-template <int N, int PT, bool XLOW = false>
-__device__ __forceinline__ void fft_fwd(cd* v, cd* ex, const TwCache<N, PT>& c, const FftPos<N, PT, XLOW>& p) {
+template <int N, int PT, bool XLOW = false, bool ALL>
+__device__ __forceinline__ void fft_fwd(cd* v, cd* ex, const TwCache<N, PT, ALL>& c, const FftPos<N, PT, XLOW>& p) {
     using E = Fft<N, PT, XLOW>;
     if constexpr (E::F > 1) {
         dft_f<PT, E::F, false>(v);
         swap_f<PT, E::F>(v);
-        apply_twiddles<PT, 1, false>(v, 0, c.w[0]);
+        apply_twiddles<PT, 1, false, ALL>(v, 0, c.w[0]);
     }
     dft_pt<PT, false>(v);
     if constexpr (E::L >= 2) {
         exchange<N, PT, XLOW, 1, true>(v, ex, p);
-        apply_twiddles<PT, 1, false>(v, 0, c.w[1]);
+        apply_twiddles<PT, 1, false, ALL>(v, 0, c.w[1]);
         dft_pt<PT, false>(v);
     }
     if constexpr (E::L >= 3) {
         exchange<N, PT, XLOW, 2, true>(v, ex, p);
-        apply_twiddles<PT, 1, false>(v, 0, c.w[2]);
+        apply_twiddles<PT, 1, false, ALL>(v, 0, c.w[2]);
         dft_pt<PT, false>(v);
     }
 }
 
 // Inverse transform, spectrum layout in, points layout out.
-template <int N, int PT, bool XLOW = false>
-__device__ __forceinline__ void fft_inv(cd* v, cd* ex, const TwCache<N, PT>& c, const FftPos<N, PT, XLOW>& p) {
+template <int N, int PT, bool XLOW = false, bool ALL>
+__device__ __forceinline__ void fft_inv(cd* v, cd* ex, const TwCache<N, PT, ALL>& c, const FftPos<N, PT, XLOW>& p) {
     using E = Fft<N, PT, XLOW>;
     dft_pt<PT, true>(v);
     if constexpr (E::L >= 3) {
-        apply_twiddles<PT, 1, true>(v, 0, c.w[2]);
+        apply_twiddles<PT, 1, true, ALL>(v, 0, c.w[2]);
         exchange<N, PT, XLOW, 2, false>(v, ex, p);
         dft_pt<PT, true>(v);
     }
     if constexpr (E::L >= 2) {
-        apply_twiddles<PT, 1, true>(v, 0, c.w[1]);
+        apply_twiddles<PT, 1, true, ALL>(v, 0, c.w[1]);
         exchange<N, PT, XLOW, 1, false>(v, ex, p);
         dft_pt<PT, true>(v);
     }
     if constexpr (E::F > 1) {
-        apply_twiddles<PT, 1, true>(v, 0, c.w[0]);
+        apply_twiddles<PT, 1, true, ALL>(v, 0, c.w[0]);
         swap_f<PT, E::F>(v);
         dft_f<PT, E::F, true>(v);
     }

@@ -39,8 +39,13 @@ __global__ __launch_bounds__(kBlock) void k_colA(Shape sh, Work w, const cd* __r
     col_pass_A<N>(sh, blockIdx.x, w, ex, tw);
 }
 
+// Wavefronts per SIMD of the row kernels that keep their twiddle powers (kRowAll): three, what
+// their LDS allows too (at most 168 registers each).
 template <int M>
-__global__ __launch_bounds__(kBlock) void k_rowB(Shape sh, Work w, const cd* __restrict__ tw) {
+constexpr int kRowWaves = kRowAll<M> ? 3 : 1;
+
+template <int M>
+__global__ __launch_bounds__(kBlock, kRowWaves<M>) void k_rowB(Shape sh, Work w, const cd* __restrict__ tw) {
     __shared__ cd lds[RowG<M>::LDS_B];
     row_pass_B<M>(sh, blockIdx.x, w, lds, tw);
 }
@@ -56,7 +61,7 @@ __global__ __launch_bounds__(kBlock) void k_colC(Shape sh, const double* __restr
 }
 
 template <int M>
-__global__ __launch_bounds__(kBlock) void k_rowD(Shape sh, Work w, double* T, int mode, double dtau,
+__global__ __launch_bounds__(kBlock, kRowWaves<M>) void k_rowD(Shape sh, Work w, double* T, int mode, double dtau,
                                                  double* J_hist, double* Jout, double* dJdTout,
                                                  const cd* __restrict__ tw) {
     __shared__ cd lds[RowG<M>::LDS];
@@ -123,8 +128,8 @@ __global__ __launch_bounds__(kBlock) void k_xi_colA(Shape sh, XiWork w, const cd
     xi_col_pass_A<N>(sh, blockIdx.x, w, ex, tw);
 }
 template <int M>
-__global__ __launch_bounds__(kBlock) void k_xi_rowB(Shape sh, XiWork w, const cd* __restrict__ tw) {
-    __shared__ cd lds[RowG<M>::LDS];
+__global__ __launch_bounds__(kBlock, kRowWaves<M>) void k_xi_rowB(Shape sh, XiWork w, const cd* __restrict__ tw) {
+    __shared__ cd lds[RowG<M>::LDS_B];
     xi_row_pass_B<M>(sh, blockIdx.x, w, lds, tw);
 }
 template <int N>
@@ -135,7 +140,7 @@ __global__ __launch_bounds__(kBlock) void k_xi_colC(Shape sh, const double* __re
     xi_col_pass_C<N>(sh, blockIdx.x, T, w, dtau, scheme, ex, red, tw);
 }
 template <int M>
-__global__ __launch_bounds__(kBlock) void k_xi_rowD(Shape sh, XiWork w, double* T, double dtau, double* J_hist,
+__global__ __launch_bounds__(kBlock, kRowWaves<M>) void k_xi_rowD(Shape sh, XiWork w, double* T, double dtau, double* J_hist,
                                                     const cd* __restrict__ tw) {
     __shared__ cd lds[RowG<M>::LDS];
     xi_row_pass_D<M>(sh, blockIdx.x, w, T, dtau, J_hist, lds, tw);
@@ -781,7 +786,7 @@ struct RagArgs {
 };
 
 template <int PASS, int V>
-__global__ __launch_bounds__(kBlock) void k_rag(RagArgs a) {
+__global__ __launch_bounds__(kBlock, is_row_pass(PASS) && V == 0 ? kRowWaves<512> : 1) void k_rag(RagArgs a) {
     constexpr RagVariant var = rag_variant(PASS, V);
     extern __shared__ __align__(16) cd lds[];  // 16-byte aligned: one ds_read_b128 per complex value
     __shared__ double red[2 * kBlock / 64];
@@ -1533,11 +1538,11 @@ namespace {
 // over by the pass that reads it, whose blocks read all of their own part before they write any of
 // it. Pass C then leaves i q r in BD instead of Cb, and in a step U1 takes u_hat's place: 240 MB
 // for 64 loops of 256 x 1024 instead of 390, and the 256 MB Infinity Cache holds most of what one
-// pass hands to the next. Measured there: a step 217.5 us instead of 240.9, loop_adjoint_grad
-// 294 instead of 313, loop_residual 182 instead of 200. Below about half the Infinity Cache both
-// orders stay in it and writing elsewhere is as fast or faster (64 loops of 256 x 512: 121 either
-// way; 8 of 256 x 1024: 53.8 in place, 52.4 apart), so calls of less than kInPlaceBytes of work
-// space keep the arrays apart.
+// pass hands to the next. Measured there, before and after: a step 240.9 and 217.5 us (now 210),
+// loop_adjoint_grad 313 and 294 (290), loop_residual 200 and 182 (178). Below about half the
+// Infinity Cache both orders stay in it and writing elsewhere is as fast or faster (64 loops of
+// 256 x 512: 121 either way; 8 of 256 x 1024: 53.8 in place, 52.4 apart), so calls of less than
+// kInPlaceBytes of work space keep the arrays apart.
 constexpr size_t kInPlaceBytes = 128u << 20;
 bool in_place_pays(const Shape& s) { return layout(s, nullptr, nullptr) > kInPlaceBytes; }
 

@@ -459,6 +459,13 @@ struct RowG {
     static constexpr int TILE = CMAX * TS;
 };
 
+// Rows of 64 to 512 points keep the twiddle powers (TwCache): they are bound by the vector units'
+// issue rate, and the registers cost them no wavefront (pass B of 64 loops of 256 x 1024 went
+// from 137 to 168, three wavefronts per SIMD either way, and from 54.3 us to 49.5; pass D 59.7
+// to 58.7). Eight points per thread; the 1024-point rows hold 16 and have no registers left.
+template <int M, int PT = RowG<M>::PT>
+constexpr bool kRowAll = PT == 8 && M >= 64 && M <= 512;
+
 // Item k of a thread: pair p and column j, consecutive lanes on consecutive pairs.
 template <class G>
 __device__ __forceinline__ bool row_item(int k, int& p, int& j) {
@@ -677,8 +684,8 @@ constexpr int kSquareMaxM = 128;
 // (u_a^2) + i (u_b^2) in physical space and one forward transform (the factor i q_j / 2 is
 // row_split's). Both fields are band-limited, so (u^2)_x of the band equals the band of 2 u u_x
 // exactly; one transform of three is saved.
-template <int M, int PT, bool XLOW>
-__device__ __forceinline__ void row_square(cd* va, cd* ex, const TwCache<M, PT>& twc, const FftPos<M, PT, XLOW>& pos) {
+template <int M, int PT, bool XLOW, bool ALL>
+__device__ __forceinline__ void row_square(cd* va, cd* ex, const TwCache<M, PT, ALL>& twc, const FftPos<M, PT, XLOW>& pos) {
     fft_inv<M, PT, XLOW>(va, ex, twc, pos);
 #pragma unroll
     for (int m = 0; m < PT; ++m) va[m] = cd{va[m].x * va[m].x, va[m].y * va[m].y};
@@ -690,8 +697,8 @@ __device__ __forceinline__ void row_square(cd* va, cd* ex, const TwCache<M, PT>&
 // values of one scale; packing f and g of one row together would let the round-off of the
 // larger (r_x can exceed u by q_max^5) swamp the smaller. Then one forward transform of
 // (f_a g_a) + i (f_b g_b).
-template <int M, int PT, bool XLOW>
-__device__ __forceinline__ void row_product(cd* va, cd* vb, cd* ex, const TwCache<M, PT>& twc,
+template <int M, int PT, bool XLOW, bool ALL>
+__device__ __forceinline__ void row_product(cd* va, cd* vb, cd* ex, const TwCache<M, PT, ALL>& twc,
                                             const FftPos<M, PT, XLOW>& pos) {
     fft_inv<M, PT, XLOW>(va, ex, twc, pos);
     fft_inv<M, PT, XLOW>(vb, ex, twc, pos);
@@ -717,9 +724,9 @@ __device__ __forceinline__ void row_dx(const cd* va, int t, double dq, cd* vb) {
 // them. Each wavefront's regions are its own until the barrier, so its exchanges reuse them.
 // DX: the square form of u u_x (one field); otherwise the product of two fields, or of one field
 // and its x-derivative.
-template <int M, int PT, int FIELDS, int WR, bool DX>
+template <int M, int PT, int FIELDS, int WR, bool DX, bool ALL>
 __device__ __forceinline__ void row_transforms(const Shape& sh, cd* lds, const FftPos<M, PT>& pos,
-                                               const TwCache<M, PT>& twc, cd* va, cd* vb) {
+                                               const TwCache<M, PT, ALL>& twc, cd* va, cd* vb) {
     using G = RowG<M, PT>;
     // the exchange addresses a wavefront's transforms as x * XS from the block's start: shift
     // the base so that they fall into the wavefront's own region
@@ -747,7 +754,7 @@ __device__ __forceinline__ void row_pass_B(const Shape& sh, int block, const Wor
     constexpr bool DX = M <= kSquareMaxM;
     const size_t nrows = (size_t)sh.nloops * sh.N;
     const FftPos<M, PT> pos(threadIdx.x);
-    TwCache<M, PT> twc;
+    TwCache<M, PT, kRowAll<M, PT>> twc;
     tw_cache_load<M, PT>(twc, pos, tw);
     auto sub = [&](size_t g0) {
         const cd* const src[1] = {w.A};
@@ -833,7 +840,7 @@ __device__ __forceinline__ void row_pass_D(const Shape& sh, int block, const Wor
     };
     constexpr int WR = G::wave_region(2);
     const FftPos<M, PT> pos(threadIdx.x);
-    TwCache<M, PT> twc;
+    TwCache<M, PT, kRowAll<M, PT>> twc;
     tw_cache_load<M, PT>(twc, pos, tw);
     auto sub = [&](size_t g0, bool first) {
         const cd* const src[2] = {w.A, w.Cb};

@@ -25,7 +25,7 @@
 // has just the threads that one round of every pass needs (64 to 512), and wavefronts that have
 // no rows or no columns skip that pass's transforms. With the state in LDS, u transformed twice,
 // every pass loading its twiddles and blocks of 256 threads for every shape, a step of one 32 x 32
-// loop took 6.6 us (now 5.2), of 256 loops of 64 x 64 10.1 (8.3), of one 64 x 128 loop 25 (12.6; the
+// loop took 6.6 us (now 4.6), of 256 loops of 64 x 64 12.2 (7.4), of one 64 x 128 loop 25 (12.9; the
 // per-pass form 19).
 #pragma once
 
@@ -69,6 +69,14 @@ struct ResG {
     static constexpr size_t BYTES = bytes(EX);
     static constexpr bool FITS = BYTES <= 160 * 1024 && N <= 512 && M <= 128 && NEED <= 512 &&
                                  (!SPLIT || PAIRS * R::TPF == NT);  // every wavefront reaches its barriers
+    // Twiddle powers kept in registers (TwCache) where they fit: 16 registers for each stage that
+    // has twiddles. Kept for rows and columns, for one of them, or (SPLIT 64 x 128) for neither;
+    // a step forms 4 or 8 products less per transform (a step of one 32 x 32 loop 4.93 -> 4.61 us,
+    // of 256 of 64 x 64 7.7 -> 7.4; 64 x 128, where they spill, would go from 12.9 to 14.1).
+    static constexpr int TW_M = 16 * (RF::L - (RF::F == 1)), TW_N = 16 * (CF::L - (CF::F == 1));
+    static constexpr bool TW_BOTH = NT <= 128 || TW_M + TW_N <= 32;
+    static constexpr bool TW_ROWS = TW_BOTH || (TW_M == 16 && !SPLIT);
+    static constexpr bool TW_COLS = TW_BOTH || (TW_M == 32 && TW_N == 16);
     // Wavefronts per SIMD the kernel is compiled for: two (at most 256 registers each), so that
     // blocks of small loops share a CU, except where LDS holds one block of four wavefronts.
     static constexpr int WPE = NT == 256 && BYTES > 80 * 1024 ? 1 : 2;
@@ -139,8 +147,8 @@ __device__ __forceinline__ void resident_loop(double L, const cd* src, cd* dst, 
     cd* const exD = alt ? A - R::rx(4) : EX;
     cd* const exC = alt ? A - R::cx(4) : EX;
     cd* const exE = alt ? X - R::cx(4) : EX;
-    TwCache<M, PT> twr;
-    TwCache<N, PT> twc;
+    TwCache<M, PT, R::TW_ROWS> twr;
+    TwCache<N, PT, R::TW_COLS> twc;
     tw_cache_load<M, PT>(twr, pr, tw);
     tw_cache_load<N, PT>(twc, pc, tw);
     const ColCoef f(col_on ? j : 0, L);

@@ -349,7 +349,7 @@ __device__ __forceinline__ void xi_row_pass_B(const Shape& sh, int block, const 
     const size_t nrows = (size_t)sh.nloops * sh.N;
     const size_t g0 = (size_t)block * G::ROWS;
     const FftPos<M, G::PT> pos(threadIdx.x);
-    TwCache<M, G::PT> twc;
+    TwCache<M, G::PT, kRowAll<M>> twc;
     tw_cache_load<M, G::PT>(twc, pos, tw);
     const double* const src[1] = {w.A};
     XiRowLoad<G, 1> ld;
@@ -372,7 +372,7 @@ __device__ __forceinline__ void xi_row_pass_D(const Shape& sh, int block, const 
     const size_t nrows = (size_t)sh.nloops * sh.N;
     const size_t g0 = (size_t)block * G::ROWS;
     const FftPos<M, G::PT> pos(threadIdx.x);
-    TwCache<M, G::PT> twc;
+    TwCache<M, G::PT, kRowAll<M>> twc;
     tw_cache_load<M, G::PT>(twc, pos, tw);
     const double* const src[2] = {w.A, w.Cb};
     XiRowLoad<G, 2> ld;
