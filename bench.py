@@ -181,9 +181,9 @@ def main():
         return bench_orbits(args, E=args.runs, per_run=args.per_run)
     if args.workload.startswith("ks-dns"):
         return bench_dns(args)
-    if nl == 1 and api.step_form(specs[0].Nx, specs[0].Ns, 1) == "resident":
+    if nl == 1 and args.workload != "plain-64x128" and api.step_form(specs[0].Nx, specs[0].Ns, 1) == "resident":
         return bench_resident(args, cfg, specs[0], steps, dtau, scheme)
-    if nl == 1:
+    if nl == 1:  # with the log of J(tau) and T(tau) that plain-64x128 asks for
         return bench_plain(args, cfg, specs[0], steps, dtau, scheme)
     if args.workload.startswith("autograd"):
         return bench_autograd(args, cfg, specs, steps, dtau, scheme)
@@ -419,7 +419,7 @@ def bench_resident(args, cfg, spec, steps, dtau, scheme):
 
 
 def bench_plain(args, cfg, spec, steps, dtau, scheme, every=10):
-    """One loop through loop_step in the per-pass form: K steps in one call (the timed region),
+    """One loop through loop_step, in whichever form it takes: K steps in one call (the timed region),
     then the log the workload asks for, J(tau) and T(tau) every `every` steps, from a run of the
     same steps in calls of `every` steps. Each call first makes the state canonical (column 0
     exactly Hermitian), which the steps inside one call keep only to rounding, so the two runs
@@ -465,11 +465,27 @@ def bench_plain(args, cfg, spec, steps, dtau, scheme, every=10):
           f"k_colC<{spec.Ns}, 3>": pass_bytes([(spec.Nx, spec.Ns)], 2),
           f"k_rowD<{spec.Nx}>": pass_bytes([(spec.Nx, spec.Ns)], 3),
           f"k_colE<{spec.Ns}, 3>": pass_bytes([(spec.Nx, spec.Ns)], 4)}
-    kern = {k: v for k, v in tr.kernels.items() if k in kb}
-    dom = max(kern, key=lambda k: kern[k]["total_us"])
-    achieved = kb[dom] / (kern[dom]["avg_us"] * 1e-6) / 1e9
     gpu_s = e0.elapsed_time(e1) * 1e-3
     pts = spec.Nx * spec.Ns
+    kernels_us = {k: round(v["avg_us"], 2) for k, v in tr.kernels.items()}
+    resident = api.step_form(spec.Nx, spec.Ns, 1) == "resident"
+    if resident:
+        # one block on one CU, every step of a call in one launch: FP64 arithmetic and LDS latency
+        fl = step_flops(spec.Nx, spec.Ns)
+        achieved = fl * steps / gpu_s / 1e12
+        roofline = {"bound": "alu", "achieved": round(achieved, 4), "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
+                    "frac": round(achieved / FP64_PEAK_TFLOPS, 6), "traffic": None,
+                    "kernel": f"k_resident<{spec.Nx}, {spec.Ns}>", "flops_per_step": fl, "cus_used": 1,
+                    "frac_of_cus_used": round(achieved / (FP64_PEAK_TFLOPS / CUS), 4), "kernels_us": kernels_us}
+    else:
+        # one loop spreads a pass over a few blocks: latency-bound, far from the HBM roofline
+        kern = {k: v for k, v in tr.kernels.items() if k in kb}
+        dom = max(kern, key=lambda k: kern[k]["total_us"])
+        achieved = kb[dom] / (kern[dom]["avg_us"] * 1e-6) / 1e9
+        roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                    "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": None, "kernel": dom,
+                    "bytes_per_launch": kb[dom], "avg_launch_us": round(kern[dom]["avg_us"], 2),
+                    "kernels_us": kernels_us}
     cpu = None if args.no_cpu else cpu_baseline([spec], dtau, scheme)
     out = {
         "metric": METRIC,
@@ -477,13 +493,11 @@ def bench_plain(args, cfg, spec, steps, dtau, scheme, every=10):
         "ms_per_step": wall / steps * 1e3, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f64", "data": "synthetic",
         "config": {"workload": args.workload, "loops": 1, "shapes": [[spec.Nx, spec.Ns]], "L": spec.L,
-                   "scheme": cfg["scheme"], "dtau": dtau, "form": "per-pass (loop_step)", "parallelism": "none (1 GPU)"},
+                   "scheme": cfg["scheme"], "dtau": dtau,
+                   "form": "resident (loop_step)" if resident else "per-pass (loop_step)",
+                   "parallelism": "none (1 GPU)"},
         "gpu_ms_per_step": gpu_s / steps * 1e3,
-        # one loop spreads a pass over a few blocks: latency-bound, far from the HBM roofline
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": None, "kernel": dom,
-                     "bytes_per_launch": kb[dom], "avg_launch_us": round(kern[dom]["avg_us"], 2),
-                     "kernels_us": {k: round(v["avg_us"], 2) for k, v in tr.kernels.items()}},
+        "roofline": roofline,
         "cpu_baseline": cpu,
         "log_every": every,
         "logged_vs_timed_J_max_rel": dev_rel,
@@ -969,12 +983,11 @@ def bench_orbits(args, E=128, per_run=2, chunk=400_000, J_tol=5e-25):
 
 
 def dns_step_flops(Nx):
-    """FP64 flops of one ETDRK4 step of one run (direct transforms, K = (Nx-1)/3 modes): four
-    nonlinear evaluations, each an inverse sum over K modes at Nx points and a forward sum over
-    Nx points for K + 1 modes (4 flops per complex-by-real term), plus the stage combinations
-    (about 40 flops per mode)."""
+    """FP64 flops of one ETDRK4 step of one run: four nonlinear evaluations, each an inverse and a
+    forward transform of Nx points (5 n log2 n each) and Nx squares, plus the stage combinations
+    (about 40 flops per mode, K = (Nx-1)/3 modes)."""
     K = (Nx - 1) // 3
-    return 4 * (4 * Nx * K + 4 * Nx * (K + 1)) + 40 * (K + 1)
+    return 4 * (2 * 5 * Nx * (Nx.bit_length() - 1) + Nx) + 40 * (K + 1)
 
 
 def bench_dns(args, E=4096, Nx=64, L=39.0, dt=0.05, every=2):

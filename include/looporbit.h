@@ -290,7 +290,11 @@ int loop_update(double L, int Nx, int Ns, int nloops, double* T, double* uhat,
 typedef enum { LOOP_BATCH_PER_PASS = 0, LOOP_BATCH_PERSISTENT = 1, LOOP_BATCH_STREAMS = 2 } loop_batch_schedule;
 int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns, void** plan);
 /* Choose how loop_batch_step runs the steps (results are identical bit for bit):
- *   LOOP_BATCH_PER_PASS (default): one kernel per pass over every loop's tiles, four per step;
+ *   LOOP_BATCH_PER_PASS (default): one kernel per pass over every loop's tiles, four per step.
+ *   On this schedule and on LOOP_BATCH_STREAMS, loops that fit in LDS (loop_resident_supported)
+ *   run all their steps in the resident form, one block each, beside the kernels of the other
+ *   loops, on streams the plan owns; loop_set_resident(0) or a variant set by hand
+ *   (loop_batch_set_variant) turns that off;
  *   LOOP_BATCH_PERSISTENT: one launch for all steps. Each loop is assigned to one XCD, and
  *   blocks pull (pass, loop, tile) items of their own XCD's list in dependency order, so that
  *   every hand-over between blocks stays within one L2 (see the scheduler notes in the

@@ -724,7 +724,7 @@ __global__ void k_batch_reset(BatchQueue* q, int* done, int nloops) {
 // transform sizes its size dispatch contains. Registers are allocated for the largest body
 // a kernel holds, so a kernel limited to short transforms can keep more wavefronts per SIMD.
 // For the row passes a variant also fixes how a tile of rows reaches LDS: staged through
-// vector registers (load_rows) or copied by the load unit (load_rows_lds). Every variant
+// vector registers (RowLoad) or copied by the load unit (load_rows_lds). Every variant
 // runs the same arithmetic; a plan starts with the narrowest staged variant that covers its
 // sizes, and loop_batch_autotune times the others.
 struct RagVariant {
@@ -1390,6 +1390,10 @@ int resident_threads(int Nx, int Ns) {
     return t;
 }
 
+// loop_step takes the resident form for every shape that has it, whatever the number of loops: it
+// measured faster everywhere (us per step, resident / per-pass: one loop of 32 x 32 4.9 / 16.6, of
+// 64 x 128 12.6 / 20.4; 2048 loops of 8 x 8 4.6 / 60, of 32 x 32 16.8 / 44.1, of 64 x 64 59 / 100, of
+// 32 x 256 92 / 181, of 64 x 128 103 / 180, of 128 x 64 96 / 182).
 bool resident_usable(int Nx, int Ns) {
     const size_t b = resident_bytes(Nx, Ns);
     return b > 0 && b <= (size_t)max_lds_per_block();

@@ -610,7 +610,7 @@ __device__ __forceinline__ void row_store(const cd* lds, cd* X, size_t g0, const
     }
 }
 
-// The same tiles as load_rows, copied by the load unit straight into LDS
+// The rows that RowLoad stages, as raw tiles copied by the load unit straight into LDS
 // (global_load_lds_dwordx4: lane i of a wavefront writes 16 bytes at the instruction's LDS
 // base + 16 i). One wavefront instruction moves 64 consecutive rows of one column j to
 // tile[j][r0 .. r0 + 63], so ROWS must be a multiple of 64. Nothing passes through vector
