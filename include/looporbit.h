@@ -299,7 +299,7 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
  *   blocks pull (pass, loop, tile) items of their own XCD's list in dependency order, so that
  *   every hand-over between blocks stays within one L2 (see the scheduler notes in the
  *   source). loop_batch_create finds the XCDs with a probe launch; a block on an XCD the
- *   probe did not see leaves and sets LOOP_ENOTSUP. It measured 1.5-2.5x slower than the
+ *   probe did not see leaves and sets LOOP_ENOTSUP. It measured 1.7-3.4x slower than the
  *   other two, and
  *   loop_batch_autotune does not choose it;
  *   LOOP_BATCH_STREAMS: the loops split into K groups of about equal work (K from
