@@ -256,7 +256,7 @@ int loop_converge(double L, int Nx, int Ns, int nloops, double* T, double* uhat,
  * multiple of the row-tile height).
  * loop_set_resident(mode) sets the choice for later calls in this process: 0 per-pass always,
  * 1 (default) resident where it was measured faster, 2 resident wherever it exists (it measures
- * faster wherever it exists, so 1 and 2 choose alike).
+ * faster wherever it exists, so 1 and 2 choose alike in loop_step; in loop_batch_step they differ).
  * It returns the previous mode, or LOOP_EINVAL for other values.
  * loop_resident_supported returns 1 when the resident form exists for an Nx x Ns loop on the
  * current device, else 0. loop_step_form returns the form loop_step takes for nloops loops of
@@ -293,8 +293,8 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
  *   LOOP_BATCH_PER_PASS (default): one kernel per pass over every loop's tiles, four per step.
  *   On this schedule and on LOOP_BATCH_STREAMS, loops that fit in LDS (loop_resident_supported)
  *   run all their steps in the resident form, one block each, beside the kernels of the other
- *   loops, on streams the plan owns; loop_set_resident(0) or a variant set by hand
- *   (loop_batch_set_variant) turns that off;
+ *   loops, on streams the plan owns, where that was measured faster (mode 1 of
+ *   loop_set_resident), always (2) or never (0, or a variant set by hand);
  *   LOOP_BATCH_PERSISTENT: one launch for all steps. Each loop is assigned to one XCD, and
  *   blocks pull (pass, loop, tile) items of their own XCD's list in dependency order, so that
  *   every hand-over between blocks stays within one L2 (see the scheduler notes in the

@@ -1452,6 +1452,7 @@ struct BatchPlan {
     size_t res_lds[4] = {0, 0, 0, 0};
     int* d_rest = nullptr;  // the other loops
     int nrest = 0;
+    double res_mb = 0.0;  // MB that a per-pass step of the resident loops moves, 16 (9W + 4S) each
     int rest_off[3] = {0, 0, 0}, rest_group_off[3][4][3] = {};  // their tile lists
     bool chosen = false;    // a variant was set by hand: every loop then takes the per-pass kernels
     mutable std::mutex mu;  // held while a call queues work on the plan's streams and events
@@ -2264,6 +2265,7 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
             if (!resident_usable(b.sh.M, b.sh.N) || resident_threads(b.sh.M, b.sh.N) != 64 << c) continue;
             is_res[l] = 1;
             res.push_back(ResDesc{b.uoff, b.sh.L, l, b.sh.M, b.sh.N, 0});
+            p->res_mb += 16e-6 * b.sh.C * (9.0 * b.sh.N + 4.0 * b.sh.NB);
             p->res_lds[c] = std::max(p->res_lds[c], resident_bytes(b.sh.M, b.sh.N));
         }
     }
@@ -2529,6 +2531,26 @@ int convert_batch(const BatchPlan* p, bool to_band, const int* ids, int n, cd* p
     return last_error();
 }
 
+// Whether a call's resident loops run beside the rest (mode 1; mode 2 takes them always). Their
+// launches, forks and joins cost a call 40 to 70 us of host time, however short it is, and the
+// rest's launches, 4 K per step on K streams, bound small batches on the host whether those loops
+// are among them or not; what is gained is the memory and CU time of the loops taken out. Measured,
+// us per call without and with them (5 or 10 steps, MB per step of the resident loops in brackets):
+// one stream [14.7] 309 / 333, [29.6] 221 / 211, [55] 301 / 290; two [29.6] 379 / 382, [54] 516 / 504;
+// three [29.6] 439 / 466, [54] 507 / 484 (5 steps 295 / 308). With no other loops a call of several
+// block sizes takes 72 us more than its steps, against 20 per step on one stream and more on several;
+// one block size needs neither fork nor join.
+bool resident_pays(const BatchPlan* p, int nsteps, int mode) {
+    if (mode != 1) return mode == 2;
+    const int K = p->schedule == LOOP_BATCH_STREAMS ? p->nstreams : 1;
+    if (p->nrest == 0) {
+        int classes = 0;
+        for (int c = 0; c < 4; ++c) classes += p->res_off[c + 1] > p->res_off[c];
+        return classes == 1 || nsteps >= (K == 1 ? 4 : 2);
+    }
+    return p->res_mb >= 8.0 + 12.0 * K && p->res_mb * nsteps >= 25.0 + 125.0 * K;
+}
+
 // The resident loops take the plan's streams that the schedule leaves free, forked from the
 // caller's stream before anything else and joined back after the rest's last pass. The long
 // resident launches are queued first: each occupies the CUs of its loops from the start, and
@@ -2618,7 +2640,7 @@ int loop_batch_step(const void* plan, double* T, double* uhat_pool, double dtau,
     char* base = static_cast<char*>(ws);
     // the same arithmetic as row variants 0 to 2, so the same bits; variant 3 pairs rows differently
     if (nsteps > 0 && p->res_off[4] > 0 && p->schedule != LOOP_BATCH_PERSISTENT && !p->chosen &&
-        p->variant[PASS_B] < 3 && p->variant[PASS_D] < 3 && g_resident.load() != 0)
+        p->variant[PASS_B] < 3 && p->variant[PASS_D] < 3 && resident_pays(p, nsteps, g_resident.load()))
         return step_with_resident(p, reinterpret_cast<cd*>(uhat_pool), nsteps,
                                   batch_args(p, base, T, J_hist, nsteps, dtau, scheme, tw), hs);
     if ((st = loop_batch_load(plan, uhat_pool, ws, ws_bytes, stream))) return st;

@@ -1,6 +1,7 @@
 """Batches whose small loops take the resident form inside loop_batch_step: only small loops
 (every block size), only large ones, and both, on the per-pass and the streams schedules, equal
-the steps with the resident form off bit for bit; recorded into a HIP graph, replayed between
+the steps with the resident form off bit for bit, with the form taken always and where it pays
+(calls on both sides of each line of that rule); recorded into a HIP graph, replayed between
 eager work, too; and two threads stepping one plan with work spaces of their own."""
 import threading
 
@@ -50,13 +51,42 @@ def test_equals_the_per_pass_kernels(api, mix):
         api.set_resident(prev)
     for schedule, k in ((b.PER_PASS, None), (b.STREAMS, 2), (b.STREAMS, 3), (b.STREAMS, 4)):
         b.set_schedule(schedule, k)
-        for nsteps in (3, 3):
-            assert all(torch.equal(x, y) for x, y in zip(step(api, b, pool, T, nsteps), ref)), (mix, schedule, k)
+        for mode in (api.RESIDENT_ALWAYS, api.RESIDENT_AUTO, api.RESIDENT_ALWAYS):
+            prev = api.set_resident(mode)
+            try:
+                out = step(api, b, pool, T)
+            finally:
+                api.set_resident(prev)
+            assert all(torch.equal(x, y) for x, y in zip(out, ref)), (mix, schedule, k, mode)
     assert b.status() == 0
 
 
+@pytest.mark.parametrize("streams", [0, 2, 3, 4])
+@pytest.mark.parametrize("mix,nsteps", [("small", 1), ("small", 2), ("small", 3), ("small", 4), ("many", 2), ("many", 4),
+                                        ("many", 10)])
+def test_where_it_pays(api, mix, nsteps, streams):
+    """Short and long calls, few loops and enough of them (47 MB per step) to be taken out."""
+    b, pool, T = batch(api, {"many": [(64, 128)] * 60 + [(32, 128)] * 60 + [(64, 256)]}.get(mix, MIXES.get(mix)))
+    if streams:
+        b.set_schedule(b.STREAMS, streams)
+    got = step(api, b, pool, T, nsteps)
+    prev = api.set_resident(api.RESIDENT_NEVER)
+    try:
+        ref = step(api, b, pool, T, nsteps)
+    finally:
+        api.set_resident(prev)
+    assert all(torch.equal(x, y) for x, y in zip(got, ref))
+
+
+@pytest.fixture
+def always(api):
+    prev = api.set_resident(api.RESIDENT_ALWAYS)
+    yield
+    api.set_resident(prev)
+
+
 @pytest.mark.parametrize("mix", ["small", "both"])
-def test_graph_replays(api, mix):
+def test_graph_replays(api, always, mix):
     b, pool, T = batch(api, MIXES[mix])
     b.set_schedule(b.STREAMS, 2)
     pg, Tg = pool.clone(), T.clone()
@@ -73,7 +103,7 @@ def test_graph_replays(api, mix):
         assert torch.equal(pg, pe) and torch.equal(Tg, Te)
 
 
-def test_two_threads_step_one_plan(api):
+def test_two_threads_step_one_plan(api, always):
     """The per-pass schedule, a work space and a stream for each thread."""
     import ctypes
 
