@@ -2465,8 +2465,30 @@ void launch_pass(const BatchPlan* p, int pass, int step, const BatchArgs& a, hip
     launch_list(p, p->tile_off, pass, step, a, hs, true);
 }
 
+// The plan's streams that a call has taken behind its own stream hs (behind the last record of
+// ev_fork). However the call ends, their work has to come before the caller's next work on hs: the
+// call leaves through join(), with its status so far, also when it fails half way. The caller
+// holds p->mu.
+struct Fork {
+    const BatchPlan* p;
+    hipStream_t hs;
+    bool on[3] = {false, false, false};
+    bool take(int k) { return on[k] || (on[k] = hipStreamWaitEvent(p->sx[k], p->ev_fork, 0) == hipSuccess); }
+    int join(int st) {
+        for (int k = 0; k < 3; ++k) {
+            if (!on[k]) continue;
+            if (hipEventRecord(p->ev_join[k], p->sx[k]) == hipSuccess &&
+                hipStreamWaitEvent(hs, p->ev_join[k], 0) == hipSuccess)
+                continue;
+            hipStreamSynchronize(p->sx[k]);  // no order on the device: the host waits
+            if (!st) st = LOOP_EHIP;
+        }
+        return st;
+    }
+};
+
 // Multi-stream schedule: group 0 on the caller's stream, group g > 0 on the plan's stream
-// sx[g - 1], each group started one pass after the previous one (after its first pass B), so
+// sx[g - 1], each started once the group before it has queued its first two passes, so
 // that the GPU runs different passes of different groups side by side, each as its own
 // kernel with its own registers and LDS. Events fork the plan's streams from the caller's and
 // join them back before the caller's next work. Returns LOOP_EHIP if an event could not be
@@ -2474,26 +2496,21 @@ void launch_pass(const BatchPlan* p, int pass, int step, const BatchArgs& a, hip
 // the K groups. The caller holds p->mu.
 int launch_streams(const BatchPlan* p, int K, const int (*off)[3], int nsteps, const BatchArgs& a, hipStream_t hs) {
     auto st = [&](int g) { return g == 0 ? hs : p->sx[g - 1]; };
+    Fork f{p, hs};
     bool ok = hipEventRecord(p->ev_fork, hs) == hipSuccess;
-    for (int g = 1; g < K; ++g) ok = ok && hipStreamWaitEvent(st(g), p->ev_fork, 0) == hipSuccess;
-    if (!ok) return LOOP_EHIP;
-    for (int g = 0; g < K; ++g) {
-        if (g > 0 && hipStreamWaitEvent(st(g), p->ev_lag[g - 1], 0) != hipSuccess) return LOOP_EHIP;
+    for (int g = 1; g < K; ++g) ok = ok && f.take(g - 1);
+    for (int g = 0; g < K && ok; ++g) {
+        if (g > 0 && hipStreamWaitEvent(st(g), p->ev_lag[g - 1], 0) != hipSuccess) return f.join(LOOP_EHIP);
         launch_list(p, off[g], PASS_A, 0, a, st(g));
         launch_list(p, off[g], PASS_B, 0, a, st(g));
-        if (g + 1 < K && hipEventRecord(p->ev_lag[g], st(g)) != hipSuccess) return LOOP_EHIP;
+        ok = g + 1 == K || hipEventRecord(p->ev_lag[g], st(g)) == hipSuccess;
     }
     // queue the groups' launches in turn, one pass each
-    for (int i = 0; i < nsteps; ++i)
+    for (int i = 0; i < nsteps && ok; ++i)
         for (int pass = PASS_B; pass <= PASS_E; ++pass)
             for (int g = 0; g < K; ++g)
                 if (!(i == 0 && pass == PASS_B)) launch_list(p, off[g], pass, i, a, st(g));
-    for (int g = 1; g < K; ++g) {
-        if (hipEventRecord(p->ev_join[g - 1], st(g)) != hipSuccess ||
-            hipStreamWaitEvent(hs, p->ev_join[g - 1], 0) != hipSuccess)
-            return LOOP_EHIP;
-    }
-    return LOOP_OK;
+    return f.join(ok ? LOOP_OK : LOOP_EHIP);
 }
 
 // The resident loops of block size 64 << c, all steps, on stream st.
@@ -2551,6 +2568,20 @@ bool resident_pays(const BatchPlan* p, int nsteps, int mode) {
     return p->res_mb >= 8.0 + 12.0 * K && p->res_mb * nsteps >= 25.0 + 125.0 * K;
 }
 
+// The per-pass kernels of the loops that do not take the resident form, on K streams.
+int step_rest(const BatchPlan* p, int K, cd* pool, int nsteps, const BatchArgs& a, hipStream_t hs) {
+    int st = convert_batch(p, true, p->d_rest, p->nrest, pool, a.ws, hs);
+    if (st) return st;
+    if (K > 1) {
+        if ((st = launch_streams(p, K, p->rest_group_off[K - 2], nsteps, a, hs))) return st;
+    } else {
+        launch_list(p, p->rest_off, PASS_A, 0, a, hs);
+        for (int i = 0; i < nsteps; ++i)
+            for (int pass = PASS_B; pass <= PASS_E; ++pass) launch_list(p, p->rest_off, pass, i, a, hs);
+    }
+    return convert_batch(p, false, p->d_rest, p->nrest, pool, a.ws, hs);
+}
+
 // The resident loops take the plan's streams that the schedule leaves free, forked from the
 // caller's stream before anything else and joined back after the rest's last pass. The long
 // resident launches are queued first: each occupies the CUs of its loops from the start, and
@@ -2559,37 +2590,23 @@ int step_with_resident(const BatchPlan* p, cd* pool, int nsteps, const BatchArgs
     std::lock_guard<std::mutex> lk(p->mu);
     const int K = p->schedule == LOOP_BATCH_STREAMS ? std::min(p->nstreams, 3) : 1;
     const ResArgs r{nullptr, pool, a.T, a.J_hist, a.status, a.tw, a.dtau, a.scheme, a.nsteps, a.nloops};
-    int st, last = -1, next = 2;  // classes from the largest blocks down, on sx[2], sx[1], .. sx[K - 1], then again
-    bool used[3] = {false, false, false};
-    if (hipEventRecord(p->ev_fork, hs) != hipSuccess) return LOOP_EHIP;
-    for (int c = 3; c >= 0; --c) {
+    Fork f{p, hs};
+    int st = hipEventRecord(p->ev_fork, hs) == hipSuccess ? LOOP_OK : LOOP_EHIP;
+    int last = -1, next = 2;  // classes from the largest blocks down, on sx[2], sx[1], .. sx[K - 1], then again
+    for (int c = 3; c >= 0 && !st; --c) {
         if (p->res_off[c + 1] == p->res_off[c]) continue;
         if (p->nrest == 0 && last < 0) {  // nothing else on the caller's stream
             last = c;
             continue;
         }
-        if (!used[next] && hipStreamWaitEvent(p->sx[next], p->ev_fork, 0) != hipSuccess) return LOOP_EHIP;
-        used[next] = true;
-        if ((st = launch_resident_class(p, c, r, p->sx[next]))) return st;
+        st = f.take(next) ? launch_resident_class(p, c, r, p->sx[next]) : LOOP_EHIP;
         next = next > K - 1 ? next - 1 : 2;
     }
-    if (last >= 0 && (st = launch_resident_class(p, last, r, hs))) return st;
-    if (p->nrest > 0) {
-        if ((st = convert_batch(p, true, p->d_rest, p->nrest, pool, a.ws, hs))) return st;
-        if (K > 1) {
-            if ((st = launch_streams(p, K, p->rest_group_off[K - 2], nsteps, a, hs))) return st;
-        } else {
-            launch_list(p, p->rest_off, PASS_A, 0, a, hs);
-            for (int i = 0; i < nsteps; ++i)
-                for (int pass = PASS_B; pass <= PASS_E; ++pass) launch_list(p, p->rest_off, pass, i, a, hs);
-        }
-        if ((st = convert_batch(p, false, p->d_rest, p->nrest, pool, a.ws, hs))) return st;
-    }
-    for (int k = 0; k < 3; ++k)
-        if (used[k] && (hipEventRecord(p->ev_join[k], p->sx[k]) != hipSuccess ||
-                        hipStreamWaitEvent(hs, p->ev_join[k], 0) != hipSuccess))
-            return LOOP_EHIP;
-    return last_error();
+    if (!st && last >= 0) st = launch_resident_class(p, last, r, hs);
+    if (!st && p->nrest > 0) st = step_rest(p, K, pool, nsteps, a, hs);
+    st = f.join(st);
+    const int err = last_error();
+    return st ? st : err;
 }
 }  // namespace
 

@@ -1,0 +1,103 @@
+"""What the library's host code asks of the HIP runtime, on a runtime that records the calls and
+runs nothing (hip_recorder.cpp): which launches go where, in what order streams and events put
+them, and what is left behind when a call fails half way. Each test runs in a process of its own."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, importlib.util, os
+R = ctypes.CDLL({rec!r}, mode=ctypes.RTLD_GLOBAL)
+spec = importlib.util.spec_from_file_location("_lib", {lib!r})
+_lib = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(_lib)
+L = _lib.lib()
+P, D, I = ctypes.c_void_p, ctypes.c_double, ctypes.c_int
+R.rec_log.argtypes, R.rec_log.restype = [ctypes.c_char_p, ctypes.c_long], ctypes.c_long
+R.rec_unordered.argtypes, R.rec_unordered.restype = [P], ctypes.c_long
+R.rec_capture.argtypes = [P, ctypes.c_ulonglong]
+R.rec_end_capture.argtypes = [ctypes.c_ulonglong]
+R.rec_fail.argtypes = [ctypes.c_char_p, I]
+R.rec_cost.argtypes = [ctypes.c_char_p, D]
+HS, HS2 = 0x10, 0x20  # the caller's streams
+
+def log():
+    buf = ctypes.create_string_buffer(R.rec_log(None, 0))
+    R.rec_log(buf, len(buf))
+    return buf.value.decode().splitlines()
+
+class Plan:
+    def __init__(self, shapes):
+        n = len(shapes)
+        self.n, self.h = n, P()
+        st = L.loop_batch_create(n, (D * n)(*[22.0] * n), (I * n)(*[m for m, _ in shapes]),
+                                 (I * n)(*[s for _, s in shapes]), ctypes.byref(self.h))
+        assert st == 0, st
+        ws, pe = ctypes.c_size_t(), ctypes.c_size_t()
+        L.loop_batch_info(self.h, ctypes.byref(ws), ctypes.byref(pe), None)
+        self.ws_bytes, self.pool_elems = ws.value, pe.value
+    def mem(self, size):  # an address with the alignment the calls ask for; kernels do not run
+        self.keep = getattr(self, "keep", []) + [ctypes.create_string_buffer(size + 512)]
+        return (ctypes.addressof(self.keep[-1]) + 255) // 256 * 256
+    def step(self, nsteps=2, hs=HS):
+        if not hasattr(self, "T"):
+            self.T, self.pool, self.ws = self.mem(8 * self.n), self.mem(16 * self.pool_elems), self.mem(64)
+        return L.loop_batch_step(self.h, self.T, self.pool, 1e-4, 1, nsteps, None, self.ws, self.ws_bytes, hs)
+
+MIXED = [(32, 32), (64, 64), (64, 128), (32, 512), (64, 256)]  # three resident block sizes and two other loops
+SMALL = MIXED[:3]
+"""
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("rec") / "hip_recorder.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(HERE, "hip_recorder.cpp"), "-o", so], check=True)
+    return so
+
+
+@pytest.fixture
+def run(recorder):
+    def go(body):
+        lib = os.path.join(ROOT, "paper_2007_06427_amd", "_lib.py")
+        code = PRELUDE.format(rec=recorder, lib=lib) + textwrap.dedent(body)
+        r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+    return go
+
+
+
+@pytest.mark.parametrize("streams", [0, 2, 3, 4])
+@pytest.mark.parametrize("shapes", ["MIXED", "SMALL"])
+def test_a_failed_step_leaves_nothing_unordered(run, shapes, streams):
+    """Whichever HIP call of a step fails, and whichever time it is made: the step says so or has
+    completed, and what it had queued on the plan's streams comes before the caller's next work."""
+    run(f"""
+    L.loop_set_resident(2)
+    p = Plan({shapes})
+    if {streams}:
+        assert L.loop_batch_set_schedule(p.h, 2) == 0 and L.loop_batch_set_streams(p.h, {streams}) == 0
+    assert p.step() == 0  # the first call also sets up the kernels
+    R.rec_reset()
+    assert p.step() == 0
+    assert R.rec_unordered(HS) == 0
+    calls = log()
+    assert any("k_resident_batch" in c for c in calls)
+    for i, c in enumerate(calls):
+        nth = sum(c in d for d in calls[:i + 1])
+        R.rec_reset()
+        R.rec_fail(c.encode(), nth)
+        st = p.step()
+        assert st == _lib.LOOP_EHIP, (c, nth, st)
+        assert R.rec_unordered(HS) == 0, (c, nth, log())
+    R.rec_reset()
+    assert p.step() == 0
+    assert [c for c in log() if "launch" in c] == [c for c in calls if "launch" in c]
+    """)
