@@ -307,8 +307,11 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
  *   the plan owns (default priority), each started one pass after the previous group, so that
  *   different passes of different groups run side by side as separate kernels. The plan's
  *   streams are forked from and joined back to `stream` with events, so the call stays
- *   ordered on `stream` and can be captured in a graph from it. Calls with one plan must not
- *   overlap (the plan's streams and events are shared). */
+ *   ordered on `stream` and can be captured in a graph from it.
+ * Calls with one plan may come from several threads and streams, each with a work space of its
+ * own; on the plan's streams they run one after the other. A capture keeps the plan's streams that
+ * a recorded call took until it ends: other calls then run on their own stream alone, in the
+ * per-pass kernels, with the same results. */
 int loop_batch_set_schedule(void* plan, int schedule);
 int loop_batch_set_streams(void* plan, int nstreams);
 /* Bound, in seconds, of one dependency wait of the persistent schedule (default 2; 0 to 3600).

@@ -2465,6 +2465,29 @@ void launch_pass(const BatchPlan* p, int pass, int step, const BatchArgs& a, hip
     launch_list(p, p->tile_off, pass, step, a, hs, true);
 }
 
+// The stream capture that s is part of, 0 for none (the legacy stream is never captured).
+int capture_of(hipStream_t s, unsigned long long* id) {
+    *id = 0;
+    if (s == nullptr || s == hipStreamLegacy) return LOOP_OK;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    unsigned long long x = 0;
+    if (hipStreamGetCaptureInfo(s, &st, &x) != hipSuccess || st == hipStreamCaptureStatusInvalidated) return LOOP_EHIP;
+    if (st == hipStreamCaptureStatusActive) *id = x;
+    return LOOP_OK;
+}
+
+// Whether a call on hs can fork the plan's streams. Streams that a recorded call has forked stay
+// part of its capture until that ends: a call outside it, or inside another, can neither order
+// them behind its own stream nor launch on them, and runs on its own stream alone. The caller
+// holds p->mu.
+bool streams_free(const BatchPlan* p, hipStream_t hs) {
+    unsigned long long own, x;
+    if (capture_of(hs, &own)) return false;
+    for (hipStream_t s : p->sx)
+        if (capture_of(s, &x) || (x != 0 && x != own)) return false;
+    return true;
+}
+
 // The plan's streams that a call has taken behind its own stream hs (behind the last record of
 // ev_fork). However the call ends, their work has to come before the caller's next work on hs: the
 // call leaves through join(), with its status so far, also when it fails half way. The caller
@@ -2548,6 +2571,13 @@ int convert_batch(const BatchPlan* p, bool to_band, const int* ids, int n, cd* p
     return last_error();
 }
 
+// Block sizes among the resident loops.
+int res_classes(const BatchPlan* p) {
+    int n = 0;
+    for (int c = 0; c < 4; ++c) n += p->res_off[c + 1] > p->res_off[c];
+    return n;
+}
+
 // Whether a call's resident loops run beside the rest (mode 1; mode 2 takes them always). Their
 // launches, forks and joins cost a call 40 to 70 us of host time, however short it is, and the
 // rest's launches, 4 K per step on K streams, bound small batches on the host whether those loops
@@ -2560,11 +2590,7 @@ int convert_batch(const BatchPlan* p, bool to_band, const int* ids, int n, cd* p
 bool resident_pays(const BatchPlan* p, int nsteps, int mode) {
     if (mode != 1) return mode == 2;
     const int K = p->schedule == LOOP_BATCH_STREAMS ? p->nstreams : 1;
-    if (p->nrest == 0) {
-        int classes = 0;
-        for (int c = 0; c < 4; ++c) classes += p->res_off[c + 1] > p->res_off[c];
-        return classes == 1 || nsteps >= (K == 1 ? 4 : 2);
-    }
+    if (p->nrest == 0) return res_classes(p) == 1 || nsteps >= (K == 1 ? 4 : 2);
     return p->res_mb >= 8.0 + 12.0 * K && p->res_mb * nsteps >= 25.0 + 125.0 * K;
 }
 
@@ -2585,13 +2611,13 @@ int step_rest(const BatchPlan* p, int K, cd* pool, int nsteps, const BatchArgs& 
 // The resident loops take the plan's streams that the schedule leaves free, forked from the
 // caller's stream before anything else and joined back after the rest's last pass. The long
 // resident launches are queued first: each occupies the CUs of its loops from the start, and
-// the per-pass kernels of the rest share the others.
-int step_with_resident(const BatchPlan* p, cd* pool, int nsteps, const BatchArgs& a, hipStream_t hs) {
-    std::lock_guard<std::mutex> lk(p->mu);
+// the per-pass kernels of the rest share the others. forks: there is more than one launch to place;
+// the caller then holds p->mu and the plan's streams are free.
+int step_with_resident(const BatchPlan* p, cd* pool, int nsteps, bool forks, const BatchArgs& a, hipStream_t hs) {
     const int K = p->schedule == LOOP_BATCH_STREAMS ? std::min(p->nstreams, 3) : 1;
     const ResArgs r{nullptr, pool, a.T, a.J_hist, a.status, a.tw, a.dtau, a.scheme, a.nsteps, a.nloops};
     Fork f{p, hs};
-    int st = hipEventRecord(p->ev_fork, hs) == hipSuccess ? LOOP_OK : LOOP_EHIP;
+    int st = !forks || hipEventRecord(p->ev_fork, hs) == hipSuccess ? LOOP_OK : LOOP_EHIP;
     int last = -1, next = 2;  // classes from the largest blocks down, on sx[2], sx[1], .. sx[K - 1], then again
     for (int c = 3; c >= 0 && !st; --c) {
         if (p->res_off[c + 1] == p->res_off[c]) continue;
@@ -2656,9 +2682,17 @@ int loop_batch_step(const void* plan, double* T, double* uhat_pool, double dtau,
     hipStream_t hs = (hipStream_t)stream;
     char* base = static_cast<char*>(ws);
     // the same arithmetic as row variants 0 to 2, so the same bits; variant 3 pairs rows differently
-    if (nsteps > 0 && p->res_off[4] > 0 && p->schedule != LOOP_BATCH_PERSISTENT && !p->chosen &&
-        p->variant[PASS_B] < 3 && p->variant[PASS_D] < 3 && resident_pays(p, nsteps, g_resident.load()))
-        return step_with_resident(p, reinterpret_cast<cd*>(uhat_pool), nsteps,
+    const bool res = nsteps > 0 && p->res_off[4] > 0 && p->schedule != LOOP_BATCH_PERSISTENT && !p->chosen &&
+                     p->variant[PASS_B] < 3 && p->variant[PASS_D] < 3 && resident_pays(p, nsteps, g_resident.load());
+    const bool lone = res && p->nrest == 0 && res_classes(p) == 1;  // one launch, on the caller's stream
+    std::unique_lock<std::mutex> lk(p->mu, std::defer_lock);
+    bool forks = false;  // the call takes the plan's streams
+    if (nsteps > 0 && !lone && (res || p->schedule == LOOP_BATCH_STREAMS)) {
+        lk.lock();
+        forks = streams_free(p, hs);
+    }
+    if (lone || (res && forks))
+        return step_with_resident(p, reinterpret_cast<cd*>(uhat_pool), nsteps, forks,
                                   batch_args(p, base, T, J_hist, nsteps, dtau, scheme, tw), hs);
     if ((st = loop_batch_load(plan, uhat_pool, ws, ws_bytes, stream))) return st;
     if (nsteps > 0) {
@@ -2669,8 +2703,7 @@ int loop_batch_step(const void* plan, double* T, double* uhat_pool, double dtau,
             hipLaunchKernelGGL(k_batch_reset, dim3((p->nloops + 255) / 256), dim3(256), 0, hs, a.q, a.done, p->nloops);
             TraceScope ts_("k_batch", 0, hs);
             ts_.launch(k_batch, dim3(p->grid), dim3(kBlock), p->lds_bytes, hs, a);
-        } else if (p->schedule == LOOP_BATCH_STREAMS) {
-            std::lock_guard<std::mutex> lk(p->mu);
+        } else if (forks) {
             if ((st = launch_streams(p, p->nstreams, p->group_off[p->nstreams - 2], nsteps, a, hs))) return st;
         } else {
             launch_list(p, p->tile_off, PASS_A, 0, a, hs);

@@ -101,3 +101,44 @@ def test_a_failed_step_leaves_nothing_unordered(run, shapes, streams):
     assert p.step() == 0
     assert [c for c in log() if "launch" in c] == [c for c in calls if "launch" in c]
     """)
+
+
+@pytest.mark.parametrize("streams", [0, 2, 3, 4])
+def test_steps_during_a_capture(run, streams):
+    """While a capture holds the plan's streams, a step on another stream, eager or inside another
+    capture, is taken on that stream alone; steps of the same capture, and later ones, fork again."""
+    run(f"""
+    L.loop_set_resident(2)
+    p = Plan(MIXED)
+    if {streams}:
+        assert L.loop_batch_set_schedule(p.h, 2) == 0 and L.loop_batch_set_streams(p.h, {streams}) == 0
+    def launches(hs):  # of a step on hs: (all, off its stream)
+        R.rec_reset()
+        assert p.step(hs=hs) == 0
+        assert R.rec_unordered(hs) == 0
+        at = [c.split("@")[1].split()[0] for c in log() if c.startswith("launch")]
+        return len(at), sum(a != "%x" % hs for a in at)
+    eager = launches(HS)
+    assert eager[1] > 0
+    R.rec_capture(HS, 7)
+    assert launches(HS) == eager          # recorded: the plan's streams belong to capture 7
+    n, off = launches(HS2)                # eager, another stream
+    assert n > 0 and off == 0
+    R.rec_capture(HS2, 8)
+    assert launches(HS2) == (n, 0)        # recorded into a second graph
+    R.rec_end_capture(8)
+    assert launches(HS) == eager          # the first capture goes on
+    R.rec_end_capture(7)
+    assert launches(HS2) == eager and launches(HS) == eager
+    R.rec_capture(HS2, 9)
+    assert launches(HS2) == eager
+    """)
+
+
+def test_one_launch_takes_no_stream_of_the_plan(run):
+    run("""
+    p = Plan([(32, 32)] * 3)
+    R.rec_reset()
+    assert p.step() == 0
+    assert [c for c in log() if c != "func attribute"] == [c for c in log() if "k_resident_batch" in c and "@10 " in c]
+    """)
