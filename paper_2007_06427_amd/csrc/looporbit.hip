@@ -1434,7 +1434,7 @@ struct BatchPlan {
     int max_nb = 1, max_c = 1, max_n = 1, max_h = 1;
     size_t lds_bytes = 0;
     int grid = 1;
-    TileDesc* d_tiles = nullptr;  // tile lists: all loops' column tiles and row tiles, then the groups'
+    TileDesc* d_tiles = nullptr;  // tile lists: all loops' column tiles and row tiles, then the groups'; owns d_res, d_rest
     int tile_off[3] = {0, 0, 0};       // column tiles from [0], row tiles from [1]
     int schedule = 0;                  // LOOP_BATCH_PER_PASS, LOOP_BATCH_PERSISTENT or LOOP_BATCH_STREAMS
     double wait_limit = kDefaultWaitLimit;  // seconds: bound of one dependency wait (persistent)
@@ -1517,8 +1517,6 @@ void free_plan(BatchPlan* p) {
     if (p->d_loops) hipFree(p->d_loops);
     if (p->d_items) hipFree(p->d_items);
     if (p->d_tiles) hipFree(p->d_tiles);
-    if (p->d_res) hipFree(p->d_res);
-    if (p->d_rest) hipFree(p->d_rest);
     if (p->ev_fork) hipEventDestroy(p->ev_fork);
     for (int k = 0; k < 3; ++k) {
         if (p->ev_lag[k]) hipEventDestroy(p->ev_lag[k]);
@@ -2256,22 +2254,28 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
     }
     // the loops that take the resident form, by block size, and the rest
     std::vector<ResDesc> res;
-    std::vector<int> rest;
-    std::vector<char> is_res(nloops, 0);
+    std::vector<int> rest, of_class[4];
+    const size_t max_lds = (size_t)max_lds_per_block();
+    for (int l : order) {
+        const Shape& sh = p->loops[l].sh;
+        const size_t lds = resident_bytes(sh.M, sh.N);
+        if (lds == 0 || lds > max_lds) {
+            rest.push_back(l);
+            continue;
+        }
+        const int c = ilog2(resident_threads(sh.M, sh.N) / 64);
+        of_class[c].push_back(l);
+        p->res_mb += 16e-6 * sh.C * (9.0 * sh.N + 4.0 * sh.NB);
+        p->res_lds[c] = std::max(p->res_lds[c], lds);
+    }
     for (int c = 0; c < 4; ++c) {
         p->res_off[c] = (int)res.size();
-        for (int l : order) {
+        for (int l : of_class[c]) {
             const BatchLoop& b = p->loops[l];
-            if (!resident_usable(b.sh.M, b.sh.N) || resident_threads(b.sh.M, b.sh.N) != 64 << c) continue;
-            is_res[l] = 1;
             res.push_back(ResDesc{b.uoff, b.sh.L, l, b.sh.M, b.sh.N, 0});
-            p->res_mb += 16e-6 * b.sh.C * (9.0 * b.sh.N + 4.0 * b.sh.NB);
-            p->res_lds[c] = std::max(p->res_lds[c], resident_bytes(b.sh.M, b.sh.N));
         }
     }
     p->res_off[4] = (int)res.size();
-    for (int l : order)
-        if (!is_res[l]) rest.push_back(l);
     p->nrest = (int)rest.size();
     // tile lists of the launch-per-pass schedules: passes A, C and E share the column tiles, B
     // and D the row tiles. Of all loops, and of the rest; for each also in K groups of about
@@ -2316,29 +2320,31 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
         hipMalloc((void**)&p->d_items, sizeof(uint32_t) * items.size()) != hipSuccess ||
         hipMemcpy(p->d_loops, p->loops.data(), sizeof(BatchLoop) * nloops, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(p->d_items, items.data(), sizeof(uint32_t) * items.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMalloc((void**)&p->d_tiles, sizeof(TileDesc) * codes.size()) != hipSuccess ||
         hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming) != hipSuccess) {
         free_plan(p);
         return LOOP_EHIP;
     }
-    if (!res.empty()) {
-        if (hipMalloc((void**)&p->d_res, sizeof(ResDesc) * res.size()) != hipSuccess ||
-            hipMemcpy(p->d_res, res.data(), sizeof(ResDesc) * res.size(), hipMemcpyHostToDevice) != hipSuccess ||
-            (!rest.empty() &&
-             (hipMalloc((void**)&p->d_rest, sizeof(int) * rest.size()) != hipSuccess ||
-              hipMemcpy(p->d_rest, rest.data(), sizeof(int) * rest.size(), hipMemcpyHostToDevice) != hipSuccess))) {
-            free_plan(p);
-            return LOOP_EHIP;
-        }
-    }
     {
-        uint32_t* d_codes = nullptr;
+        // one allocation: tile records | resident loops | the other loops | item codes
         const int n = (int)codes.size();
-        bool ok = hipMalloc((void**)&d_codes, sizeof(uint32_t) * n) == hipSuccess &&
-                  hipMemcpy(d_codes, codes.data(), sizeof(uint32_t) * n, hipMemcpyHostToDevice) == hipSuccess;
-        if (ok) hipLaunchKernelGGL(k_fill_tiles, dim3((n + 255) / 256), dim3(256), 0, 0, p->d_loops, d_codes, n, p->d_tiles);
+        const size_t at_res = sizeof(TileDesc) * n, at_rest = at_res + sizeof(ResDesc) * res.size(),
+                     at_codes = at_rest + sizeof(int) * rest.size(), end = at_codes + sizeof(uint32_t) * n;
+        std::vector<char> h(end - at_res);
+        std::copy_n(reinterpret_cast<const char*>(res.data()), at_rest - at_res, h.data());
+        std::copy_n(reinterpret_cast<const char*>(rest.data()), at_codes - at_rest, h.data() + (at_rest - at_res));
+        std::copy_n(reinterpret_cast<const char*>(codes.data()), end - at_codes, h.data() + (at_codes - at_res));
+        char* d = nullptr;
+        bool ok = hipMalloc((void**)&d, end) == hipSuccess;
+        if (ok) {
+            p->d_tiles = reinterpret_cast<TileDesc*>(d);
+            p->d_res = reinterpret_cast<ResDesc*>(d + at_res);
+            p->d_rest = reinterpret_cast<int*>(d + at_rest);
+            ok = hipMemcpy(d + at_res, h.data(), h.size(), hipMemcpyHostToDevice) == hipSuccess;
+        }
+        if (ok)
+            hipLaunchKernelGGL(k_fill_tiles, dim3((n + 255) / 256), dim3(256), 0, 0, p->d_loops,
+                               reinterpret_cast<const uint32_t*>(d + at_codes), n, p->d_tiles);
         ok = ok && hipGetLastError() == hipSuccess && hipStreamSynchronize(0) == hipSuccess;
-        if (d_codes) hipFree(d_codes);
         if (!ok) {
             free_plan(p);
             return LOOP_EHIP;

@@ -142,3 +142,19 @@ def test_one_launch_takes_no_stream_of_the_plan(run):
     assert p.step() == 0
     assert [c for c in log() if c != "func attribute"] == [c for c in log() if "k_resident_batch" in c and "@10 " in c]
     """)
+
+
+def test_plan_creation_asks_little_of_the_runtime(run):
+    """Neither allocations nor queries grow with the number of loops."""
+    run("""
+    Plan(MIXED)
+    counts = []
+    for k in (1, 40):
+        R.rec_reset()
+        p = Plan(MIXED * k)
+        c = log()
+        L.loop_batch_destroy(p.h)
+        counts.append([sum(x == y for x in c) for y in ("malloc", "memcpy", "attribute", "free")])
+    assert counts[0] == counts[1], counts
+    assert counts[0][0] <= 4 and counts[0][2] <= 3, counts
+    """)
