@@ -355,7 +355,7 @@ int loop_batch_store(const void* plan, double* uhat_pool, void* ws, size_t ws_by
  * A variant is usable for a plan when its size range covers every loop's Nx (row passes)
  * or Ns (column passes). A new plan takes the narrowest staged variant for every pass, or
  * the configuration an earlier loop_batch_autotune chose for a plan with the same multiset
- * of (Nx, Ns) on the same device in this process.
+ * of (Nx, Ns) on the same device in this process (with loop_set_resident's mode 0, or not, as now).
  *
  * loop_batch_set_variant: pass 0..4, variant 0..LOOP_BATCH_VARIANTS-1; LOOP_EINVAL when the
  * variant does not cover the plan's sizes.
@@ -364,10 +364,13 @@ int loop_batch_store(const void* plan, double* uhat_pool, void* ws, size_t ws_by
  *
  * loop_batch_autotune times, on the caller's state (T[nloops], uhat_pool as for
  * loop_batch_step; neither is modified), every usable variant of every pass over `reps`
- * back-to-back launches (best of three trials, hipEvent timing on `stream`), keeps the
- * fastest per pass (the plan's current variant unless another is faster by more than 1%),
- * then times `reps` whole steps of the per-pass schedule and of the multi-stream one with 2, 3
- * and 4 streams, and keeps the fastest (the persistent schedule is not timed; its entry in the
+ * launches, as the steps would launch it: over the loops that do not take the resident form, and
+ * with the arrays that large plans' steps write over (best of three trials, hipEvent timing on
+ * `stream`). It keeps the fastest per pass (the plan's current variant unless another is faster by
+ * more than 1%). Row variant 3, with which no loop takes the resident form, is timed only for plans
+ * whose loops never would. It then times calls of `reps` whole steps on the per-pass schedule and
+ * on the multi-stream one with 2, 3 and 4 streams (reps should be the steps of the program's own
+ * calls: short calls gain less from streams and the resident form), and keeps the fastest (the persistent schedule is not timed; its entry in the
  * report is -1). The work of every kernel is independent of dtau
  * and scheme, so the timing runs use a step of 1e-30 (IMEX), which leaves the state unchanged
  * to the last bit in practice and keeps every repetition finite. It allocates temporary

@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <algorithm>
 #include <atomic>
+#include <climits>
 #include <cstring>
 #include <map>
 #include <string>
@@ -1590,8 +1591,8 @@ int step_impl(const Shape& s, Work w, const cd* tw, double* T, cd* u, double dta
 }  // namespace
 
 // ============================================================================ C ABI
-// Configurations chosen by loop_batch_autotune, per device and multiset of (Nx, Ns), for
-// the plans created later in the process.
+// Configurations chosen by loop_batch_autotune, per device, resident form on or off, and multiset
+// of (Nx, Ns), for the plans created later in the process.
 struct TunedConfig {
     int schedule, nstreams;
     int variant[5];
@@ -1605,7 +1606,7 @@ std::vector<int> plan_signature(const BatchPlan* p) {
     std::vector<std::pair<int, int>> sh;
     for (const BatchLoop& b : p->loops) sh.emplace_back(b.sh.M, b.sh.N);
     std::sort(sh.begin(), sh.end());
-    std::vector<int> key{p->device};
+    std::vector<int> key{p->device, g_resident.load() != 0};
     for (const auto& x : sh) {
         key.push_back(x.first);
         key.push_back(x.second);
@@ -2593,11 +2594,13 @@ int res_classes(const BatchPlan* p) {
 // three [29.6] 439 / 466, [54] 507 / 484 (5 steps 295 / 308). With no other loops a call of several
 // block sizes takes 72 us more than its steps, against 20 per step on one stream and more on several;
 // one block size needs neither fork nor join.
-bool resident_pays(const BatchPlan* p, int nsteps, int mode) {
+bool resident_pays_on(const BatchPlan* p, int nsteps, int mode, int K) {
     if (mode != 1) return mode == 2;
-    const int K = p->schedule == LOOP_BATCH_STREAMS ? p->nstreams : 1;
     if (p->nrest == 0) return res_classes(p) == 1 || nsteps >= (K == 1 ? 4 : 2);
     return p->res_mb >= 8.0 + 12.0 * K && p->res_mb * nsteps >= 25.0 + 125.0 * K;
+}
+bool resident_pays(const BatchPlan* p, int nsteps, int mode) {
+    return resident_pays_on(p, nsteps, mode, p->schedule == LOOP_BATCH_STREAMS ? p->nstreams : 1);
 }
 
 // The per-pass kernels of the loops that do not take the resident form, on K streams.
@@ -2799,20 +2802,56 @@ int loop_batch_autotune(void* plan, const double* T, const double* uhat_pool, in
         }
         return best;
     };
-    // Every pass is a function of the work space alone (pass D also moves the copy of T), so
-    // after one full step each pass can be repeated in place and timed.
+    // Variants are timed on what the steps launch them for: the loops that do not take the resident
+    // form, with the arrays the steps use. With the arrays apart, every pass is a function of the
+    // work space alone (pass D also moves the copy of T), so after one full step each pass can be
+    // repeated and timed. In place, passes C and D write over what they read: whole steps run, and
+    // the pass is timed within them. Row variant 3 turns the resident form off (loop_batch_step), so
+    // it competes only where no call, however long, would take that form.
+    p->chosen = false;
+    const int mode = g_resident.load();
+    const bool res = p->res_off[4] > 0 && resident_pays(p, reps, mode);
+    const bool res_ever = p->res_off[4] > 0 && resident_pays_on(p, INT_MAX, mode, 1);
+    const int* off = res && p->nrest > 0 ? p->rest_off : p->tile_off;
+    const bool in_place = p->ws_bytes > kInPlaceBytes;
     loop_batch_load(p, tpool, ws, ws_bytes, stream);
     const BatchArgs a = batch_args(p, base, tT, nullptr, 2, dtau, scheme, tw);
-    for (int pass = PASS_A; pass <= PASS_E; ++pass) launch_pass(p, pass, 0, a, hs);
+    auto launch = [&](int pass) { launch_list(p, off, pass, 0, a, hs, !in_place); };
+    auto time_pass = [&](int pass) -> double {
+        if (!in_place || pass == PASS_A) {
+            launch(pass);  // the first launch of a kernel also loads its code
+            return time_calls([&] { launch(pass); }, reps);
+        }
+        double best = 1e300;
+        for (int trial = 0; trial < 4; ++trial) {  // the first loads the code
+            double us = 0.0;
+            for (int i = 0; i < reps; ++i) {
+                for (int q = PASS_B; q <= PASS_E; ++q) {
+                    if (q == pass) timed_ok = timed_ok && hipEventRecord(e0, hs) == hipSuccess;
+                    launch(q);
+                    if (q == pass) timed_ok = timed_ok && hipEventRecord(e1, hs) == hipSuccess;
+                }
+                float ms = 0.0f;
+                timed_ok = timed_ok && hipEventSynchronize(e1) == hipSuccess &&
+                           hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
+                us += 1e3 * (double)ms;
+            }
+            if (trial > 0) best = std::min(best, us / reps);
+        }
+        return best;
+    };
+    if (res_ever)
+        for (int pass : {PASS_B, PASS_D})
+            if (p->variant[pass] == 3) p->variant[pass] = rag_default(p, pass);
+    for (int pass = PASS_A; pass <= PASS_E; ++pass) launch(pass);
     for (int pass = PASS_A; pass <= PASS_E; ++pass) {
         const int incumbent = p->variant[pass];
         int best_v = incumbent;
         double best_t = 1e300;
         for (int v = 0; v < rag_count(pass); ++v) {
-            if (!rag_covers(p, pass, v)) continue;
+            if (!rag_covers(p, pass, v) || (v == 3 && res_ever)) continue;
             p->variant[pass] = v;
-            launch_pass(p, pass, 0, a, hs);  // the first launch of a kernel also loads its code
-            const double t = time_calls([&] { launch_pass(p, pass, 0, a, hs); }, reps);
+            const double t = time_pass(pass);
             rep[pass * kRagVariants + v] = t;
             if (t < best_t) {
                 best_t = t;

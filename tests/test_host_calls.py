@@ -48,6 +48,7 @@ class Plan:
     def step(self, nsteps=2, hs=HS):
         if not hasattr(self, "T"):
             self.T, self.pool, self.ws = self.mem(8 * self.n), self.mem(16 * self.pool_elems), self.mem(64)
+            ctypes.c_uint64.from_address(self.ws + 8).value = 0x4C4F4F504F524254  # a prepared work space
         return L.loop_batch_step(self.h, self.T, self.pool, 1e-4, 1, nsteps, None, self.ws, self.ws_bytes, hs)
 
 MIXED = [(32, 32), (64, 64), (64, 128), (32, 512), (64, 256)]  # three resident block sizes and two other loops
@@ -157,4 +158,73 @@ def test_plan_creation_asks_little_of_the_runtime(run):
         counts.append([sum(x == y for x in c) for y in ("malloc", "memcpy", "attribute", "free")])
     assert counts[0] == counts[1], counts
     assert counts[0][0] <= 4 and counts[0][2] <= 3, counts
+    """)
+
+
+TUNE = """
+    def tune(p, reps=4):
+        p.step()
+        p.rep = (D * 25)()
+        R.rec_reset()
+        st = L.loop_batch_autotune(p.h, p.T, p.pool, reps, p.rep, p.ws, p.ws_bytes, HS)
+        assert st == 0, st
+        return log()
+    def variants(p):
+        v = (I * 5)()
+        L.loop_batch_get_config(p.h, None, v, None)
+        return list(v)
+    def launches(p, nsteps=4):
+        R.rec_reset()
+        assert p.step(nsteps) == 0
+        return [c for c in log() if c.startswith("launch")]
+    R.rec_cost(b"k_rag", 100.0)
+    R.rec_cost(b"k_ragILi1ELi3E", 80.0)  # row variant 3 is the fastest of passes B and D alone
+    R.rec_cost(b"k_ragILi3ELi3E", 80.0)
+    R.rec_cost(b"k_ragILi1ELi2E", 90.0)
+"""
+
+
+@pytest.mark.parametrize("mode,count", [(2, 1), (1, 60)])
+def test_tuner_keeps_the_resident_form(run, mode, count):
+    """Row variant 3 turns the resident form off: the tuner leaves it out where steps take that
+    form, and takes it where no loop has the form, or the form is off."""
+    run(TUNE + f"""
+    L.loop_set_resident({mode})
+    shapes = MIXED * {count}
+    p = Plan(shapes)
+    tune(p)
+    assert variants(p)[1] == 2 and variants(p)[3] != 3 and p.rep[4 + 3] == -1
+    assert any("k_resident_batch" in c for c in launches(p, 40))
+    q = Plan([(64, 256), (32, 512)])
+    tune(q)
+    assert variants(q)[1] == 3 and variants(q)[3] == 3
+    L.loop_set_resident(0)
+    r = Plan(shapes)
+    assert variants(r)[1] != 2  # tuned with the form on
+    tune(r)
+    assert variants(r)[1] == 3
+    L.loop_set_resident({mode})
+    assert variants(Plan(shapes))[1] == 2  # and each choice is kept for its own mode
+    """)
+
+
+def test_tuner_times_what_steps_launch(run):
+    """Over the loops that do not take the resident form; for plans whose steps write their
+    intermediates in place, within whole steps; and a plan whose variants were set by hand is the
+    tuner's again."""
+    run(TUNE + """
+    grid = lambda c: c.split("grid")[1]
+    L.loop_set_resident(2)
+    p = Plan(MIXED)
+    L.loop_batch_set_variant(p.h, 1, 0)
+    calls = [c for c in tune(p) if "k_ragILi1ELi1E" in c]
+    assert L.loop_batch_set_schedule(p.h, 0) == 0
+    step = launches(p)
+    assert any("k_resident_batch" in c for c in step)
+    rest = {grid(c) for c in step if "k_ragILi1E" in c}
+    assert len(rest) == 1 and {grid(c) for c in calls} == rest, (rest, calls)
+    big = Plan([(64, 256)] * 400)  # 160 MB of intermediates
+    assert big.ws_bytes > 128 << 20
+    calls = "".join(c.split("k_ragILi")[1][0] for c in tune(big) if "k_ragILi" in c and "@10 " in c)
+    assert "22" not in calls and "33" not in calls, calls  # no pass C or D over its own output
     """)
