@@ -166,14 +166,15 @@ __device__ __forceinline__ void nonlinear(const cd (&v)[3], const double (&hs)[3
     for (int r = 0; r < 3; ++r) out[r] = cd{hs[r] * w[r].y, -hs[r] * w[r].x};
 }
 
-// Stores the modes of a run (zero beyond K) into a row of H values; y0: imaginary part of the mean.
+// Stores the modes of a run (zero beyond K) into a row of H values; y0: imaginary part of the mean,
+// which u holds apart as zero, or as NaN once the run has overflowed.
 template <int NX>
 __device__ __forceinline__ void store_modes(const cd (&u)[3], double y0, int t, cd* row) {
     using D = Dns<NX>;
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
         const int j = t + r * D::TPF;
-        if (j <= D::K) row[j] = cd{u[r].x, j == 0 ? y0 : u[r].y};
+        if (j <= D::K) row[j] = cd{u[r].x, j == 0 ? y0 + u[r].y : u[r].y};
     }
     for (int j = D::K + 1 + t; j < D::H; j += D::TPF) row[j] = cd{0.0, 0.0};
 }
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(64) void k_ks_etdrk4(double L, int sym, double h, i
 #pragma unroll
                 for (int r = 0; r < 3; ++r) {
                     const bool mean = r == 0 && t == 0;
-                    const double y = mean ? y0 : u[r].y;
+                    const double y = mean ? y0 + u[r].y : u[r].y;
                     e += (mean ? 1.0 : 2.0) * (u[r].x * u[r].x + y * y);
                 }
                 if constexpr (D::E::L == 1) {  // a run's lanes are equal modulo RUNS
