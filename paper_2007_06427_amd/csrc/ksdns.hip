@@ -416,7 +416,10 @@ __global__ __launch_bounds__(kScanBlock) void k_ks_recurrences(const double* nor
 // (j, four k's), each taking every eighth sample, so a sample is loaded once for four k's
 // and the lanes' sums are added in a fixed order. The n roots of unity sit in LDS: evaluating
 // sincospi per term, as one thread per (j, k) did, costs two hundred instructions instead of one
-// LDS read, and is kept only where the roots do not fit (n > kRoots).
+// LDS read, and is kept only where the roots do not fit (n > kRoots). With kc = 0 the sums are
+// plain ones and need no root: forming the item's three unused modes from sincospi there took 4000
+// us for 2000 loops of 64 x 64 cut from segments of 5000 samples, against 628 without (before
+// the roots were tabulated 2183).
 constexpr int kSegBlock = 1024, kSegLanes = 8, kSegK = 4, kRoots = 4096;
 
 __global__ __launch_bounds__(kSegBlock) void k_ks_segments(const cd* snaps, int H, int ntraj, int ns, int stride,
@@ -442,7 +445,7 @@ __global__ __launch_bounds__(kSegBlock) void k_ks_segments(const cd* snaps, int 
         sincospi(2.0 * (double)m / n, &s, &c);
         return cd{c, s};
     };
-    if (table)
+    if (table && kc > 0)
         for (int m = threadIdx.x; m < n; m += kSegBlock) root[m] = root_of(m);
     __syncthreads();
     const cd* seg = snaps + ((size_t)tr * stride + a) * H;
@@ -464,7 +467,9 @@ __global__ __launch_bounds__(kSegBlock) void k_ks_segments(const cd* snaps, int 
             C[q] = cd{__builtin_fma(x.x, w.x, C[q].x), __builtin_fma(x.y, w.x, C[q].y)};
             S[q] = cd{__builtin_fma(x.x, w.y, S[q].x), __builtin_fma(x.y, w.y, S[q].y)};
         };
-        if (table) {
+        if (kc == 0) {
+            for (int i = lane; i < n; i += kSegLanes) term(seg[(size_t)i * H + j], cd{1.0, 0.0}, 0);
+        } else if (table) {
 #pragma unroll 2
             for (int i = lane; i < n; i += kSegLanes) {
                 const cd x = seg[(size_t)i * H + j];
