@@ -98,6 +98,15 @@ def pass_bytes(shapes, p):
     return 16 * tot
 
 
+def batched_step_bytes(shapes, resident, steps):
+    """Algorithmic bytes of one step of a loop_batch_step call of `steps` steps: the four passes of
+    the loops that take the per-pass kernels, and for the loops that take the resident form
+    (resident[l]) one load and one store of their spectrum per call."""
+    rest = [s for s, r in zip(shapes, resident) if not r]
+    held = sum(2 * 16 * Ns * (Nx // 2 + 1) for (Nx, Ns), r in zip(shapes, resident) if r)
+    return sum(pass_bytes(rest, p) for p in (1, 2, 3, 4)) + held / steps
+
+
 def step_flops(Nx, Ns):
     """Algorithmic FP64 flops of one step of one loop (5 n log2 n per complex n-point transform):
     four transforms per band column (C: forward and inverse; E: forward and the next step's
@@ -225,8 +234,17 @@ def main():
     assert np.all(np.isfinite(J))
     value = pts_step * steps / wall
 
-    # ---- per-kernel timing, pass by pass (each pass over every loop, alone on the stream, as
-    # the per-pass schedule runs it), with events on the launch stream. Every pass is a
+    # ---- which form the timed call took: a call of the same kind under the kernel trace
+    with api.trace() as tr:
+        pool, T = pool0.clone(), T0.clone()
+        batch.step(pool, T, dtau, scheme, min(steps, 200))
+        torch.cuda.synchronize()
+    took = any(k.startswith("k_resident_batch") for k in tr.kernels)
+    resident = [took and api.resident_supported(Nx, Ns) for Nx, Ns in shapes]
+
+    # ---- per-kernel timing, pass by pass (each pass over every loop, also those that the timed
+    # call takes in the resident form, with the intermediates apart, alone on the stream: the
+    # building blocks of loop_batch_pass), with events on the launch stream. Every pass is a
     # function of the work space alone, so pass p is launched R times back to back between one
     # event pair; the launches take a negligible step (a kernel's work does not depend on it),
     # so that pass D's repeated period updates leave T where it is. A backlog of queued whole
@@ -253,14 +271,17 @@ def main():
     by = pass_bytes(shapes, dom)
     achieved = by / (avg_us[dom] * 1e-6) / 1e9
     traffic = measured_traffic(args.workload, kernel_of(dom))
-    step_bytes = sum(pass_bytes(shapes, p) for p in (1, 2, 3, 4))
+    step_bytes = batched_step_bytes(shapes, resident, steps)
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "kernel": f"{kernel_of(dom)} pass {PASS_NAMES[dom]}", "bytes_per_launch": by,
                 "avg_launch_us": round(avg_us[dom], 2),
                 "passes_us": {kernel_of(p): round(v, 2) for p, v in avg_us.items()},
-                "passes_sum_vs_step": round(passes_sum_us / (step_s * 1e6), 3),
-                "step_bytes": step_bytes,
+                "passes_form": "every loop, intermediates apart",
+                # no such ratio where the timed step runs fewer tiles than the passes timed here
+                "passes_sum_vs_step": None if took else round(passes_sum_us / (step_s * 1e6), 3),
+                "resident_loops": sum(resident),
+                "step_bytes": round(step_bytes),
                 # the whole step, every pass, as the timed region ran it (its kernels may overlap)
                 "step_achieved": round(step_bytes / (e0.elapsed_time(e1) * 1e-3 / steps) / 1e9, 1),
                 "step_frac": round(step_bytes / (e0.elapsed_time(e1) * 1e-3 / steps) / 1e9 / HBM_PEAK_GBS, 4)}

@@ -41,6 +41,18 @@ def test_passes_add_up_to_the_step_model():
         assert sum(bench.pass_bytes([(Nx, Ns)], p) for p in (1, 2, 3, 4)) == 16 * (9 * W + 4 * S)
 
 
+def test_resident_loops_move_their_spectrum_once_per_call():
+    """A loop in the resident form is loaded and stored once per call, whatever its passes would
+    move; the others are charged their passes."""
+    small, large = (64, 128), (64, 512)
+    passes = sum(bench.pass_bytes([large], p) for p in (1, 2, 3, 4))
+    spectrum = 16 * 128 * 33
+    assert bench.batched_step_bytes([small, large], [False, False], 10) == \
+        sum(bench.pass_bytes([small, large], p) for p in (1, 2, 3, 4))
+    assert bench.batched_step_bytes([small, large], [True, False], 10) == passes + 2 * spectrum / 10
+    assert bench.batched_step_bytes([small, small], [True, True], 1) == 4 * spectrum
+
+
 @pytest.mark.parametrize("workload", ["batched-ragged-256", "batched-256x1024"])
 def test_byte_model_agrees_with_the_measured_traffic(workload):
     """Every pass moves, by FETCH_SIZE + WRITE_SIZE (calibrated by a device copy), within 5% of
