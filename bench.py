@@ -1004,11 +1004,10 @@ def bench_orbits(args, E=128, per_run=2, chunk=400_000, J_tol=5e-25):
 
 
 def dns_step_flops(Nx):
-    """FP64 flops of one ETDRK4 step of one run: four nonlinear evaluations, each an inverse and a
-    forward transform of Nx points (5 n log2 n each) and Nx squares, plus the stage combinations
-    (about 40 flops per mode, K = (Nx-1)/3 modes)."""
-    K = (Nx - 1) // 3
-    return 4 * (2 * 5 * Nx * (Nx.bit_length() - 1) + Nx) + 40 * (K + 1)
+    """FP64 flops of one ETDRK4 step of one run: four nonlinear evaluations, each two transforms of a
+    real row of Nx points (half of 5 n log2 n each: the inverse gives real values, the forward
+    takes them), and 20 flops per mode of its half spectrum for the products and the stages."""
+    return 4 * (5 * Nx * (Nx.bit_length() - 1) + 20 * (Nx // 2 + 1))
 
 
 def bench_dns(args, E=4096, Nx=64, L=39.0, dt=0.05, every=2):

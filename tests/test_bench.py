@@ -107,3 +107,11 @@ def test_autograd_byte_model_agrees_with_the_measured_traffic():
     for name, alg in want.items():
         got = d["kernels"][name]["bytes_per_launch"]
         assert abs(got / alg - 1.0) < 0.05, (name, got, alg)
+
+
+@pytest.mark.parametrize("Nx", [16, 64, 256])
+def test_run_flops_are_those_of_the_timed_cases(Nx):
+    """One count for a run's step, here and in perf/cases.py: real rows, not complex ones."""
+    from perf import cases
+    case = dict(kind="runs", Nx=Nx, nsteps=1, every=1, runs=1)
+    assert bench.dns_step_flops(Nx) == cases.work(case)["flops"]
