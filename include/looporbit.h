@@ -286,7 +286,8 @@ int loop_update(double L, int Nx, int Ns, int nloops, double* T, double* uhat,
  * a conversion into band layout (which also makes every loop canonical), the steps (see
  * loop_batch_set_schedule), and the conversion back. Its work space
  * (loop_batch_info bytes) must be prepared once by loop_batch_workspace_init; a call that
- * ended in LOOP_EHANG leaves it ready for the next call. */
+ * ended in LOOP_EHANG leaves it ready for the next call. A step leaves no state in it for
+ * loop_batch_store or loop_batch_pass to go on from: those follow loop_batch_load. */
 typedef enum { LOOP_BATCH_PER_PASS = 0, LOOP_BATCH_PERSISTENT = 1, LOOP_BATCH_STREAMS = 2 } loop_batch_schedule;
 int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns, void** plan);
 /* Choose how loop_batch_step runs the steps (results are identical bit for bit):
@@ -294,14 +295,15 @@ int loop_batch_create(int nloops, const double* L, const int* Nx, const int* Ns,
  *   On this schedule and on LOOP_BATCH_STREAMS, loops that fit in LDS (loop_resident_supported)
  *   run all their steps in the resident form, one block each, beside the kernels of the other
  *   loops, on streams the plan owns, where that was measured faster (mode 1 of
- *   loop_set_resident), always (2) or never (0, or a variant set by hand);
+ *   loop_set_resident), always (2) or never (0, or a variant set by hand since the last
+ *   loop_batch_autotune, or row variant 3). The other loops of a plan on four streams then run in
+ *   three groups;
  *   LOOP_BATCH_PERSISTENT: one launch for all steps. Each loop is assigned to one XCD, and
  *   blocks pull (pass, loop, tile) items of their own XCD's list in dependency order, so that
  *   every hand-over between blocks stays within one L2 (see the scheduler notes in the
  *   source). loop_batch_create finds the XCDs with a probe launch; a block on an XCD the
  *   probe did not see leaves and sets LOOP_ENOTSUP. It measured 1.7-3.4x slower than the
- *   other two, and
- *   loop_batch_autotune does not choose it;
+ *   other two, and loop_batch_autotune does not choose it;
  *   LOOP_BATCH_STREAMS: the loops split into K groups of about equal work (K from
  *   loop_batch_set_streams, 2 to 4, default 2), group 0 on `stream` and the others on streams
  *   the plan owns (default priority), each started one pass after the previous group, so that

@@ -725,9 +725,10 @@ __global__ void k_batch_reset(BatchQueue* q, int* done, int nloops) {
 // transform sizes its size dispatch contains. Registers are allocated for the largest body
 // a kernel holds, so a kernel limited to short transforms can keep more wavefronts per SIMD.
 // For the row passes a variant also fixes how a tile of rows reaches LDS: staged through
-// vector registers (RowLoad) or copied by the load unit (load_rows_lds). Every variant
-// runs the same arithmetic; a plan starts with the narrowest staged variant that covers its
-// sizes, and loop_batch_autotune times the others.
+// vector registers (RowLoad) or copied by the load unit (load_rows_lds). Variants 0 to 2 of a
+// pass run the same arithmetic; row variant 3 pairs rows and factors its transforms
+// differently and agrees to rounding. A plan starts with the narrowest staged variant that covers
+// its sizes, and loop_batch_autotune times the others.
 struct RagVariant {
     int lo, hi;  // transform sizes compiled in: powers of two in [lo, hi]
     bool dma;    // row tiles copied straight into LDS
@@ -1354,12 +1355,13 @@ int launch_xi_step(const Shape& s, const XiWork& w, double* T, double dtau, int 
 // ---------------------------------------------------------------------------- resident form
 int last_error() { return hipGetLastError() == hipSuccess ? LOOP_OK : LOOP_EHIP; }
 
-// loop_set_resident: 0 never, 1 (default) and 2 wherever it fits. Mode 1 took the faster form by loop
-// count while the two crossed; the resident form now measures faster at every loop count (us
-// per step, resident / per-pass, at 1, 256 and 2048 loops):
-//   32 x 32  5.2 / 15.1   5.5 / 24.5   17.6 / 44.5      32 x 256   11.4 / 18.2  12.7 / 41.0   92 / 200
-//   64 x 64  7.5 / 16.7   8.3 / 30.3   60.6 / 96.7      64 x 128   12.6 / 19.2  13.9 / 42.3  102 / 202
-//   8 x 512  6.9 / 16.7   7.5 / 30.4   35.6 / 98.3      128 x 64   11.8 / 19.4  13.1 / 42.5   95 / 202
+// loop_set_resident: 0 never, 1 (default) and 2 wherever it fits. loop_step takes the resident form
+// for every shape that has it, whatever the number of loops: it measured faster everywhere (us per
+// step in calls of 40 steps, resident / per-pass, at 1, 256 and 2048 loops; calls of 1 to 5 steps of
+// up to 8192 loops alike: one step of 2048 loops of 64 x 128 takes 149 us, 334 in the per-pass form).
+//   8 x 8    3.3 / 13.8   2.8 / 54.6   4.6 / 60.0       32 x 256  11.1 / 19.0  12.3 / 41.1  90.8 / 178
+//   32 x 32  5.0 / 15.7   5.1 / 24.8   16.6 / 44.4      64 x 128  12.7 / 19.9  13.9 / 42.2  103 / 178
+//   64 x 64  7.3 / 17.7   8.1 / 30.9   59.0 / 97.0      128 x 64  11.2 / 19.7  12.9 / 42.9  92.5 / 177
 std::atomic<int> g_resident{1};
 
 int max_lds_per_block() {
@@ -1391,10 +1393,6 @@ int resident_threads(int Nx, int Ns) {
     return t;
 }
 
-// loop_step takes the resident form for every shape that has it, whatever the number of loops: it
-// measured faster everywhere (us per step, resident / per-pass: one loop of 32 x 32 4.9 / 16.6, of
-// 64 x 128 12.6 / 20.4; 2048 loops of 8 x 8 4.6 / 60, of 32 x 32 16.8 / 44.1, of 64 x 64 59 / 100, of
-// 32 x 256 92 / 181, of 64 x 128 103 / 180, of 128 x 64 96 / 182).
 bool resident_usable(int Nx, int Ns) {
     const size_t b = resident_bytes(Nx, Ns);
     return b > 0 && b <= (size_t)max_lds_per_block();
@@ -2593,7 +2591,11 @@ int res_classes(const BatchPlan* p) {
 // one stream [14.7] 309 / 333, [29.6] 221 / 211, [55] 301 / 290; two [29.6] 379 / 382, [54] 516 / 504;
 // three [29.6] 439 / 466, [54] 507 / 484 (5 steps 295 / 308). With no other loops a call of several
 // block sizes takes 72 us more than its steps, against 20 per step on one stream and more on several;
-// one block size needs neither fork nor join.
+// one block size needs neither fork nor join. Over 880 calls (44 random batches of 3 to 600 loops, 1
+// to 4 streams, 1 to 30 steps) the choice was more than 3% faster than no resident loops in 232
+// and more than 3% slower in 4, by 8% at most. Replays of recorded calls follow it: 10 steps of 256
+// ragged loops on one stream take 523 us without and 508 with them, where it takes them, of 40 such
+// loops 270 and 328, where it does not.
 bool resident_pays_on(const BatchPlan* p, int nsteps, int mode, int K) {
     if (mode != 1) return mode == 2;
     if (p->nrest == 0) return res_classes(p) == 1 || nsteps >= (K == 1 ? 4 : 2);
@@ -2623,7 +2625,7 @@ int step_rest(const BatchPlan* p, int K, cd* pool, int nsteps, const BatchArgs& 
 // the per-pass kernels of the rest share the others. forks: there is more than one launch to place;
 // the caller then holds p->mu and the plan's streams are free.
 int step_with_resident(const BatchPlan* p, cd* pool, int nsteps, bool forks, const BatchArgs& a, hipStream_t hs) {
-    const int K = p->schedule == LOOP_BATCH_STREAMS ? std::min(p->nstreams, 3) : 1;
+    const int K = p->schedule == LOOP_BATCH_STREAMS ? std::min(p->nstreams, 3) : 1;  // one of the three stays free
     const ResArgs r{nullptr, pool, a.T, a.J_hist, a.status, a.tw, a.dtau, a.scheme, a.nsteps, a.nloops};
     Fork f{p, hs};
     int st = !forks || hipEventRecord(p->ev_fork, hs) == hipSuccess ? LOOP_OK : LOOP_EHIP;
@@ -2865,8 +2867,8 @@ int loop_batch_autotune(void* plan, const double* T, const double* uhat_pool, in
         p->variant[pass] = best_v;
     }
     // schedules: per-pass, then the multi-stream one with 2, 3 and 4 streams. The persistent
-    // schedule is not timed: it measured 3-5x slower than these on every workload (an
-    // agent-scope release per item to order work across the XCDs' separate L2 caches).
+    // schedule is not timed: it measured 1.7x (256 ragged loops) and 3.4x (64 of 256 x 1024) slower
+    // than these (its one kernel holds every pass body, 248 registers and a stack per lane).
     double best_us = 1e300;
     int best_s = LOOP_BATCH_PER_PASS, best_k = 2;
     for (int c = 0; c < 5; ++c) {
