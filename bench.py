@@ -72,6 +72,8 @@ def parse():
     ap.add_argument("--steps", type=int, default=None)
     ap.add_argument("--warmup", type=int, default=10)
     ap.add_argument("--workload", default="autograd-256x1024", choices=sorted(WORKLOADS))
+    ap.add_argument("--no-resident", action="store_true",
+                    help="batches: keep every loop on the per-pass kernels (for their counters over all loops)")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle baseline")
     ap.add_argument("--runs", type=int, default=128, help="orbits-39: chaotic runs")
     ap.add_argument("--per-run", type=int, default=2, help="orbits-39: loops cut from each run")
@@ -203,6 +205,9 @@ def main():
     batch = api.Batch([(s.L, s.Nx, s.Ns) for s in specs])
     pool0 = batch.pack([torch.from_numpy(s.uhat) for s in specs])
     T0 = torch.tensor([s.T for s in specs], dtype=torch.float64, device=dev)
+
+    if args.no_resident:
+        api.set_resident(api.RESIDENT_NEVER)
 
     # ---- kernel variants and schedule chosen by the autotuner (before any timed work)
     tuning = batch.autotune(pool0, T0, reps=20)
@@ -345,6 +350,7 @@ def main():
     # ---- plain method on the same loops: loop_step per loop, one after another
     plain = None
     if nl > 1:
+        api.set_resident(api.RESIDENT_AUTO)
         Kp = 10
         sub = []
         for s in specs:

@@ -130,13 +130,18 @@ def summarize_traffic(fetch_csv: str, write_csv: str, workload: str, command: st
     wfac = (wcopy / want_kib) if wcopy else 1.0
     # Per kernel, the launch over every loop of the plan (the largest grid), taken from
     # dispatches of the same grid in both runs: a schedule that splits the loops into groups
-    # also launches the kernel on part of them, and the two runs may tune differently.
+    # also launches the kernel on part of them, and the two runs may tune differently. Batch kernels
+    # launched over part of the loops alone (variants that the tuner timed beside resident loops) are left out.
+    whole = collections.defaultdict(int)
+    for (name, g) in fetch:
+        if name.startswith("k_rag<"):
+            whole[name.split(",")[0]] = max(whole[name.split(",")[0]], int(g))
     kernels = {}
     for key in sorted(set(fetch) & set(write), key=lambda k: (k[0], -int(k[1]))):
         name = key[0]
         if not name.startswith("k_"):
             continue
-        if name in kernels:
+        if name in kernels or int(key[1]) < whole.get(name.split(",")[0], 0):
             continue
         f = sum(fetch[key]) / len(fetch[key])
         w = sum(write[key]) / len(write[key])
