@@ -247,16 +247,38 @@ struct FftPos {
 // before it. These depend only on the thread, so it loads them once and reuses them for
 // every transform it runs. The cache holds w, w^2, w^4 (and w^8) as read from the table, and
 // the other powers are formed by one or two complex products, each within a few units in the
-// last place. The inverse transform uses the conjugates, after its butterflies.
+// last place. The inverse transform uses the conjugates, after its butterflies, so an error in a
+// power's magnitude does not cancel between the two. The stage after the radix-F stage has few
+// positions to average such errors over (F of them), and transforms of F > 1 multiply by formed
+// powers in one stage more than radix 8 first and F last would. That stage therefore forms its powers
+// by quarter turns of the table's, without rounding, where the registers cost no wavefront: with F = 2
+// w^4 is such a turn, and w^3 = w^4 conj(w); in 32-point transforms w^8 is one, and w^5, w^6, w^7 =
+// w^8 conj(w^3, w^2, w), w^3 from the table. With F = 4 of 256 points, and 16 points per thread, w^3
+// alone comes from the table. The cost J of loops whose products outweigh their linear part (rms
+// relative error against long double, in units of 1e-16, with all of that stage's powers formed by
+// products and now): 16 x 32 4.9 and 2.5, 32 x 32 4.9 and 2.3, 128 x 64 6.5 and 5.7, 256 x 32 6.9 and
+// 4.9, at the same speed.
 //
 // With ALL it holds every power instead, formed once by the same products (equal bit for bit): 16
 // registers more per stage, and four products (16 instructions of about 100) less per stage
 // of every transform.
+enum Powers { FORMED, WITH_W3, TURNED_2, TURNED_4 };  // WITH_W3: FORMED, but w^3 from the table
+template <int N, int PT>
+constexpr Powers tw_how(int stage) {
+    using E = Fft<N, PT>;
+    if (PT == 16) return WITH_W3;
+    if (PT != 8 || stage != 1 || E::F == 1) return FORMED;
+    return E::F == 2 ? TURNED_2 : E::L == 1 ? TURNED_4 : WITH_W3;
+}
+// Entry b of a stage's cache holds this power: 1, 2, 4 (and 8), then w^3, then w^8.
+constexpr int tw_entries(int PT, Powers how) { return ilog2(PT) + (how == WITH_W3 ? 1 : how == TURNED_4 ? 2 : 0); }
+constexpr int tw_power(int b, int PT) { return b == ilog2(PT) ? 3 : b > ilog2(PT) ? 8 : 1 << b; }
+
 template <int N, int PT, bool ALL_ = false>
 struct TwCache {
     static_assert(!ALL_ || PT == 8, "tw_powers");
     static constexpr bool ALL = ALL_;
-    static constexpr int NB = ALL ? PT - 1 : ilog2(PT);
+    static constexpr int NB = ALL ? PT : ilog2(PT) + 2;
     static constexpr int L = Fft<N, PT>::L;
     cd w[L][NB];
 };
@@ -268,12 +290,19 @@ __device__ __forceinline__ cd opaque(cd w) {
     return w;
 }
 
-// w^3, w^5, w^6, w^7 from w, w^2, w^4 (w[m - 1] = w^m), formed as apply_twiddles forms them
+template <bool INV>
+__device__ __forceinline__ cd cmul_tw(cd a, cd w) {
+    return INV ? cd{__builtin_fma(a.x, w.x, a.y * w.y), __builtin_fma(a.y, w.x, -(a.x * w.y))} : cmul(a, w);
+}
+
+// w^3, w^5, w^6, w^7 from w, w^2, w^4 (w[m - 1] = w^m), and w^3 and w^8 with some, formed as apply_twiddles forms them
+template <Powers HOW>
 __device__ __forceinline__ void tw_powers(cd* w) {
-    w[2] = cmul(w[0], w[1]);
-    w[4] = cmul(w[0], w[3]);
-    w[5] = cmul(w[1], w[3]);
-    w[6] = cmul(w[2], w[3]);
+    if constexpr (HOW == FORMED) w[2] = cmul(w[0], w[1]);
+    if constexpr (HOW == TURNED_2) w[2] = cmul_tw<true>(w[3], w[0]);
+    w[4] = HOW == TURNED_4 ? cmul_tw<true>(w[7], w[2]) : cmul(w[0], w[3]);
+    w[5] = HOW == TURNED_4 ? cmul_tw<true>(w[7], w[1]) : cmul(w[1], w[3]);
+    w[6] = HOW == TURNED_4 ? cmul_tw<true>(w[7], w[0]) : cmul(w[2], w[3]);
 #pragma unroll
     for (int b = 0; b < 7; ++b) w[b] = opaque(w[b]);
 }
@@ -294,8 +323,9 @@ __device__ __forceinline__ void tw_cache_fill(TwCache<N, PT, ALL>& c, const Pos&
             ti = p.f1;  // the middle stage of three
         }
 #pragma unroll
-        for (int b = 0; b < ilog2(PT); ++b) c.w[I - 1][ALL ? (1 << b) - 1 : b] = tw[((ti << b) * step) & (TW_N - 1)];
-        if constexpr (ALL) tw_powers(c.w[I - 1]);
+        for (int b = 0; b < tw_entries(PT, tw_how<N, PT>(I)); ++b)
+            c.w[I - 1][ALL ? tw_power(b, PT) - 1 : b] = tw[(ti * tw_power(b, PT) * step) & (TW_N - 1)];
+        if constexpr (ALL) tw_powers<tw_how<N, PT>(I)>(c.w[I - 1]);
     }
     if constexpr (I < E::L) tw_cache_fill<N, PT, I + 1, ALL>(c, p, tw);
 }
@@ -305,32 +335,37 @@ __device__ __forceinline__ void tw_cache_load(TwCache<N, PT, ALL>& c, const Pos&
     tw_cache_fill<N, PT, 1, ALL>(c, p, tw);
 }
 
-template <bool INV>
-__device__ __forceinline__ cd cmul_tw(cd a, cd w) {
-    return INV ? cd{__builtin_fma(a.x, w.x, a.y * w.y), __builtin_fma(a.y, w.x, -(a.x * w.y))} : cmul(a, w);
-}
-
 // Apply w^(k r) to element r of butterfly i (elements in slots i + r NB), from the cache.
-template <int R, int NB, bool INV, bool ALL = false>
+template <int R, int NB, bool INV, bool ALL, Powers HOW>
 __device__ __forceinline__ void apply_twiddles(cd* v, int i, const cd* base) {
     if constexpr (ALL) {
 #pragma unroll
         for (int m = 1; m < R; ++m) v[i + m * NB] = cmul_tw<INV>(v[i + m * NB], base[m - 1]);
         return;
     }
+    constexpr int LR = ilog2(R);
     const cd w1 = opaque(base[0]);
     v[i + NB] = cmul_tw<INV>(v[i + NB], w1);
     if constexpr (R >= 4) {
         const cd w2 = opaque(base[1]);
-        const cd w3 = cmul(w1, w2);
+        const cd w3 = HOW == WITH_W3 || HOW == TURNED_4 ? opaque(base[LR])
+                      : HOW == TURNED_2                 ? cmul_tw<true>(opaque(base[2]), w1)
+                                                        : cmul(w1, w2);
         v[i + 2 * NB] = cmul_tw<INV>(v[i + 2 * NB], w2);
         v[i + 3 * NB] = cmul_tw<INV>(v[i + 3 * NB], w3);
         if constexpr (R >= 8) {
             const cd w4 = opaque(base[2]);
             v[i + 4 * NB] = cmul_tw<INV>(v[i + 4 * NB], w4);
-            v[i + 5 * NB] = cmul_tw<INV>(v[i + 5 * NB], cmul(w1, w4));
-            v[i + 6 * NB] = cmul_tw<INV>(v[i + 6 * NB], cmul(w2, w4));
-            v[i + 7 * NB] = cmul_tw<INV>(v[i + 7 * NB], cmul(w3, w4));
+            if constexpr (HOW == TURNED_4) {
+                const cd w8 = opaque(base[LR + 1]);
+                v[i + 5 * NB] = cmul_tw<INV>(v[i + 5 * NB], cmul_tw<true>(w8, w3));
+                v[i + 6 * NB] = cmul_tw<INV>(v[i + 6 * NB], cmul_tw<true>(w8, w2));
+                v[i + 7 * NB] = cmul_tw<INV>(v[i + 7 * NB], cmul_tw<true>(w8, w1));
+            } else {
+                v[i + 5 * NB] = cmul_tw<INV>(v[i + 5 * NB], cmul(w1, w4));
+                v[i + 6 * NB] = cmul_tw<INV>(v[i + 6 * NB], cmul(w2, w4));
+                v[i + 7 * NB] = cmul_tw<INV>(v[i + 7 * NB], cmul(w3, w4));
+            }
             if constexpr (R >= 16) {
                 const cd w8 = opaque(base[3]);
                 v[i + 8 * NB] = cmul_tw<INV>(v[i + 8 * NB], w8);
@@ -516,17 +551,17 @@ __device__ __forceinline__ void fft_fwd(cd* v, cd* ex, const TwCache<N, PT, ALL>
     if constexpr (E::F > 1) {
         dft_f<PT, E::F, false>(v);
         swap_f<PT, E::F>(v);
-        apply_twiddles<PT, 1, false, ALL>(v, 0, c.w[0]);
+        apply_twiddles<PT, 1, false, ALL, tw_how<N, PT>(1)>(v, 0, c.w[0]);
     }
     dft_pt<PT, false>(v);
     if constexpr (E::L >= 2) {
         exchange<N, PT, XLOW, 1, true>(v, ex, p);
-        apply_twiddles<PT, 1, false, ALL>(v, 0, c.w[1]);
+        apply_twiddles<PT, 1, false, ALL, tw_how<N, PT>(2)>(v, 0, c.w[1]);
         dft_pt<PT, false>(v);
     }
     if constexpr (E::L >= 3) {
         exchange<N, PT, XLOW, 2, true>(v, ex, p);
-        apply_twiddles<PT, 1, false, ALL>(v, 0, c.w[2]);
+        apply_twiddles<PT, 1, false, ALL, tw_how<N, PT>(3)>(v, 0, c.w[2]);
         dft_pt<PT, false>(v);
     }
 }
@@ -537,17 +572,17 @@ __device__ __forceinline__ void fft_inv(cd* v, cd* ex, const TwCache<N, PT, ALL>
     using E = Fft<N, PT, XLOW>;
     dft_pt<PT, true>(v);
     if constexpr (E::L >= 3) {
-        apply_twiddles<PT, 1, true, ALL>(v, 0, c.w[2]);
+        apply_twiddles<PT, 1, true, ALL, tw_how<N, PT>(3)>(v, 0, c.w[2]);
         exchange<N, PT, XLOW, 2, false>(v, ex, p);
         dft_pt<PT, true>(v);
     }
     if constexpr (E::L >= 2) {
-        apply_twiddles<PT, 1, true, ALL>(v, 0, c.w[1]);
+        apply_twiddles<PT, 1, true, ALL, tw_how<N, PT>(2)>(v, 0, c.w[1]);
         exchange<N, PT, XLOW, 1, false>(v, ex, p);
         dft_pt<PT, true>(v);
     }
     if constexpr (E::F > 1) {
-        apply_twiddles<PT, 1, true, ALL>(v, 0, c.w[0]);
+        apply_twiddles<PT, 1, true, ALL, tw_how<N, PT>(1)>(v, 0, c.w[0]);
         swap_f<PT, E::F>(v);
         dft_f<PT, E::F, true>(v);
     }

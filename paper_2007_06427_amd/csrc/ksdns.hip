@@ -138,12 +138,12 @@ __device__ __forceinline__ void nonlinear(const cd (&v)[3], const double (&hs)[3
     // lo::fft_inv with the zero inputs left out
     dft8_inv_low3(w);
     if constexpr (E::L >= 2) {
-        lo::apply_twiddles<8, 1, true, true>(w, 0, c.w[1]);
+        lo::apply_twiddles<8, 1, true, true, lo::FORMED>(w, 0, c.w[1]);
         lo::exchange<NX, 8, false, 1, false>(w, ex, p);
         lo::dft_pt<8, true>(w);
     }
     if constexpr (E::F > 1) {
-        lo::apply_twiddles<8, 1, true, true>(w, 0, c.w[0]);
+        lo::apply_twiddles<8, 1, true, true, lo::FORMED>(w, 0, c.w[0]);
         lo::swap_f<8, E::F>(w);
         lo::dft_f<8, E::F, true>(w);
     }
@@ -154,7 +154,7 @@ __device__ __forceinline__ void nonlinear(const cd (&v)[3], const double (&hs)[3
         dft8_fwd_real(g, w);
         if constexpr (E::L >= 2) {
             lo::exchange<NX, 8, false, 1, true>(w, ex, p);
-            lo::apply_twiddles<8, 1, false, true>(w, 0, c.w[1]);
+            lo::apply_twiddles<8, 1, false, true, lo::FORMED>(w, 0, c.w[1]);
             lo::dft_pt<8, false>(w);
         }
     } else {
@@ -198,12 +198,15 @@ __global__ __launch_bounds__(64) void k_ks_etdrk4(double L, int sym, double h, i
         const int span = i == 0 ? D::E::F : D::E::F * 8;  // as lo::tw_cache_load, at most two stages
         const int ti = i == D::E::L - 1 ? p.t : p.f0;
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {
+        for (int m : {1, 2, 3, 4, 8}) {
             double sn, cs;
-            sincospi(-2.0 * (double)(ti << b) / (double)(span * 8), &sn, &cs);
-            twc.w[i][(1 << b) - 1] = cd{cs, sn};
+            sincospi(-2.0 * (double)(ti * m) / (double)(span * 8), &sn, &cs);
+            twc.w[i][m - 1] = cd{cs, sn};
         }
-        lo::tw_powers(twc.w[i]);
+        if (i == 0)
+            lo::tw_powers<D::E::F == 4 ? lo::TURNED_4 : lo::WITH_W3>(twc.w[i]);  // F = 2: w^4 is a quarter turn
+        else
+            lo::tw_powers<lo::WITH_W3>(twc.w[i]);
     }
     __syncthreads();
     Etd co[3];
