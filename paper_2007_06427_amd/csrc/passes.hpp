@@ -459,12 +459,13 @@ struct RowG {
     static constexpr int TILE = CMAX * TS;
 };
 
-// Rows of 64 to 512 points keep the twiddle powers (TwCache): they are bound by the vector units'
+// Rows of 32 to 512 points keep the twiddle powers (TwCache): they are bound by the vector units'
 // issue rate, and the registers cost them no wavefront (pass B of 64 loops of 256 x 1024 went
 // from 137 to 168, three wavefronts per SIMD either way, and from 54.3 us to 49.5; pass D 59.7
-// to 58.7). Eight points per thread; the 1024-point rows hold 16 and have no registers left.
+// to 58.7; pass B of 32-point rows holds 92 so, 110 when each transform forms them, five and four
+// wavefronts: a step of 256 ragged loops 38.6 and 40.1 us). Eight points per thread; the 1024-point rows hold 16 and have no registers left.
 template <int M, int PT = RowG<M>::PT>
-constexpr bool kRowAll = PT == 8 && M >= 64 && M <= 512;
+constexpr bool kRowAll = PT == 8 && M >= 32 && M <= 512;
 
 // Item k of a thread: pair p and column j, consecutive lanes on consecutive pairs.
 template <class G>
